@@ -436,19 +436,6 @@ void fill_tiles(int32_t* pfx, const int64_t* G, int q, int tile) {
   for (int g = 0; g < q; ++g) pfx[g + 1] = pfx[g] + tiles_of(G[g + 1] - G[g], tile);
 }
 
-// One workgroup per CU at most (each uses 96-128 KB of LDS); a multiple of
-// 8 so that every XCD gets the same number of workgroups.
-int persistent_grid(int64_t upper_tiles) {
-  const int64_t cap = static_cast<int64_t>(cu_count());
-  int64_t g = std::min<int64_t>(std::max<int64_t>(upper_tiles, 1), cap);
-  g = (g + 7) / 8 * 8;
-  return static_cast<int>(g);
-}
-
-// Column-tile width of the fp32 kernel's forward and activation-gradient
-// tiles: 128 columns.
-constexpr int kFp32NW = 2;
-
 star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_ERR_HIP; }
 
 // bf16 operands take the kernel fed by direct global-to-LDS copies (its
@@ -498,8 +485,7 @@ hipError_t launch_narrow(NarrowParams& pn, hipStream_t stream) {
   return launch_gemm_narrow(pn, gemm_narrow_row_blocks_upper(pn.M, pn.q), pn.NTp[pn.q], cu_count(), stream);
 }
 
-hipError_t launch_proj_gemm(int mode, const GemmParams& p, int nw, int64_t upper,
-                            hipStream_t stream) {
+hipError_t launch_proj_gemm(int mode, const GemmParams& p, hipStream_t stream) {
   if (mode == kModeFwd && use_narrow_fwd(p)) {
     NarrowParams pn;
     std::memset(&pn, 0, sizeof(pn));
@@ -540,7 +526,7 @@ hipError_t launch_proj_gemm(int mode, const GemmParams& p, int nw, int64_t upper
     const int64_t rows_upper = static_cast<int64_t>(p.M) / kTileM + p.q;
     return launch_gemm_async(mode, pa, rows_upper * pa.NTp[p.q], cu_count(), stream);
   }
-  return launch_gemm(mode, p, nw, persistent_grid(upper), stream);
+  return launch_gemm(mode, p, stream);
 }
 
 star_status run_plan(const int32_t* row_type, int64_t M, int q, void* ws, const PlanWs& pw,
@@ -584,11 +570,7 @@ star_status run_fwd(const Alg& a, int64_t M, const int32_t* perm, const int32_t*
   p.Z = Z;
   p.Y = Y;
   p.ydtype = yt;
-  const int64_t rows_upper = M / kTileM + a.q;
-  const int nw = kFp32NW;
-  fill_tiles(p.NTp, a.R, a.q, 64 * nw);
-  const int64_t upper = rows_upper * static_cast<int64_t>(p.NTp[a.q]);
-  star_status st = hip_status(launch_proj_gemm(kModeFwd, p, nw, upper, stream));
+  star_status st = hip_status(launch_proj_gemm(kModeFwd, p, stream));
   // graph law: the output groups that are not slots of a row's type
   if (st == STAR_OK && a.law == STAR_LAW_GRAPH) st = hip_status(launch_graph_fill(kModeFwd, p, stream));
   return st;
@@ -776,11 +758,7 @@ star_status star_proj_bwd_data_planned(const star_algebra* alg, int64_t M, const
   p.act = Z_prev ? act_prev : STAR_ACT_NONE;
   p.Y = dX;
   p.ydtype = dxt;
-  const int64_t rows_upper = M / kTileM + a.q;
-  const int nw = kFp32NW;
-  fill_tiles(p.NTp, a.S, a.q, 64 * nw);
-  const int64_t upper = rows_upper * static_cast<int64_t>(p.NTp[a.q]);
-  st = hip_status(launch_proj_gemm(kModeBwdData, p, nw, upper, stream));
+  st = hip_status(launch_proj_gemm(kModeBwdData, p, stream));
   // graph law: zero gradient for the input groups that are not slots
   if (st == STAR_OK && a.law == STAR_LAW_GRAPH) st = hip_status(launch_graph_fill(kModeBwdData, p, stream));
   return st;
@@ -865,8 +843,6 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
     if (st != STAR_OK) return st;
     return hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream));
   }
-  fill_tiles(p.NTp, a.R, a.q, 64 * kBwdWeightNW);
-  fill_tiles(p.MTp, a.S, a.q, kTileM);
   p.A = X;
   p.B = dY;
   p.dW = dW;
@@ -878,8 +854,7 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
     p.partial = at<float>(ws, bw.partial);
     p.dbias_part = at<float>(ws, bw.dbias_part);
   }
-  const int64_t upper = static_cast<int64_t>(p.MTp[a.q]) * p.NTp[a.q] * p.nsplit;
-  st = hip_status(launch_gemm(kModeBwdWeight, p, kBwdWeightNW, persistent_grid(upper), stream));
+  st = hip_status(launch_gemm(kModeBwdWeight, p, stream));
   if (st == STAR_OK && bw.nsplit > 1) st = hip_status(launch_split_reduce(p, stream));
   if (st != STAR_OK || a.law != STAR_LAW_GRAPH || !dbias) return st;
   const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);

@@ -1,13 +1,11 @@
 // Grouped, row-typed GEMM on gfx950 MFMA for fp32 operands: the forward
 // projection, its activation gradient and its weight gradient (Alg. 1 and
-// the VJPs of the appendix) in one persistent kernel template.  bf16
-// operands run in the pipelined kernel of gemm_async.hip.
+// the VJPs of the appendix) in one kernel template.  bf16 operands run in
+// the pipelined kernel of gemm_async.hip.
 //
-// Work decomposition.  C is cut into tiles of 256 rows x BN columns
-// (BN = 64 * WN, WN = 2).  A workgroup of 4 wavefronts (one per
-// SIMD) computes a tile; the wavefronts form a 2 x 2 grid and each owns
-// 128 x (32 * WN) of C as 4 x WN blocks of v_mfma_f32_32x32x16_bf16 (or of
-// v_mfma_f32_32x32x2f32 for fp32 operands), accumulated in AGPRs.
+// Work decomposition.  C is cut into tiles of 64 rows x 64 columns.  A
+// workgroup of 4 wavefronts (2 x 2) computes a tile, each wave one 32 x 32
+// block with v_mfma_f32_32x32x2f32.
 //
 //  * FWD: a tile is (row type i, row tile of I_i, output group j, column
 //    tile).  Its K range is the concatenation of the input groups in
@@ -27,34 +25,46 @@
 //    second kernel sums in a fixed order.  The bias gradient is summed from
 //    the dY tiles that the diagonal tiles already stage.
 //
-// Scheduling.  The kernel is persistent: one workgroup per CU walks its
-// share of the tile list.  Tiles with the longer contraction come first
-// (pass 0), the shorter ones after (pass 1).  Within a pass the list is cut
-// into 8 contiguous chunks, one per XCD (workgroups are dispatched
-// round-robin over the 8 XCDs), and consecutive tiles of a chunk share
-// their weight panel, so the tiles running together on one XCD hit the same
-// L2.  A workgroup runs its tiles as one flat sequence of K steps: while the
-// last step of a tile computes, the first step of the next tile (whose row
-// indices were fetched a whole tile earlier) is already being loaded.
+// What bounds it: the fp32 matrix rate (157 TFLOP/s nominal; a 4096^3
+// library product reaches 138).  An fp32 MFMA of 32 x 32 x 2 holds its SIMD
+// for 64 cycles and takes one float per lane and operand, so LDS reads are
+// far from a limit (32 bytes a clock of 128) and neither operand needs a
+// transposed copy: a 4-byte read per lane and K index serves an operand that
+// is contiguous along the tile rows.  What matters is that every SIMD has a
+// tile: small tiles, three workgroups per CU, and operands copied ahead.
+// Against 256 x 128 tiles staged through registers by one workgroup per CU
+// (1111 rows of three types, 768 <-> 2304: 40 to 100 workgroups on the
+// chip): forward 162 and 386 -> 33 us, activation gradients 192 and 460 ->
+// 52 us, weight gradients 416 -> 43 us each.  128 x 128 tiles of the same
+// kernel: 10 % faster on 4096 x 1024 x 4096 (311 against 351 us), three
+// times slower where the long contractions are few (172 against 52 us), so
+// they are not built.
 //
-// LDS layout.  Each K step stages 8 "kpacks" (16 bytes of K: 8 bf16 or 4
-// fp32) per tile row, double-buffered.  A tile is stored kpack-major:
-// unit (kp, row) holds the 16 bytes of K of that row, at
-// (kp * rows + swz(row, kp)) * 16, where swz XORs the low three bits of the
-// row with bits 3..5 of the row and the kpack index.  With it the three
-// access patterns are free of bank conflicts: the MFMA operand read (32
-// consecutive rows, one kpack), the direct store of K-contiguous rows
-// (8 kpacks of one row from 8 lanes) and the transposed store.  Operands
-// that are contiguous along the tile rows (W in the forward product, X and
-// dY in the weight gradient) are transposed in registers on the way: each
-// thread loads 4 source rows x 16 bytes and writes one 4-element piece per
-// tile row.  Fragments for the next 16-wide K slice are read from LDS while
-// the MFMAs of the current slice run.
+// Operands go from global memory straight into LDS (16 bytes per lane, 1 KB
+// per copy instruction) in steps of 32 K elements, two steps ahead of the
+// one being multiplied, in a ring of three 16 KB stages.  A wait counts the
+// copies still allowed in flight, so a step never drains the ring; a step's
+// copies go between its MFMAs (issued in a burst ahead of them: 4096 x 1024
+// x 4096 weight gradient 390 -> 335 us).
+//
+// LDS layout of a stage.  K-contiguous operand (X and dY rows, W^T): 128
+// bytes a row, 16-byte chunk c of row r at c ^ ((r >> 1) & 7).  Operand
+// contiguous along the tile rows (W in the forward, X and dY in the weight
+// gradient): one K index a row, its 16-byte chunks rotated by 8 for every
+// other group of 4 K indexes, so the two lane halves of a 4-byte read sit
+// in different halves of the 64 banks.
+//
+// Scheduling.  Each pass's tiles (pass 0: the longer contractions) are cut
+// into 8 contiguous chunks, one per XCD (workgroups are dispatched
+// round-robin over the 8 XCDs); consecutive tiles of a chunk share rows and
+// weight panels in that XCD's L2.
 //
 // Epilogue.  The MFMA is issued with the operands swapped (it computes
 // C^T blocks), so each lane ends with 4 consecutive columns of one row of
-// C and writes them as one 8- or 16-byte store.  The activation and its
+// C and writes them as one 16-byte store.  The activation and its
 // derivative are the shared ones of common.hpp.
+#include <algorithm>
+
 #include "gemm_common.hpp"
 
 namespace starq {
@@ -63,459 +73,339 @@ namespace {
 
 using namespace gemm;
 
-// ---- operand staging -----------------------------------------------------
+constexpr int kThreads = 256;        // 4 wavefronts, 2 x 2 over a tile
+constexpr int TM = 64, TN = 64;      // tile of C
+constexpr int BK = 32;               // K elements per step (128 bytes)
+constexpr int kStages = 3;           // LDS ring
+constexpr int kAhead = kStages - 1;  // steps copied ahead
+constexpr int kABytes = TM * BK * 4;
+constexpr int kStageBytes = kABytes + TN * BK * 4;  // 16 KB
+constexpr int kPerCU = 3;                           // workgroups per CU
+constexpr int CA = TM / 32, CB = TN / 32;           // copies per wave and step
+constexpr int kChunks = 16;                         // 16-byte chunks per K index of a row-contiguous operand
+static_assert(TM == 4 * kChunks && TN == 4 * kChunks && CA == CB, "one copy layout for both operands");
 
-// K-contiguous source rows.  Unit u = tid + THREADS * i covers kpack u % 8
-// of tile row u / 8 (8 lanes read one 128-byte row segment).
-template <typename T, int ROWS>
-struct DirectLoader {
-  static constexpr int VEC = Tr<T>::VEC;
-  static constexpr int UPT = ROWS * 8 / THREADS;
-  static_assert(UPT * THREADS == ROWS * 8, "whole units per thread");
-  uint4 reg[UPT];
+#define STARQ_LDS __attribute__((address_space(3)))
 
-  __device__ __forceinline__ static int row_of(int i) { return (threadIdx.x + THREADS * i) >> 3; }
-  __device__ __forceinline__ static int kp_of() { return threadIdx.x & 7; }
+// 256 zero bytes: the source of every copy past a step's K range
+__device__ __attribute__((aligned(256))) uint32_t g_f32_zero[64];
 
-  __device__ __forceinline__ void load(const T* __restrict__ src, int64_t ld, const int32_t* rowid,
-                                       int32_t k0, int32_t kend) {
-    const int32_t kk = k0 + kp_of() * VEC;
+// 16 (dma16) or 4 (dma4) bytes per lane from global memory into LDS at
+// lds_addr + 16 * lane (4 * lane); issued as assembly so that the compiler
+// does not wait for the copies in flight before every LDS read.
+__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma4(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+__device__ __forceinline__ void block_barrier() {
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(p)));
+}
+
+// Chunk of K-contiguous row r, and of K index k of a row-contiguous operand.
+__device__ __forceinline__ int kc_chunk(int r, int c) { return c ^ ((r >> 1) & 7); }
+__device__ __forceinline__ int rc_chunk(int k, int c) { return c ^ (8 * ((k >> 2) & 1)); }
+
+// The four K values 4 (2 rs + lh) .. + 3 of tile row `row` (lane half lh
+// supplies K element 4 kp + e of MFMA e; both operands use the same
+// assignment, so the products pair up).
+template <bool KC>
+__device__ __forceinline__ void read_frag(const char* tile, int rs, int lh, int row, float (&f)[4]) {
+  if constexpr (KC) {
+    const float4 v = *reinterpret_cast<const float4*>(tile + row * 128 + kc_chunk(row, 2 * rs + lh) * 16);
+    f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+  } else {
 #pragma unroll
-    for (int i = 0; i < UPT; ++i)
-      reg[i] = load16(src, static_cast<int64_t>(rowid[i]) * ld + kk, rowid[i] >= 0 && kk < kend);
-  }
-  __device__ __forceinline__ void store(char* lds) const {
-#pragma unroll
-    for (int i = 0; i < UPT; ++i)
-      *reinterpret_cast<uint4*>(lds + unit_off<ROWS>(kp_of(), row_of(i))) = reg[i];
-  }
-};
-
-// Source contiguous along the tile rows (a source row is one K index).
-// Block b = tid + THREADS * i covers source rows 4 q .. 4 q + 3 (q = b / CB)
-// and tile rows VEC c .. VEC c + VEC - 1 (c = b % CB).
-template <typename T, int ROWS>
-struct TransLoader {
-  static constexpr int VEC = Tr<T>::VEC;
-  static constexpr int CB = ROWS / VEC;
-  static constexpr int NQ = Tr<T>::BK / 4;
-  static constexpr int BPT = CB * NQ / THREADS;
-  static_assert(BPT * THREADS == CB * NQ, "whole blocks per thread");
-  static_assert(THREADS % CB == 0, "a thread keeps its column chunk across blocks");
-  uint4 reg[BPT][4];
-
-  __device__ __forceinline__ static int cb_of() { return threadIdx.x % CB; }
-  __device__ __forceinline__ static int q_of(int i) { return (threadIdx.x + THREADS * i) / CB; }
-
-  template <typename RowFn>
-  __device__ __forceinline__ void load(const T* __restrict__ src, int64_t ld, int32_t k0, int32_t c0,
-                                       int32_t cend, RowFn srow) {
-    const int32_t col = c0 + cb_of() * VEC;
-#pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        const int32_t row = srow(k0 + 4 * q_of(i) + e);
-        reg[i][e] = load16(src, static_cast<int64_t>(row) * ld + col, row >= 0 && col < cend);
-      }
+    for (int e = 0; e < 4; ++e) {
+      const int k = 8 * rs + 4 * lh + e;
+      f[e] = *reinterpret_cast<const float*>(tile + k * (16 * kChunks) + rc_chunk(k, row >> 2) * 16 + (row & 3) * 4);
     }
-  }
-
-  // optionally adds the staged values into per-column sums colsum[v]
-  template <bool kSum>
-  __device__ __forceinline__ void store(char* lds, float* colsum) const {
-#pragma unroll
-    for (int i = 0; i < BPT; ++i) {
-      const int kbase = 4 * q_of(i);
-      const int kp = kbase / VEC;
-      const int boff = (kbase % VEC) * static_cast<int>(sizeof(T));
-#pragma unroll
-      for (int v = 0; v < VEC; ++v) {
-        const int row = cb_of() * VEC + v;
-        char* dst = lds + unit_off<ROWS>(kp, row) + boff;
-        if constexpr (sizeof(T) == 2) {
-          const int w = v >> 1, sh = (v & 1) * 16;
-          const uint32_t e0 = (word_of(reg[i][0], w) >> sh) & 0xffffu;
-          const uint32_t e1 = (word_of(reg[i][1], w) >> sh) & 0xffffu;
-          const uint32_t e2 = (word_of(reg[i][2], w) >> sh) & 0xffffu;
-          const uint32_t e3 = (word_of(reg[i][3], w) >> sh) & 0xffffu;
-          *reinterpret_cast<uint2*>(dst) = make_uint2(e0 | (e1 << 16), e2 | (e3 << 16));
-          if constexpr (kSum)
-            colsum[v] += (bf16_to_f32(e0) + bf16_to_f32(e1)) + (bf16_to_f32(e2) + bf16_to_f32(e3));
-        } else {
-          const uint4 piece = make_uint4(word_of(reg[i][0], v), word_of(reg[i][1], v),
-                                         word_of(reg[i][2], v), word_of(reg[i][3], v));
-          *reinterpret_cast<uint4*>(dst) = piece;
-          if constexpr (kSum)
-            colsum[v] += (__uint_as_float(piece.x) + __uint_as_float(piece.y)) +
-                         (__uint_as_float(piece.z) + __uint_as_float(piece.w));
-        }
-      }
-    }
-  }
-};
-
-template <int MODE, typename T, int WN> struct OperandLoaders;
-template <typename T, int WN> struct OperandLoaders<kModeFwd, T, WN> {
-  using A = DirectLoader<T, BM>;
-  using B = TransLoader<T, Geo<WN>::BN>;
-};
-template <typename T, int WN> struct OperandLoaders<kModeBwdData, T, WN> {
-  using A = DirectLoader<T, BM>;
-  using B = DirectLoader<T, Geo<WN>::BN>;
-};
-template <typename T, int WN> struct OperandLoaders<kModeBwdWeight, T, WN> {
-  using A = TransLoader<T, BM>;
-  using B = TransLoader<T, Geo<WN>::BN>;
-};
-
-// Eight K steps of 16 (bf16) or 8 (fp32) per LDS stage: 4 slices, each one
-// kpack per lane half.  Fragments of slice rs + 1 are read while the MFMAs
-// of slice rs issue.
-template <typename T, int WN>
-__device__ __forceinline__ void compute_step(const char* As, const char* Bs, f32x16_t (&acc)[4][WN]) {
-  constexpr int BN = Geo<WN>::BN;
-  const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
-  const int wm = wave >> 1, wn = wave & 1;
-  const int lr = lane & 31, lh = lane >> 5;
-  uint4 fa[2][4], fb[2][WN];
-  auto read = [&](int rs, int set) {
-    const int kp = 2 * rs + lh;
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-      fa[set][mi] = *reinterpret_cast<const uint4*>(As + unit_off<BM>(kp, wm * 128 + mi * 32 + lr));
-#pragma unroll
-    for (int ni = 0; ni < WN; ++ni)
-      fb[set][ni] = *reinterpret_cast<const uint4*>(Bs + unit_off<BN>(kp, wn * (32 * WN) + ni * 32 + lr));
-  };
-  read(0, 0);
-#pragma unroll
-  for (int rs = 0; rs < 4; ++rs) {
-    if (rs + 1 < 4) read(rs + 1, (rs + 1) & 1);
-#pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < WN; ++ni) mma(acc[mi][ni], fb[rs & 1][ni], fa[rs & 1][mi], T());
-  }
-  // Pin the pipeline order for the scheduler: the reads of slice 0 and 1,
-  // then each slice's MFMAs followed by the reads of the slice after next.
-  constexpr int kReads = 4 + WN;
-  constexpr int kMfma = 4 * WN * (sizeof(T) == 2 ? 1 : 4);
-  __builtin_amdgcn_sched_group_barrier(0x100, 2 * kReads, 0);
-#pragma unroll
-  for (int rs = 0; rs < 4; ++rs) {
-    __builtin_amdgcn_sched_group_barrier(0x008, kMfma, 0);
-    if (rs + 2 < 4) __builtin_amdgcn_sched_group_barrier(0x100, kReads, 0);
   }
 }
 
-// Gathered row indices a thread needs for one FWD/BWD_DATA tile: the rows
-// of its direct A loads and the rows its epilogue writes.
-template <int UPT>
-struct Rows {
-  int32_t a[UPT];
-  int32_t e[4];
-};
+template <int MODE, int LAW>
+__global__ __launch_bounds__(kThreads, kPerCU) void star_gemm_f32_kernel(const GemmParams p) {
+  constexpr bool kAKC = MODE != kModeBwdWeight;  // A K-contiguous
+  constexpr bool kBKC = MODE == kModeBwdData;    // B K-contiguous
+  // a step's copies of one wave: operands, and the weight gradient's perm
+  // entries of a later step
+  constexpr int kGroup = CA + CB + (MODE == kModeBwdWeight ? 1 : 0);
+  __shared__ __attribute__((aligned(256))) char smem[kStages * kStageBytes];
+  // weight gradient: rows (perm entries) of the positions of a step, for
+  // each wave alone (copied 2 kAhead steps ahead, read kAhead steps ahead)
+  constexpr int kRowSlots = 4;
+  static_assert(kAhead + 1 <= kRowSlots, "perm ring");
+  __shared__ __attribute__((aligned(16))) int32_t prow_s[MODE == kModeBwdWeight ? 4 : 1][kRowSlots][64];
 
-template <int UPT>
-__device__ __forceinline__ void fetch_rows(const GemmParams& p, const Tile& t, Rows<UPT>& r) {
-  const int lane = threadIdx.x & 63;
-  const int wm = (threadIdx.x >> 6) >> 1;
-#pragma unroll
-  for (int i = 0; i < UPT; ++i) {
-    const int row = (threadIdx.x + THREADS * i) >> 3;
-    r.a[i] = row < t.nrows ? p.perm[t.pos0 + row] : -1;
-  }
-#pragma unroll
-  for (int mi = 0; mi < 4; ++mi) {
-    const int row = wm * 128 + mi * 32 + (lane & 31);
-    r.e[mi] = row < t.nrows ? p.perm[t.pos0 + row] : -1;
-  }
-}
-
-template <typename T, int MODE, int LAW, int WN>
-__global__ __launch_bounds__(THREADS, 1) void star_gemm_kernel(const GemmParams p) {
-  using G = Geo<WN>;
-  using LA = typename OperandLoaders<MODE, T, WN>::A;
-  using LB = typename OperandLoaders<MODE, T, WN>::B;
-  constexpr int BK = Tr<T>::BK;
-  constexpr int BN = G::BN;
-  constexpr int VEC = Tr<T>::VEC;
-  constexpr int UPT = DirectLoader<T, BM>::UPT;  // row ids of the gathered A rows
-  constexpr int BUPT = DirectLoader<T, BN>::UPT;   // BWD_DATA: rows of W per thread
-  extern __shared__ __attribute__((aligned(16))) char smem[];
-  __shared__ int32_t units_s[kMaxQGroups];
-  __shared__ int32_t pfx_s[2][kMaxQGroups + 1];
-
-  auto As = [&](int buf) { return smem + buf * G::STAGE; };
-  auto Bs = [&](int buf) { return smem + buf * G::STAGE + G::A_BYTES; };
-  const T* __restrict__ Ag = static_cast<const T*>(p.A);
-  const T* __restrict__ Bg = static_cast<const T*>(p.B);
+  const float* __restrict__ Ag = static_cast<const float*>(p.A);
+  const float* __restrict__ Bg = static_cast<const float*>(p.B);
+  const void* zero = g_f32_zero;
   const int q = p.q;
   const int lane = threadIdx.x & 63;
-  const int wave = threadIdx.x >> 6;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int wm = wave >> 1, wn = wave & 1;
   const int lr = lane & 31, lh = lane >> 5;
+  const uint32_t lds0 = lds_addr(smem);
 
-  for (int i = threadIdx.x; i < q; i += THREADS) {
-    if constexpr (MODE == kModeBwdWeight) {
-      units_s[i] = (p.MTp[i + 1] - p.MTp[i]) * p.nsplit;
-    } else {
-      const int32_t mi = p.offsets[i + 1] - p.offsets[i];
-      units_s[i] = (mi + BM - 1) / BM;
-    }
+  // ---- tiles per class and pass: lane i holds class i (q <= 64) ----
+  int32_t units = 0, cnt[2] = {0, 0}, pfx[2];
+  if (lane < q) {
+    if constexpr (MODE == kModeBwdWeight) units = (p.MTp[lane + 1] - p.MTp[lane]) * p.nsplit;
+    else units = (p.offsets[lane + 1] - p.offsets[lane] + TM - 1) / TM;
+#pragma unroll
+    for (int ps = 0; ps < 2; ++ps) cnt[ps] = units * ncols_sel(p, sel_for(MODE, LAW, ps), lane);
   }
-  __syncthreads();
-  if (threadIdx.x < 2) {
-    const int sel = sel_for(MODE, LAW, threadIdx.x);
-    int32_t run = 0;
-    for (int i = 0; i < q; ++i) {
-      pfx_s[threadIdx.x][i] = run;
-      run += units_s[i] * ncols_sel(p, sel, i);
+  int32_t chunk[2], total[2];
+#pragma unroll
+  for (int ps = 0; ps < 2; ++ps) {
+    int32_t v = cnt[ps];
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int32_t u = __shfl_up(v, o);
+      if (lane >= o) v += u;
     }
-    pfx_s[threadIdx.x][q] = run;
+    pfx[ps] = v;  // inclusive
+    total[ps] = __builtin_amdgcn_readlane(v, 63);
+    chunk[ps] = (total[ps] + 7) >> 3;
   }
-  __syncthreads();
-
-  // ---- this workgroup's tile sequence ----
   const int xcd = blockIdx.x & 7;
-  const int slot_stride = gridDim.x >> 3;
-  int it_pass = 0;
-  int32_t it_slot = blockIdx.x >> 3;
 
-  // zero tile of a weight-gradient split with an empty row range
-  auto write_zero_tile = [&](const Tile& t) {
-    float* out = p.nsplit > 1 ? p.partial + static_cast<int64_t>(t.split) * p.K * p.N : p.dW;
-    for (int idx = threadIdx.x; idx < BM * BN / 4; idx += THREADS) {
-      const int32_t r = t.rstart + idx / (BN / 4);
-      const int32_t c = t.cstart + (idx % (BN / 4)) * 4;
-      if (r < t.rend && c < t.cend)
-        *reinterpret_cast<float4*>(out + static_cast<int64_t>(r) * p.N + c) = make_float4(0, 0, 0, 0);
+  for (int32_t slot = blockIdx.x >> 3; slot < chunk[0] + chunk[1]; slot += gridDim.x >> 3) {
+    const int ps = slot < chunk[0] ? 0 : 1;
+    const int32_t logical = xcd * chunk[ps] + (ps == 0 ? slot : slot - chunk[0]);
+    if (logical >= total[ps]) continue;
+    const int32_t mypfx = ps == 0 ? pfx[0] : pfx[1];
+    const int cls = __popcll(__ballot(mypfx <= logical));
+    const int32_t before = __builtin_amdgcn_readlane(mypfx - (ps == 0 ? cnt[0] : cnt[1]), cls);
+    const Tile t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - before,
+                                                __builtin_amdgcn_readlane(units, cls), p.offsets, TM);
+
+    // ---- copy sources of this tile ----
+    // K-contiguous A: the lane's row of copy j (rows past the tile's end read
+    // its first row; their products are not stored)
+    int32_t arow[CA], brow[CB];
+    const int kslot = (lane & 7) ^ ((4 * (wave & 1) + (lane >> 4)) & 7);  // chunk of every K-contiguous copy
+    if constexpr (kAKC) {
+#pragma unroll
+      for (int j = 0; j < CA; ++j) {
+        const int row = 8 * (wave + 4 * j) + (lane >> 3);
+        arow[j] = p.perm[t.pos0 + (row < t.nrows ? row : 0)];
+      }
     }
-    if (t.do_dbias) {
-      for (int c = threadIdx.x; c < BN; c += THREADS) {
-        const int32_t gc = t.cstart + c;
-        if (gc < t.cend) {
-          if (p.nsplit > 1) p.dbias_part[static_cast<int64_t>(t.split) * p.N + gc] = 0.f;
-          else p.dbias[gc] = 0.f;
+    if constexpr (kBKC) {
+#pragma unroll
+      for (int j = 0; j < CB; ++j) {
+        const int row = 8 * (wave + 4 * j) + (lane >> 3);
+        brow[j] = t.cstart + (t.cstart + row < t.cend ? row : 0);
+      }
+    }
+    // row of C this lane writes, -1 for none
+    int32_t erow = -1;
+    {
+      const int row = 32 * wm + lr;
+      if constexpr (MODE != kModeBwdWeight) erow = row < t.nrows ? p.perm[t.pos0 + row] : -1;
+      else erow = t.rstart + row < t.rend ? t.rstart + row : -1;
+    }
+
+    // weight gradient: the rows at the positions of step s, into this wave's
+    // perm slot (zeros past the step's range)
+    auto copy_perm = [&](int32_t s) {
+      if constexpr (MODE == kModeBwdWeight) {
+        int32_t k0 = 0, kend = 0;
+        if (s < t.nsteps) step_range<MODE, LAW, BK>(p, t, p.offsets, s, k0, kend);
+        dma4(k0 + lane < kend ? static_cast<const void*>(p.perm + k0 + lane) : zero,
+             lds_addr(&prow_s[wave][s & (kRowSlots - 1)][0]));
+      }
+    };
+    // The operands of a step, in CA + CB copies: copy_begin picks the step
+    // (past the last one: zeros) and reads the rows of its positions (weight
+    // gradient), copy_a(j) and copy_b(j) issue one copy each.  Without a
+    // branch, so that a step's copies can sit between its MFMAs.
+    int32_t ck0 = 0, cklen = 0, prow[CA];
+    uint32_t cla = lds0;
+    auto copy_begin = [&](int32_t s) {
+      int32_t kend = 0;
+      ck0 = 0;
+      if (s < t.nsteps) step_range<MODE, LAW, BK>(p, t, p.offsets, s, ck0, kend);
+      cklen = kend - ck0;
+      cla = lds0 + (s % kStages) * kStageBytes;
+      if constexpr (MODE == kModeBwdWeight) {
+#pragma unroll
+        for (int j = 0; j < CA; ++j)
+          prow[j] = prow_s[wave][s & (kRowSlots - 1)][(wave + 4 * j) * (64 / kChunks) + lane / kChunks];
+      }
+    };
+    auto copy_a = [&](int j) {
+      const int ci = wave + 4 * j;
+      const float* g;
+      bool ok;
+      if constexpr (kAKC) {
+        ok = 4 * kslot < cklen;
+        g = Ag + arow[j] * static_cast<int64_t>(MODE == kModeFwd ? p.K : p.N) + ck0 + 4 * kslot;
+      } else {
+        const int k = ci * (64 / kChunks) + lane / kChunks;
+        const int32_t col = t.rstart + 4 * rc_chunk(k, lane % kChunks);
+        ok = k < cklen;
+        g = Ag + static_cast<int64_t>(prow[j]) * p.K + (col < t.rend ? col : t.rstart);
+      }
+      dma16(ok ? static_cast<const void*>(g) : zero, cla + ci * 1024);
+    };
+    auto copy_b = [&](int j) {
+      const int ci = wave + 4 * j;
+      const float* g;
+      bool ok;
+      if constexpr (kBKC) {
+        ok = 4 * kslot < cklen;
+        g = Bg + static_cast<int64_t>(brow[j]) * p.N + ck0 + 4 * kslot;
+      } else {
+        const int k = ci * (64 / kChunks) + lane / kChunks;
+        const int32_t col = t.cstart + 4 * rc_chunk(k, lane % kChunks);
+        ok = k < cklen;
+        g = Bg + static_cast<int64_t>(MODE == kModeFwd ? ck0 + k : prow[j]) * p.N + (col < t.cend ? col : t.cstart);
+      }
+      dma16(ok ? static_cast<const void*>(g) : zero, cla + kABytes + ci * 1024);
+    };
+    auto copy_step = [&](int32_t s) {
+      copy_begin(s);
+#pragma unroll
+      for (int j = 0; j < CA; ++j) copy_a(j);
+#pragma unroll
+      for (int j = 0; j < CB; ++j) copy_b(j);
+    };
+
+    block_barrier();  // every wave is done with the previous tile's stages
+    if constexpr (MODE == kModeBwdWeight) {
+#pragma unroll
+      for (int s = 0; s < kAhead; ++s) copy_perm(s);
+      wait_vm<0>();
+    }
+#pragma unroll
+    for (int s = 0; s < kAhead; ++s) {
+      copy_perm(s + kAhead);
+      copy_step(s);
+    }
+
+    f32x16_t acc;
+#pragma unroll
+    for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+    float colsum = 0.f;
+
+    for (int32_t s = 0; s < t.nsteps; ++s) {
+      wait_vm<(kAhead - 1) * kGroup>();  // this wave's copies of step s have landed
+      block_barrier();                  // and everyone's; the stage of step s - 1 is free
+      const char* As = smem + (s % kStages) * kStageBytes;
+      const char* Bs = As + kABytes;
+      // every fragment of the step is read ahead of its MFMAs: a CU with one
+      // tile has no other wave to fill the LDS latency of each slice
+      float fa[4][4], fb[4][4];
+#pragma unroll
+      for (int rs = 0; rs < 4; ++rs) {
+        read_frag<kAKC>(As, rs, lh, 32 * wm + lr, fa[rs]);
+        read_frag<kBKC>(Bs, rs, lh, 32 * wn + lr, fb[rs]);
+      }
+      copy_begin(s + kAhead);
+      copy_perm(s + 2 * kAhead);
+#pragma unroll
+      for (int rs = 0; rs < 4; ++rs) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+          acc = __builtin_amdgcn_mfma_f32_32x32x2f32(fb[rs][e], fa[rs][e], acc, 0, 0, 0);
+        // the copies of step s + kAhead, spread over the slices
+        __builtin_amdgcn_sched_barrier(0);
+        if (rs < CA) copy_a(rs);
+        else copy_b(rs - CA);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (MODE == kModeBwdWeight) {
+        if (t.do_dbias) {
+          // one column per thread, its share of the step's K indexes
+          constexpr int kPart = BK * TN / kThreads;
+          const int c = threadIdx.x % TN, k0 = (threadIdx.x / TN) * kPart;
+#pragma unroll
+          for (int k = k0; k < k0 + kPart; ++k)
+            colsum += *reinterpret_cast<const float*>(Bs + k * (16 * kChunks) + rc_chunk(k, c >> 2) * 16 + (c & 3) * 4);
         }
       }
     }
-  };
+    wait_vm<0>();  // the copies past the last step, before the stages are reused
 
-  auto advance = [&](Tile& t) -> bool {
-    while (it_pass < 2) {
-      const int32_t total = pfx_s[it_pass][q];
-      const int32_t chunk = (total + 7) >> 3;
-      const int32_t logical = xcd * chunk + it_slot;
-      if (it_slot >= chunk || logical >= total) {
-        ++it_pass;
-        it_slot = blockIdx.x >> 3;
-        continue;
-      }
-      it_slot += slot_stride;
-      int cls = 0;
-      while (logical >= pfx_s[it_pass][cls + 1]) ++cls;
-      const int sel = sel_for(MODE, LAW, it_pass);
-      t = make_tile<MODE, LAW, BN, BK>(p, sel, cls, logical - pfx_s[it_pass][cls], units_s[cls],
-                                       p.offsets);
-      if (t.nsteps == 0) {  // only weight-gradient splits can be empty
-        write_zero_tile(t);
-        continue;
-      }
-      return true;
-    }
-    return false;
-  };
-
-  Tile cur, nxt;
-  if (!advance(cur)) return;
-  bool has_nxt = advance(nxt);
-  Rows<UPT> rc, rn;
-  if constexpr (MODE != kModeBwdWeight) {
-    fetch_rows(p, cur, rc);
-    if (has_nxt) fetch_rows(p, nxt, rn);
-  }
-  int32_t brow[BUPT];
-  float colsum[VEC], colsum_n[VEC];
+    // ---- epilogue ----
+    // lane holds C[row m][columns n .. n+3] with m = 32 wm + lr and
+    // n = 32 wn + 8 a + 4 lh, values acc[4a .. 4a+3]
+    const int64_t crow = erow * static_cast<int64_t>(MODE == kModeBwdData ? p.K : p.N);
+    auto each = [&](auto fn) {  // fn(element index of C, column, the 4 values)
 #pragma unroll
-  for (int v = 0; v < VEC; ++v) colsum[v] = colsum_n[v] = 0.f;
-
-  LA la;
-  LB lb;
-  // stage s of tile t into the loader registers
-  auto load_stage = [&](const Tile& t, const Rows<UPT>& r, int32_t s) {
-    int32_t k0, kend;
-    step_range<MODE, LAW, BK>(p, t, p.offsets, s, k0, kend);
-    if constexpr (MODE == kModeFwd) {
-      la.load(Ag, p.K, r.a, k0, kend);
-      lb.load(Bg, p.N, k0, t.cstart, t.cend, [&](int32_t k) { return k < kend ? k : -1; });
-    } else if constexpr (MODE == kModeBwdData) {
+      for (int a = 0; a < 4; ++a) {
+        const int32_t col = t.cstart + 32 * wn + 4 * lh + 8 * a;
+        if (erow >= 0 && col < t.cend) {
+          float v[4];
 #pragma unroll
-      for (int i = 0; i < BUPT; ++i) {
-        const int32_t kk = t.cstart + DirectLoader<T, BN>::row_of(i);
-        brow[i] = kk < t.cend ? kk : -1;
-      }
-      la.load(Ag, p.N, r.a, k0, kend);
-      lb.load(Bg, p.N, brow, k0, kend);
-    } else {
-      const int32_t* __restrict__ perm = p.perm;
-      auto srow = [&](int32_t k) { return k < kend ? perm[k] : -1; };
-      la.load(Ag, p.K, k0, t.rstart, t.rend, srow);
-      lb.load(Bg, p.N, k0, t.cstart, t.cend, srow);
-    }
-  };
-  auto store_stage = [&](int buf, bool dbias, float* cs) {
-    if constexpr (MODE == kModeFwd) {
-      la.store(As(buf));
-      lb.template store<false>(Bs(buf), cs);
-    } else if constexpr (MODE == kModeBwdData) {
-      la.store(As(buf));
-      lb.store(Bs(buf));
-    } else {
-      la.template store<false>(As(buf), cs);
-      if (dbias) lb.template store<true>(Bs(buf), cs);
-      else lb.template store<false>(Bs(buf), cs);
-    }
-  };
-
-  load_stage(cur, rc, 0);
-  store_stage(0, cur.do_dbias, colsum);  // colsum starts at zero
-  __syncthreads();
-
-  int buf = 0;
-  while (true) {
-    f32x16_t acc[4][WN];
+          for (int j = 0; j < 4; ++j) v[j] = acc[4 * a + j];
+          fn(crow + col, col, v);
 #pragma unroll
-    for (int mi = 0; mi < 4; ++mi)
-#pragma unroll
-      for (int ni = 0; ni < WN; ++ni)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) acc[mi][ni][e] = 0.f;
-
-    for (int32_t s = 0; s < cur.nsteps; ++s) {
-      // the next stage: step s + 1 of this tile, or step 0 of the next one
-      const bool more = s + 1 < cur.nsteps;
-      const bool next_stage = more || has_nxt;
-      const Tile lt = more ? cur : nxt;
-      if (next_stage) {
-        Rows<UPT> lrow;
-#pragma unroll
-        for (int i = 0; i < UPT; ++i) lrow.a[i] = more ? rc.a[i] : rn.a[i];
-        load_stage(lt, lrow, more ? s + 1 : 0);
-      }
-      compute_step<T, WN>(As(buf), Bs(buf), acc);
-      if (next_stage) {
-        float cs[VEC];
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) cs[v] = 0.f;
-        store_stage(buf ^ 1, lt.do_dbias, cs);
-        if constexpr (MODE == kModeBwdWeight) {
-#pragma unroll
-          for (int v = 0; v < VEC; ++v) {
-            colsum[v] += more ? cs[v] : 0.f;
-            colsum_n[v] += more ? 0.f : cs[v];
-          }
+          for (int j = 0; j < 4; ++j) acc[4 * a + j] = v[j];
         }
       }
-      __syncthreads();
-      buf ^= 1;
-    }
-    // `buf` now holds the next tile's first stage; `buf ^ 1` is free until
-    // the next store into it
-
-    // ---- epilogue of `cur` ----
-    // lane holds C[row m][columns n .. n+3] with m = wm*128 + mi*32 + lr and
-    // n = wn*32*WN + ni*32 + 8a + 4lh, values acc[mi][ni][4a .. 4a+3]
-    if constexpr (MODE == kModeFwd || MODE == kModeBwdData) {
-      const int64_t ldc = (MODE == kModeFwd) ? p.N : p.K;
-#pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        const int32_t grow = rc.e[mi];
-        if (grow < 0) continue;
-#pragma unroll
-        for (int ni = 0; ni < WN; ++ni)
-#pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            const int32_t gcol = cur.cstart + wn * (32 * WN) + ni * 32 + 8 * a + 4 * lh;
-            if (gcol >= cur.cend) continue;
-            const int64_t idx = static_cast<int64_t>(grow) * ldc + gcol;
-            float v[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) v[j] = acc[mi][ni][4 * a + j];
-            if constexpr (MODE == kModeFwd) {
-              if (p.bias) {
-                const float4 bv = *reinterpret_cast<const float4*>(p.bias + gcol);
-                v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
-              }
-              if (p.Z) store4(p.Z, p.ydtype, idx, v);
-              if (p.act != kActNone) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] = act_apply(p.act, v[j]);
-              }
-            } else {
-              if (p.Zprev) {
-                float z[4];
-                load4(p.Zprev, p.elem == 0 ? 0 : 1, idx, z);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[j] *= act_deriv(p.act, z[j]);
-              }
-            }
-            store4(p.Y, p.ydtype, idx, v);
-          }
-      }
+    };
+    if constexpr (MODE == kModeBwdWeight) {
+      float* dw = p.nsplit > 1 ? p.partial + static_cast<int64_t>(t.split) * p.K * p.N : p.dW;
+      each([&](int64_t idx, int32_t, float (&v)[4]) { store4(dw, 0, idx, v); });
     } else {
-      float* out = p.nsplit > 1 ? p.partial + static_cast<int64_t>(cur.split) * p.K * p.N : p.dW;
+      if constexpr (MODE == kModeFwd) {
+        if (p.bias)
+          each([&](int64_t, int32_t col, float (&v)[4]) {
+            const float4 bv = *reinterpret_cast<const float4*>(p.bias + col);
+            v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
+          });
+        if (p.Z) each([&](int64_t idx, int32_t, float (&v)[4]) { store4(p.Z, p.ydtype, idx, v); });
+        if (p.act != kActNone)
+          each([&](int64_t, int32_t, float (&v)[4]) {
 #pragma unroll
-      for (int mi = 0; mi < 4; ++mi) {
-        const int32_t grow = cur.rstart + wm * 128 + mi * 32 + lr;
-        if (grow >= cur.rend) continue;
+            for (int j = 0; j < 4; ++j) v[j] = act_apply(p.act, v[j]);
+          });
+      } else if (p.Zprev) {
+        each([&](int64_t idx, int32_t, float (&v)[4]) {
+          float z[4];
+          load4(p.Zprev, 0, idx, z);
 #pragma unroll
-        for (int ni = 0; ni < WN; ++ni)
-#pragma unroll
-          for (int a = 0; a < 4; ++a) {
-            const int32_t gcol = cur.cstart + wn * (32 * WN) + ni * 32 + 8 * a + 4 * lh;
-            if (gcol >= cur.cend) continue;
-            *reinterpret_cast<float4*>(out + static_cast<int64_t>(grow) * p.N + gcol) =
-                make_float4(acc[mi][ni][4 * a], acc[mi][ni][4 * a + 1], acc[mi][ni][4 * a + 2],
-                            acc[mi][ni][4 * a + 3]);
-          }
+          for (int j = 0; j < 4; ++j) v[j] *= act_deriv(p.act, z[j]);
+        });
       }
-      if (cur.do_dbias) {
-        // column sums of the staged dY: a thread keeps one column chunk;
-        // reduce over the threads sharing it through LDS (free stage buffer)
-        constexpr int kSlots = THREADS / LB::CB;
-        float* red = reinterpret_cast<float*>(As(buf ^ 1));
-        const int cb = LB::cb_of();
-        const int slotr = threadIdx.x / LB::CB;
-#pragma unroll
-        for (int v = 0; v < VEC; ++v) red[slotr * BN + cb * VEC + v] = colsum[v];
+      each([&](int64_t idx, int32_t, float (&v)[4]) { store4(p.Y, p.ydtype, idx, v); });
+    }
+    if constexpr (MODE == kModeBwdWeight) {
+      if (t.do_dbias) {
+        // the threads of a column, added in a fixed order
+        float* red = reinterpret_cast<float*>(smem);
+        block_barrier();  // every wave is done with the stages
+        red[threadIdx.x] = colsum;
         __syncthreads();
-        for (int c = threadIdx.x; c < BN; c += THREADS) {
+        if (threadIdx.x < TN && t.cstart + static_cast<int32_t>(threadIdx.x) < t.cend) {
           float sum = 0.f;
-          for (int sl = 0; sl < kSlots; ++sl) sum += red[sl * BN + c];
-          const int32_t gcol = cur.cstart + c;
-          if (gcol < cur.cend) {
-            if (p.nsplit > 1) p.dbias_part[static_cast<int64_t>(cur.split) * p.N + gcol] = sum;
-            else p.dbias[gcol] = sum;
-          }
+#pragma unroll
+          for (int g = 0; g < kThreads / TN; ++g) sum += red[g * TN + threadIdx.x];
+          const int32_t col = t.cstart + threadIdx.x;
+          if (p.nsplit > 1) p.dbias_part[static_cast<int64_t>(t.split) * p.N + col] = sum;
+          else p.dbias[col] = sum;
         }
         __syncthreads();
       }
-    }
-
-    if (!has_nxt) break;
-    cur = nxt;
-    rc = rn;
-#pragma unroll
-    for (int v = 0; v < VEC; ++v) {
-      colsum[v] = colsum_n[v];
-      colsum_n[v] = 0.f;
-    }
-    has_nxt = advance(nxt);
-    if constexpr (MODE != kModeBwdWeight) {
-      if (has_nxt) fetch_rows(p, nxt, rn);
     }
   }
 }
@@ -560,42 +450,46 @@ __global__ void fill_zero_kernel(float* __restrict__ dst, int64_t n) {
     dst[i] = 0.f;
 }
 
-template <typename T, int MODE, int WN, int LAW>
-hipError_t launch_law(const GemmParams& p, int grid, hipStream_t stream) {
-  using G = Geo<WN>;
-  auto kern = star_gemm_kernel<T, MODE, LAW, WN>;
-  // allow more than the default dynamic LDS (once per kernel and device)
-  static std::atomic<unsigned long long> lds_set{0};
-  const hipError_t attr = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_set, G::SMEM);
-  if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(kern, dim3(grid), dim3(THREADS), G::SMEM, stream, p);
+// One workgroup per tile (at most kMaxGrid; a workgroup then takes every
+// gridDim-th of its XCD's tiles).
+constexpr int64_t kMaxGrid = int64_t{1} << 20;
+
+template <int MODE, int LAW>
+hipError_t launch_law(const GemmParams& p0, hipStream_t stream) {
+  GemmParams p = p0;
+  const int32_t* G = MODE == kModeBwdData ? p.S : p.R;  // column groups of C
+  p.NTp[0] = p.MTp[0] = 0;
+  for (int g = 0; g < p.q; ++g) {
+    p.NTp[g + 1] = p.NTp[g] + (G[g + 1] - G[g] + TN - 1) / TN;
+    p.MTp[g + 1] = p.MTp[g] + (p.S[g + 1] - p.S[g] + TM - 1) / TM;
+  }
+  const int64_t units = MODE == kModeBwdWeight ? static_cast<int64_t>(p.MTp[p.q]) * p.nsplit
+                                               : static_cast<int64_t>(p.M) / TM + p.q;
+  // (each XCD's share of a pass rounds up)
+  const int64_t per_xcd = (units * p.NTp[p.q] + 7) / 8 + 2;
+  const int64_t grid = 8 * std::min(per_xcd, kMaxGrid / 8);
+  hipLaunchKernelGGL((star_gemm_f32_kernel<MODE, LAW>), dim3(static_cast<unsigned>(grid)), dim3(kThreads), 0, stream,
+                     p);
   return hipGetLastError();
 }
 
-template <typename T, int MODE, int WN>
-hipError_t launch_typed(const GemmParams& p, int grid, hipStream_t stream) {
+template <int MODE>
+hipError_t launch_mode(const GemmParams& p, hipStream_t stream) {
   switch (p.law) {
-    case 1: return launch_law<T, MODE, WN, 1>(p, grid, stream);
-    case 2: return launch_law<T, MODE, WN, 2>(p, grid, stream);
-    case 3: return launch_law<T, MODE, WN, 3>(p, grid, stream);
-    default: return launch_law<T, MODE, WN, 0>(p, grid, stream);
+    case 1: return launch_law<MODE, 1>(p, stream);
+    case 2: return launch_law<MODE, 2>(p, stream);
+    case 3: return launch_law<MODE, 3>(p, stream);
+    default: return launch_law<MODE, 0>(p, stream);
   }
-}
-
-// fp32 operands only: bf16 operands run in the pipelined kernel.
-template <int MODE, int WN>
-hipError_t launch_mode(const GemmParams& p, int grid, hipStream_t stream) {
-  if (p.elem != 0) return hipErrorInvalidValue;
-  return launch_typed<float, MODE, WN>(p, grid, stream);
 }
 
 }  // namespace
 
-hipError_t launch_gemm(int mode, const GemmParams& p, int nw, int grid, hipStream_t stream) {
-  if (nw != 2) return hipErrorInvalidValue;
-  if (mode == kModeFwd) return launch_mode<kModeFwd, 2>(p, grid, stream);
-  if (mode == kModeBwdData) return launch_mode<kModeBwdData, 2>(p, grid, stream);
-  return launch_mode<kModeBwdWeight, 2>(p, grid, stream);
+hipError_t launch_gemm(int mode, const GemmParams& p, hipStream_t stream) {
+  if (p.elem != 0) return hipErrorInvalidValue;  // bf16 operands run in the pipelined kernel
+  if (mode == kModeFwd) return launch_mode<kModeFwd>(p, stream);
+  if (mode == kModeBwdWeight) return launch_mode<kModeBwdWeight>(p, stream);
+  return launch_mode<kModeBwdData>(p, stream);
 }
 
 hipError_t launch_fill_zero(float* dst, int64_t n, hipStream_t stream) {

@@ -9,37 +9,6 @@ namespace starq {
 namespace gemm {
 
 constexpr int BM = kTileM;  // 256
-constexpr int THREADS = 256;
-
-template <typename T> struct Tr;
-template <> struct Tr<float> {
-  static constexpr int VEC = 4;  // elements per 16-byte kpack
-  static constexpr int BK = 32;  // K per step: 8 kpacks
-};
-template <> struct Tr<uint16_t> {
-  static constexpr int VEC = 8;
-  static constexpr int BK = 64;
-};
-
-template <int WN> struct Geo {
-  static constexpr int BN = 64 * WN;
-  static constexpr int A_BYTES = 8 * BM * 16;
-  static constexpr int B_BYTES = 8 * BN * 16;
-  static constexpr int STAGE = A_BYTES + B_BYTES;
-  static constexpr int SMEM = 2 * STAGE;
-};
-
-__device__ __forceinline__ int swz(int row, int kp) { return row ^ (((row >> 3) ^ kp) & 7); }
-
-template <int ROWS>
-__device__ __forceinline__ int unit_off(int kp, int row) {
-  return (kp * ROWS + swz(row, kp)) * 16;
-}
-
-__device__ __forceinline__ uint32_t word_of(const uint4& r, int w) {
-  return w == 0 ? r.x : (w == 1 ? r.y : (w == 2 ? r.z : r.w));
-}
-
 enum Sel : int { kSelNone = 0, kSelOnly = 1, kSelExcept = 2, kSelAll = 3, kSelTensor = 4, kSelGraph = 10 };
 
 // Law 2, the tensor power of the two-group law (q = 2^L): input group k is
@@ -215,15 +184,6 @@ __device__ __forceinline__ void mma(f32x16_t& acc, const uint4& a, const uint4& 
   acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8_t, a),
                                                 __builtin_bit_cast(bf16x8_t, b), acc, 0, 0, 0);
 }
-__device__ __forceinline__ void mma(f32x16_t& acc, const uint4& a, const uint4& b, float) {
-  // lane half h supplies K element 4 kp + j of instruction j; both operands
-  // use the same assignment, so the products pair up.
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.x), __uint_as_float(b.x), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.y), __uint_as_float(b.y), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.z), __uint_as_float(b.z), acc, 0, 0, 0);
-  acc = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a.w), __uint_as_float(b.w), acc, 0, 0, 0);
-}
-
 // 4 consecutive values of a row of an fp32 or bf16 matrix
 __device__ __forceinline__ void store4(void* base, int dtype, int64_t idx, const float (&v)[4]) {
   if (dtype == 0) {
@@ -245,14 +205,6 @@ __device__ __forceinline__ void load4(const void* base, int dtype, int64_t idx, 
     v[0] = bf16_to_f32(w.x & 0xffffu); v[1] = bf16_to_f32(w.x >> 16);
     v[2] = bf16_to_f32(w.y & 0xffffu); v[3] = bf16_to_f32(w.y >> 16);
   }
-}
-
-// One 16-byte load that reads zeros when `ok` is false.  The address is
-// clamped to the (always valid) first element instead of branching.
-template <typename T>
-__device__ __forceinline__ uint4 load16(const T* __restrict__ src, int64_t off, bool ok) {
-  const uint4 v = *reinterpret_cast<const uint4*>(src + (ok ? off : 0));
-  return ok ? v : make_uint4(0, 0, 0, 0);
 }
 
 // ---- tile iteration ----------------------------------------------------------

@@ -62,9 +62,9 @@ hipError_t launch_type_plan(const int32_t* types, int64_t M, int q, int32_t* per
 hipError_t launch_count_bad_types(const int32_t* types, int64_t M, int q,
                                   unsigned long long* n_bad, hipStream_t stream);
 
-// Persistent grouped GEMM for fp32 operands: tiles of kTileM rows x 128
-// columns (nw must be 2), `grid` workgroups of 256 threads.
-hipError_t launch_gemm(int mode, const GemmParams& p, int nw, int grid, hipStream_t stream);
+// Grouped GEMM for fp32 operands (it picks its tiles and counts them in its
+// own copy of p).
+hipError_t launch_gemm(int mode, const GemmParams& p, hipStream_t stream);
 // bf16 forward / activation-gradient / weight-gradient GEMM fed by direct
 // global-to-LDS copies: tiles of p.tile_m x p.tile_n (see GemmParams; p.NTp
 // and p.MTp must count tiles of that shape); `upper_tiles` bounds

@@ -266,6 +266,36 @@ def test_bwd_data_parity(P, law, dtype, q, s, r, M, fused):
     assert rel_fro(to_host(dX), ref) <= bar(dtype)
 
 
+@pytest.mark.parametrize("law", ["star", "dense", "tensor2"])
+@pytest.mark.parametrize("s,r", [([64, 64, 64, 64], [64, 64, 64, 64]),      # whole tiles, whole steps
+                                 ([8, 72, 32, 136], [56, 8, 200, 64])])    # remainders of both
+def test_fp32_tile_edges(P, law, s, r):
+    """The fp32 products at the edges of their 64 x 64 tiles and 32-deep
+    steps: 1, 64, 65 and 127 rows of the four types, a row of no valid type,
+    groups narrower than a step and wider than a tile.  Every product's error
+    is a sum of at most 400 terms of one sign pattern in 32 bits: TOL_F32."""
+    ga, oa = algs(P, 4, s, r, law)
+    t = np.repeat([0, 1, 2, 3, 4], [1, 64, 65, 127, 1]).astype(np.int32)
+    t = t[np.random.default_rng(77).permutation(len(t))]
+    ok = t < 4
+    M = len(t)
+    X = synth.gaussian(78, 0, (M, oa.K), 1.0, "f32")
+    W = synth.gaussian(78, 1, (oa.K, oa.N), 0.1, "f32")
+    dY = synth.gaussian(78, 2, (M, oa.N), 1.0, "f32")
+    Zp = synth.gaussian(78, 3, (M, oa.K), 1.0, "f32")
+    b = synth.gaussian(78, 4, (oa.N,), 0.5, "f32")
+    td = types_dev(t)
+    Y, Z = P.star_proj_fwd(ga, td, to_dev(X), to_dev(W), f32_dev(b.exact), "gelu_tanh", Z_out=True)
+    dX = P.star_proj_bwd_data(ga, td, to_dev(dY), to_dev(W), Z_prev=to_dev(Zp), act_prev="gelu_tanh")
+    dW, db = P.star_proj_bwd_weight(ga, td, to_dev(X), to_dev(dY))
+    rY, rZ, _, _ = oracle.proj_fwd(oa, t[ok], X.exact[ok], W.exact, b.exact, "gelu_tanh", want_z=True)
+    rX = oracle.proj_bwd_data(oa, t[ok], dY.exact[ok], W.exact, Zprev=Zp.exact[ok], act_prev="gelu_tanh")
+    rW, rb = oracle.proj_bwd_weight(oa, t[ok], X.exact[ok], dY.exact[ok])
+    for got, ref in ((to_host(Y)[ok], rY), (to_host(Z)[ok], rZ), (to_host(dX)[ok], rX), (to_host(dW), rW),
+                     (to_host(db), rb)):
+        assert rel_fro(got, ref) <= TOL_F32
+
+
 @pytest.mark.parametrize("law", ["star", "tensor2"])
 @pytest.mark.parametrize("mode", ["fwd", "bwd_data"])
 def test_half_height_last_round(P, law, mode):
