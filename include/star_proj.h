@@ -233,7 +233,12 @@ star_status star_ffn_fwd(const star_algebra *up, const star_algebra *down, int64
  *   W_up, W_down, b_up, b_down: host arrays of n_layers device pointers
  *             (bf16 [D, F], bf16 [F, D], float[F] or NULL, float[D] or NULL)
  *   Y         device [M, D] of dtype yt: the final h
- *   ws        at least star_workspace_bytes(STAR_OP_DECODE, up, down, M) bytes
+ *   ws        star_workspace_bytes(STAR_OP_DECODE, up, down, M) bytes.  Where
+ *             projections run one launch each, those bytes end with room for
+ *             partial sums of K splits; a smaller workspace that holds h
+ *             (float[M, D]), its bf16 copy and H behind a 256-byte line, each
+ *             at a 256-byte boundary, is taken too, with fewer splits (the
+ *             same result to the rounding of fp32 sums)
  * Where the stack fits, it runs as one persistent launch of at most one
  * workgroup per CU whose workgroups wait on each other, so they must all be
  * resident at once: the device must not be held by long-running work on other
@@ -262,9 +267,10 @@ star_status star_decode(const star_algebra *up, const star_algebra *down, int32_
  *           set to 1 if the step was lost to a wait bound (the flag
  *           star_decode_status reports for star_decode); with NULL the flag
  *           is kept in the static buffer and not reported
- * A shape whose star_decode workspace (star_workspace_bytes(STAR_OP_DECODE,
- * up, down, M)) exceeds STAR_DECODE_SCRATCH_BYTES returns STAR_ERR_WORKSPACE
- * before anything is launched; every shape with D, F <= 4096 and M <= 64
+ * A shape whose smallest star_decode workspace (what star_workspace_bytes(
+ * STAR_OP_DECODE, up, down, M) gives without the partial sums of wide
+ * projections, see star_decode) exceeds STAR_DECODE_SCRATCH_BYTES returns
+ * STAR_ERR_WORKSPACE before anything is launched; every shape with D, F <= 4096 and M <= 64
  * fits (wider ones may not).  Every call on one device shares that device's
  * buffer, and each call clears the parts that must start at zero: calls that
  * overlap in time on one device (other streams, other threads) race and

@@ -315,10 +315,18 @@ BwdWs bwd_weight_layout(const Alg& a, int64_t M) {
 // read by star_decode_status.
 constexpr size_t kDecodeStatusBytes = kCounterStride * sizeof(int32_t);
 
+// One launch per projection: h, the bf16 inputs and H, then (as room allows)
+// the arrival counters and partial sums of the projections' K splits, which
+// both projections use in turn.
 struct DecodeWs {
-  size_t h = 0, xb = 0, H = 0, end = 0;
+  size_t h = 0, xb = 0, H = 0, end = 0;      // end: what the call cannot do without
+  size_t cnt = 0, cnt_words = 0, part = 0;
+  int splits_up = 1, splits_dn = 1;
+  size_t full = 0;  // with the splits
 };
-DecodeWs decode_layout(const Alg& up, int64_t M) {
+// room: the workspace's size; fewer splits are used where the wanted ones do
+// not fit
+DecodeWs decode_layout(const Alg& up, const Alg& down, int64_t M, size_t room = SIZE_MAX) {
   DecodeWs w;
   const int64_t D = up.K(), F = up.N();
   size_t cur = kDecodeStatusBytes;
@@ -328,7 +336,22 @@ DecodeWs decode_layout(const Alg& up, int64_t M) {
   cur = align_up(cur + sizeof(uint16_t) * M * D);
   w.H = cur;
   cur = align_up(cur + sizeof(uint16_t) * M * F);
-  w.end = cur;
+  w.end = w.full = cur;
+  const int32_t tu = static_cast<int32_t>(col_tiles(up, true, kDecodePhaseN));
+  const int32_t td = static_cast<int32_t>(col_tiles(down, true, kDecodePhaseN));
+  w.cnt = cur;
+  w.cnt_words = static_cast<size_t>(std::max(tu, td));
+  w.part = align_up(cur + sizeof(int32_t) * w.cnt_words);
+  auto fit = [&](const Alg& a, int32_t tiles) {
+    int n = decode_phase_splits(a.law, a.q, a.S, tiles, M);
+    while (n > 1 && (w.part > room || decode_phase_part_bytes(tiles, n, M) > room - w.part)) --n;
+    return n;
+  };
+  w.splits_up = fit(up, tu);
+  w.splits_dn = fit(down, td);
+  if (w.splits_up > 1 || w.splits_dn > 1)
+    w.full = align_up(w.part + std::max(decode_phase_part_bytes(tu, w.splits_up, M),
+                                        decode_phase_part_bytes(td, w.splits_dn, M)));
   return w;
 }
 
@@ -387,6 +410,13 @@ StackPlan stack_plan(const Alg& u, const Alg& d, int64_t M, int n_layers, bool g
           decode_stack_smem(static_cast<int>(M), kmax, static_cast<int>(D), sp.ns, gated) > 0 &&
           sp.grid <= cu_count();
   return sp;
+}
+
+// The bytes a decode call cannot do without (for the persistent stack: where
+// a stack of one layer can run).
+size_t decode_need(const Alg& u, const Alg& d, int64_t M) {
+  const StackPlan sp = stack_plan(u, d, std::max<int64_t>(M, 1), 1);
+  return std::max(decode_layout(u, d, M).end, sp.ok ? sp.end : 0);
 }
 
 template <typename T>
@@ -621,7 +651,7 @@ size_t star_workspace_bytes(int32_t op, const star_algebra* alg, const star_alge
       const int64_t m = std::min<int64_t>(M, kDecodeMaxRows);
       // the single-launch stack's layout only where the stack can run
       const StackPlan sp = stack_plan(a, d, std::max<int64_t>(m, 1), 1);
-      return sp.ok ? std::max(decode_layout(a, m).end, sp.end) : decode_layout(a, m).end;
+      return std::max(decode_layout(a, d, m).full, sp.ok ? sp.end : 0);
     }
     default:
       return 0;
@@ -955,7 +985,7 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
         (gated && b_gate && b_gate[l] && !aligned16(b_gate[l])))
       return STAR_ERR_ALIGN;
   }
-  const DecodeWs dw = decode_layout(u, M);
+  const DecodeWs dw = decode_layout(u, d, M, ws_bytes);
   const StackPlan sp = stack_plan(u, d, M, n_layers, gated);
   if (!ws || ws_bytes < (sp.ok ? std::max(dw.end, sp.end) : dw.end)) return STAR_ERR_WORKSPACE;
   if (!aligned16(ws)) return STAR_ERR_ALIGN;
@@ -1020,9 +1050,8 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
     return hip_status(launch_decode_stack(k, sp.grid, stream));
   }
 
-  // the status line reads zero: the per-projection kernels do not wait
-  if (!err_word) {
-    st = hip_status(launch_fill_zero(at<float>(ws, 0), kDecodeStatusBytes / sizeof(float), stream));
+  if (dw.splits_up > 1 || dw.splits_dn > 1) {
+    st = hip_status(launch_fill_zero(at<float>(ws, dw.cnt), static_cast<int64_t>(dw.cnt_words), stream));
     if (st != STAR_OK) return st;
   }
   float* h = at<float>(ws, dw.h);
@@ -1039,7 +1068,9 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
       p.S[g] = static_cast<int32_t>(a.S[g]);
       p.R[g] = static_cast<int32_t>(a.R[g]);
     }
-    fill_tiles(p.NTp, a.R, a.q, kDecodeTileN);
+    fill_tiles(p.NTp, a.R, a.q, kDecodePhaseN);
+    p.cnt = at<int32_t>(ws, dw.cnt);
+    p.part = at<uint64_t>(ws, dw.part);
     for (int g = 0; g < kMaxQGroups; ++g) p.adj[g] = a.adj[g];
     p.types = row_type;
     p.act = act;
@@ -1048,6 +1079,8 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
   DecodePhase pu, pd;
   fill(pu, u);
   fill(pd, d);
+  pu.splits = dw.splits_up;
+  pd.splits = dw.splits_dn;
   pu.mode = 0;
   pu.out_bf16 = Hb;
   pd.mode = 1;
@@ -1058,6 +1091,7 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
     pu.A = first ? static_cast<const uint16_t*>(X) : xb;
     pu.W = static_cast<const uint16_t*>(W_up[l]);
     pu.bias = b_up ? b_up[l] : nullptr;
+    pu.status = first && !err_word ? at<int32_t>(ws, 0) : nullptr;
     st = hip_status(launch_decode_phase(pu, stream));
     if (st != STAR_OK) return st;
     pd.W = static_cast<const uint16_t*>(W_down[l]);
@@ -1104,8 +1138,8 @@ star_status star_decode_noalloc(const star_algebra* up, const star_algebra* down
   if (status && !aligned4(status)) return STAR_ERR_ALIGN;
   if (M == 0) return decode_impl(up, down, n_layers, M, row_type, X, xt, nullptr, nullptr, W_up, b_up, W_down,
                                  b_down, act, residual, Y, yt, nullptr, 0, stream);
-  // a shape whose workspace exceeds the static scratch is refused
-  if (star_workspace_bytes(STAR_OP_DECODE, up, down, M) > kDecodeScratchBytes) return STAR_ERR_WORKSPACE;
+  // a shape whose smallest workspace exceeds the static scratch is refused
+  if (decode_need(u, d, M) > kDecodeScratchBytes) return STAR_ERR_WORKSPACE;
   void* scratch = nullptr;
   if (decode_scratch(&scratch) != hipSuccess) return STAR_ERR_HIP;
   return decode_impl(up, down, n_layers, M, row_type, X, xt, nullptr, nullptr, W_up, b_up, W_down, b_down, act,

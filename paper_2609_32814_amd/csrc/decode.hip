@@ -7,25 +7,29 @@
 // some row's support reaches is streamed exactly once per step, and rows
 // whose support skips the block multiply zeros.
 //
-// A workgroup owns 16 output columns (inside one output group j) over the
-// whole K range, so no partial sums cross workgroups and no workgroup ever
-// waits on another (a kernel boundary separates dependent phases).  K is cut
-// into 32-row slices; a slice is needed when some row's support reaches one
-// of its input groups (k in B(t_b, j)).  Each of the 4 wavefronts streams
-// every fourth needed slice straight from global memory into LDS with one
-// 16-byte-per-lane direct load (32 rows x 32 bytes = 1 KB per slice), all
-// issued before any is consumed, so the whole weight tile is in flight at
-// once (in passes of up to 128 slices when K is wider than 4096: a wave
-// reuses only its own slots, so the passes need no barrier).  The wavefront then reads each slice back with the LDS transpose
-// read (two reads give every lane 8 consecutive K values of one column),
-// loads the rows' 8-element input pieces (zero where the support skips
-// them), and multiplies with v_mfma_f32_16x16x32_bf16.  The four
-// wavefronts' partial sums are added in LDS in a fixed order, then the bias,
-// activation or residual are applied and the outputs written.
+// A workgroup owns 64 output columns (inside one output group j) and one of
+// `splits` equal shares of the K slices they need: K is cut into 32-row
+// slices, and a slice is needed when some row's support reaches one of its
+// input groups (k in B(t_b, j)).  What bounds it is the weight stream, and
+// below about 20 MB the chain of round trips around it: types, slices,
+// weights, hand-over.  64 columns make every row piece of a slice a whole
+// 128-byte line, and splitting K fills the chip: each projection of 8 rows,
+// 2560 <-> 9728, q = 4 (46 MB of weights), 81 -> 16 to 20 us against
+// 16-column tiles over all of K (32-byte pieces, up to 128 slices copied and
+// then waited for at once).  Each wavefront streams every fourth slice of
+// the share straight from global memory into a ring of its own in LDS (four
+// copies of 1 KB for the weights, one per 16 rows for their input pieces;
+// two or three slices, so that two workgroups fit a CU), waits only for the
+// oldest slice, reads it back with the LDS transpose read (two reads give
+// every lane 8 consecutive K values of one column) and multiplies with
+// v_mfma_f32_16x16x32_bf16.  No barrier in the stream.  The four
+// wavefronts' sums are added in LDS in a fixed order.
 //
-// Column tiles are mapped to workgroups so that the four tiles sharing a
-// 128-byte line of a weight row run on the same XCD (workgroups are
-// dispatched round-robin over the 8 XCDs) and share one L2 fetch.
+// With more than one split, a workgroup stores its sums (agent-coherent
+// stores, acknowledged before its arrival is counted) and the last of a
+// tile's workgroups to arrive adds all of them in split order, so results do
+// not depend on timing.  It also sets the tile's counter back to zero for
+// the next projection.  Nobody waits for anybody.
 #include <algorithm>
 
 #include "common.hpp"
@@ -36,10 +40,10 @@ namespace starq {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int TN = kDecodeTileN;      // 16 output columns
+constexpr int TN = kDecodePhaseN;     // 64 output columns
 constexpr int SLICE = kDecodeSliceK;  // 32 K rows
-constexpr int kRedBytes = 4 * 4 * 64 * 16;  // 4 waves x 4 row blocks x 64 lanes x float4
-constexpr int kPassSlices = 128;            // most slices held in LDS at once (128 KB)
+constexpr int kSliceBytes = SLICE * TN * 2;
+constexpr int kBlocks = TN / 16;
 
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 #define STARQ_LDS __attribute__((address_space(3)))
@@ -71,38 +75,72 @@ __device__ __forceinline__ int group_of(const int32_t* starts, int q, int32_t x)
   return lo;
 }
 
-__global__ __launch_bounds__(kThreads) void decode_phase_kernel(const DecodePhase p) {
+// Slices a wave holds in LDS: two workgroups per CU fit.
+constexpr int wave_slots(int mb) { return mb <= 2 ? 3 : 2; }
+
+// 16-column block cb of slice row r sits at block cb ^ col_swz(r): the rows
+// a transposing read takes together (0-3 and 8-11 of a 16-row half) then
+// cover all banks.
+__device__ __forceinline__ int col_swz(int r) { return ((r >> 1) & 1) | (((r >> 3) & 1) << 1); }
+
+__device__ __forceinline__ void st_agent64(uint64_t* p, uint64_t v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint64_t ld_agent64(const uint64_t* p) {
+  return __hip_atomic_load(const_cast<uint64_t*>(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// 64 zero bytes: the source of an input piece that no support reaches
+__device__ __attribute__((aligned(64))) uint32_t g_decode_zero[16];
+
+// 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane;
+// issued as assembly so that the compiler does not wait for every copy in
+// flight before an LDS read (the waits are explicit and counted).
+__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+template <int N> __device__ __forceinline__ void wait_vm() {
+  static_assert(N >= 0 && N < 64, "vmcnt is six bits");
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+// MB: 16-row blocks of the step (M <= 16 MB)
+template <int MB>
+__global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodePhase p) {
+  constexpr int kSlots = wave_slots(MB);
+  constexpr int kSlot = kSliceBytes + MB * 1024;  // a slice's weights and input pieces
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ unsigned long long rowmask_s[kMaxQGroups];
   __shared__ int32_t S_s[kMaxQGroups + 1];
   __shared__ int16_t slices_s[kDecodeMaxK / SLICE];
   __shared__ int32_t wave_cnt_s[4];
+  __shared__ int32_t last_s;
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = tid >> 6;
 
-  // column tile of this workgroup (XCD-aware: 4 consecutive tiles per XCD)
-  const int b = blockIdx.x;
-  const int xcd = b & 7, s = b >> 3;
-  const int ct = 4 * (8 * (s >> 2) + xcd) + (s & 3);
-  const int nt_total = p.NTp[p.q];
-  if (ct >= nt_total) return;
-  int j = 0;
-  while (ct >= p.NTp[j + 1]) ++j;
+  // the status line reads zero: these kernels do not wait
+  if (p.status && blockIdx.x == 0 && tid < kCounterStride) p.status[tid] = 0;
+
+  const int nt = p.NTp[p.q];
+  const int ct = blockIdx.x % nt, split = blockIdx.x / nt;
+  const int j = __popcll(__ballot(lane < p.q && ct >= p.NTp[lane + 1]));
   const int32_t n0 = p.R[j] + (ct - p.NTp[j]) * TN;
   const int32_t nend = p.R[j + 1];
 
   // the input group starts, searched from LDS below
   for (int i = tid; i <= p.q; i += kThreads) S_s[i] = p.S[i];
-  __syncthreads();
-  // which rows need block (g, j), per input group g: wave 0 holds one row
-  // per lane and takes one ballot per group
-  if (wave == 0) {
+  // which rows need block (g, j), per input group g: one row per lane, one
+  // ballot per group
+  {
     // a row whose type lies outside [0, q) has an empty support
     const int t = lane < p.M ? p.types[lane] : -1;
     const bool valid = t >= 0 && t < p.q;
-    for (int g = 0; g < p.q; ++g) {
+    for (int g = wave; g < p.q; g += 4) {
       const unsigned long long m = __ballot(valid && in_support(p.law, p.adj, t, j, g));
       if (lane == 0) rowmask_s[g] = m;
     }
@@ -132,168 +170,244 @@ __global__ __launch_bounds__(kThreads) void decode_phase_kernel(const DecodePhas
     found += wave_cnt_s[0] + wave_cnt_s[1] + wave_cnt_s[2] + wave_cnt_s[3];
     __syncthreads();  // every thread has read the counts before the next round writes them
   }
-  const int nslices = found;
+  // this split's share of them
+  const int lo = found * split / p.splits, hi = found * (split + 1) / p.splits;
 
   // compute: lane group G = lane/16 holds K rows 8G..8G+7 of a slice for
-  // column n0 + lane%16 (transpose reads), and the input pieces of rows
-  // 16 mb + lane%16
+  // column lane%16 of each 16-column block (transpose reads), and the input
+  // pieces of rows 16 mb + lane%16
   const int G = lane >> 4;
   const int pl = lane & 15;
-  const int mblocks = (p.M + 15) >> 4;
-  f32x4_t acc[4];
+  f32x4_t acc[kBlocks][MB];
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) acc[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-  // input pieces of slice `i` (zero where the row's support skips it)
-  auto load_x = [&](int i, uint4 (&xv)[4]) {
-    const int32_t kk = slices_s[i] * SLICE + 8 * G;
+  for (int cb = 0; cb < kBlocks; ++cb)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) acc[cb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+  // this wave's slices: lo + wave + 4 t, t < n
+  const int n = max(0, (hi - lo - wave + 3) >> 2);
+  char* mine = lds + wave * (kSlots * kSlot);
+  const uint32_t mine_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(mine)));
+  // Slice t into its slot: weights, 8 rows a copy (lane l: row l/8, 16 bytes
+  // of it), then the rows' input pieces, one copy a row block (zeros where
+  // the support skips them).  Rows past K repeat row K-1 and columns past
+  // the group repeat its first ones (finite values; their products are
+  // either multiplied by zero inputs or never stored).
+  auto copy = [&](int t) {
+    const int32_t k0 = slices_s[lo + wave + 4 * t] * SLICE;
+    const uint32_t dst = mine_lds + (t % kSlots) * kSlot;
+#pragma unroll
+    for (int d = 0; d < SLICE / 8; ++d) {
+      const int r = 8 * d + (lane >> 3), c = lane & 7;
+      int32_t col = n0 + 16 * ((c >> 1) ^ col_swz(r)) + 8 * (c & 1);
+      col = col < nend ? col : n0;
+      dma16(p.W + static_cast<int64_t>(min(k0 + r, p.K - 1)) * p.N + col, dst + d * 1024);
+    }
+    const int32_t kk = k0 + 8 * G;
     const unsigned long long gm = kk < p.K ? rowmask_s[group_of(S_s, p.q, kk)] : 0ull;
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
+    for (int mb = 0; mb < MB; ++mb) {
       const int m = 16 * mb + pl;
-      const bool ok = mb < mblocks && m < p.M && ((gm >> m) & 1ull);
-      const uint4 xa = *reinterpret_cast<const uint4*>(p.A + (ok ? static_cast<int64_t>(m) * p.K + kk : 0));
-      xv[mb] = ok ? xa : make_uint4(0, 0, 0, 0);
+      const bool ok = m < p.M && ((gm >> m) & 1ull);
+      dma16(ok ? static_cast<const void*>(p.A + static_cast<int64_t>(m) * p.K + kk) : g_decode_zero,
+            dst + kSliceBytes + mb * 1024);
     }
   };
-  const int pass = p.slots;  // slices held in LDS at once (the launch's LDS room)
-  for (int p0 = 0; p0 < nslices; p0 += pass) {
-    const int p1 = min(nslices, p0 + pass);
-    // stream this wave's slices of the pass into LDS (slot i - p0): lane l
-    // carries row l/2, 16 bytes (8 columns) at half l%2.  Rows past K repeat
-    // row K-1 and columns past the group repeat its first column (finite
-    // values; their products are either multiplied by zero inputs or never
-    // stored).
-    for (int i = p0 + wave; i < p1; i += 4) {
-      int32_t row = slices_s[i] * SLICE + (lane >> 1);
-      row = row < p.K ? row : p.K - 1;
-      int32_t col = n0 + 8 * (lane & 1);
-      col = col < nend ? col : n0;
-      const uint16_t* g = p.W + static_cast<int64_t>(row) * p.N + col;
-      __builtin_amdgcn_global_load_lds(g, (STARQ_LDS void*)(lds + (i - p0) * 1024), 16, 0, 0);
-    }
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    __asm__ volatile("" ::: "memory");
-    // the input pieces, prefetched two slices ahead
-    uint4 x0[4], x1[4], x2[4];
-    if (p0 + wave < p1) load_x(p0 + wave, x0);
-    if (p0 + wave + 4 < p1) load_x(p0 + wave + 4, x1);
-    for (int i = p0 + wave; i < p1; i += 4) {
-      if (i + 8 < p1) load_x(i + 8, x2);
-      const char* base = lds + (i - p0) * 1024 + (8 * G + (pl >> 2)) * 32 + (pl & 3) * 8;
-      const v4i16_t w0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(base));
-      const v4i16_t w1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(base + 128));
-      uint4 wf;
-      wf.x = static_cast<uint16_t>(w0[0]) | (static_cast<uint32_t>(static_cast<uint16_t>(w0[1])) << 16);
-      wf.y = static_cast<uint16_t>(w0[2]) | (static_cast<uint32_t>(static_cast<uint16_t>(w0[3])) << 16);
-      wf.z = static_cast<uint16_t>(w1[0]) | (static_cast<uint32_t>(static_cast<uint16_t>(w1[1])) << 16);
-      wf.w = static_cast<uint16_t>(w1[2]) | (static_cast<uint32_t>(static_cast<uint16_t>(w1[3])) << 16);
+  constexpr int kCopies = SLICE / 8 + MB;  // of a slice
+  for (int t = 0; t < min(n, kSlots); ++t) copy(t);
+  for (int t = 0; t < n; ++t) {
+    // slice t has landed (the copies of the kSlots - 1 slices after it may
+    // still be in flight)
+    if (t + kSlots - 1 < n) wait_vm<(kSlots - 1) * kCopies>();
+    else wait_vm<0>();
+    const char* slot = mine + (t % kSlots) * kSlot;
+    uint4 wf[kBlocks], x[MB];
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        if (mb < mblocks) {
-          // D[n][m] += W^T x^T: lane ends with 4 consecutive columns of row m
-          acc[mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, wf),
-                                                            __builtin_bit_cast(bf16x8_t, x0[mb]),
-                                                            acc[mb], 0, 0, 0);
-        }
-      }
+    for (int mb = 0; mb < MB; ++mb) x[mb] = *reinterpret_cast<const uint4*>(slot + kSliceBytes + mb * 1024 + lane * 16);
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        x0[mb] = x1[mb];
-        x1[mb] = x2[mb];
-      }
+    for (int cb = 0; cb < kBlocks; ++cb) {
+      const int r = 8 * G + (pl >> 2);
+      const char* a0 = slot + r * (2 * TN) + (cb ^ col_swz(r)) * 32 + (pl & 3) * 8;
+      const char* a1 = slot + (r + 4) * (2 * TN) + (cb ^ col_swz(r + 4)) * 32 + (pl & 3) * 8;
+      const v4i16_t w0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a0));
+      const v4i16_t w1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a1));
+      wf[cb].x = static_cast<uint16_t>(w0[0]) | (static_cast<uint32_t>(static_cast<uint16_t>(w0[1])) << 16);
+      wf[cb].y = static_cast<uint16_t>(w0[2]) | (static_cast<uint32_t>(static_cast<uint16_t>(w0[3])) << 16);
+      wf[cb].z = static_cast<uint16_t>(w1[0]) | (static_cast<uint32_t>(static_cast<uint16_t>(w1[1])) << 16);
+      wf[cb].w = static_cast<uint16_t>(w1[2]) | (static_cast<uint32_t>(static_cast<uint16_t>(w1[3])) << 16);
     }
-    // the wave's slots are free for the next pass once its reads are done
-    __builtin_amdgcn_s_waitcnt(0);
-    __builtin_amdgcn_wave_barrier();
-    __asm__ volatile("" ::: "memory");
+    // the slot is free once its reads are done
+    asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
+    if (t + kSlots < n) copy(t + kSlots);
+#pragma unroll
+    for (int cb = 0; cb < kBlocks; ++cb)
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb)
+        // D[n][m] += W^T x^T: lane ends with 4 consecutive columns of row m
+        acc[cb][mb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+            __builtin_bit_cast(bf16x8_t, wf[cb]), __builtin_bit_cast(bf16x8_t, x[mb]), acc[cb][mb], 0, 0, 0);
   }
 
-  // add the four waves' partial sums in a fixed order
-  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds + p.slots * 1024);
+  // add the four waves' sums in a fixed order: thread tid then holds, for
+  // row block mb, columns n0 + 16 (tid / 64) + 4 (lane / 16) .. + 3 of row
+  // 16 mb + lane % 16
+  __syncthreads();  // every wave is done with its slots
+  f32x4_t* red = reinterpret_cast<f32x4_t*>(lds);
 #pragma unroll
-  for (int mb = 0; mb < 4; ++mb) red[(wave * 4 + mb) * 64 + lane] = acc[mb];
+  for (int cb = 0; cb < kBlocks; ++cb)
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) red[((wave * kBlocks + cb) * MB + mb) * 64 + lane] = acc[cb][mb];
   __syncthreads();
-  {
-    const int mb = tid >> 6;
-    const int l = tid & 63;
-    const int m = 16 * mb + (l & 15);
-    const int32_t n = n0 + 4 * (l >> 4);
-    if (mb < mblocks && m < p.M && n < nend) {
-      f32x4_t z = red[(0 * 4 + mb) * 64 + l];
-      z += red[(1 * 4 + mb) * 64 + l];
-      z += red[(2 * 4 + mb) * 64 + l];
-      z += red[(3 * 4 + mb) * 64 + l];
-      if (p.bias) {
-        const float4 bv = *reinterpret_cast<const float4*>(p.bias + n);
-        z[0] += bv.x; z[1] += bv.y; z[2] += bv.z; z[3] += bv.w;
+  f32x4_t z[MB];
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    z[mb] = red[(wave * MB + mb) * 64 + lane];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) z[mb] += red[((w * kBlocks + wave) * MB + mb) * 64 + lane];
+  }
+
+  if (p.splits > 1) {
+    // sums as two 8-byte words, one 16 MB x 64 block of them per (tile,
+    // split); rows past M are not stored
+    const int64_t block = static_cast<int64_t>(MB) * kThreads * 2;
+    uint64_t* tile = p.part + static_cast<int64_t>(ct) * p.splits * block;
+    uint64_t* dst = tile + split * block + 2 * tid;
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      if (16 * mb + pl < p.M) {
+        const uint2 a = make_uint2(__float_as_uint(z[mb][0]), __float_as_uint(z[mb][1]));
+        const uint2 b = make_uint2(__float_as_uint(z[mb][2]), __float_as_uint(z[mb][3]));
+        st_agent64(dst + mb * 2 * kThreads, __builtin_bit_cast(uint64_t, a));
+        st_agent64(dst + mb * 2 * kThreads + 1, __builtin_bit_cast(uint64_t, b));
       }
-      const int64_t o = static_cast<int64_t>(m) * p.N + n;
-      if (p.mode == 0) {
-        uint2 w;
-        w.x = f32_to_bf16(act_apply(p.act, z[0])) | (static_cast<uint32_t>(f32_to_bf16(act_apply(p.act, z[1]))) << 16);
-        w.y = f32_to_bf16(act_apply(p.act, z[2])) | (static_cast<uint32_t>(f32_to_bf16(act_apply(p.act, z[3]))) << 16);
-        *reinterpret_cast<uint2*>(p.out_bf16 + o) = w;
-      } else {
-        float hv[4];
-        if (p.residual) {
-          if (p.h_init) {
-            const uint2 hi = *reinterpret_cast<const uint2*>(p.h_init + o);
-            hv[0] = bf16_to_f32(hi.x & 0xffffu); hv[1] = bf16_to_f32(hi.x >> 16);
-            hv[2] = bf16_to_f32(hi.y & 0xffffu); hv[3] = bf16_to_f32(hi.y >> 16);
-          } else {
-            const float4 hp = *reinterpret_cast<const float4*>(p.h_in + o);
-            hv[0] = hp.x; hv[1] = hp.y; hv[2] = hp.z; hv[3] = hp.w;
+    }
+    __builtin_amdgcn_s_waitcnt(0);  // the stores are acknowledged ...
+    __syncthreads();                // ... every thread's
+    if (tid == 0) {
+      const int32_t n = __hip_atomic_fetch_add(p.cnt + ct, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_s = n == p.splits - 1;
+    }
+    __syncthreads();
+    if (!last_s) return;
+    if (tid == 0) __hip_atomic_store(p.cnt + ct, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll
+    for (int mb = 0; mb < MB; ++mb) {
+      z[mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+      if (16 * mb + pl >= p.M) continue;
+      const uint64_t* src = tile + 2 * tid + mb * 2 * kThreads;
+      for (int s0 = 0; s0 < p.splits; s0 += 8) {
+        uint64_t a[8], b[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          const int s = min(s0 + u, p.splits - 1);
+          a[u] = ld_agent64(src + s * block);
+          b[u] = ld_agent64(src + s * block + 1);
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          if (s0 + u < p.splits) {
+            const uint2 av = __builtin_bit_cast(uint2, a[u]), bv = __builtin_bit_cast(uint2, b[u]);
+            z[mb][0] += __uint_as_float(av.x); z[mb][1] += __uint_as_float(av.y);
+            z[mb][2] += __uint_as_float(bv.x); z[mb][3] += __uint_as_float(bv.y);
           }
-        } else {
-          hv[0] = hv[1] = hv[2] = hv[3] = 0.f;
-        }
-#pragma unroll
-        for (int e = 0; e < 4; ++e) hv[e] += z[e];
-        if (p.h_out) *reinterpret_cast<float4*>(p.h_out + o) = make_float4(hv[0], hv[1], hv[2], hv[3]);
-        if (p.out_bf16) {
-          uint2 w;
-          w.x = f32_to_bf16(hv[0]) | (static_cast<uint32_t>(f32_to_bf16(hv[1])) << 16);
-          w.y = f32_to_bf16(hv[2]) | (static_cast<uint32_t>(f32_to_bf16(hv[3])) << 16);
-          *reinterpret_cast<uint2*>(p.out_bf16 + o) = w;
-        }
-        if (p.Y) {
-#pragma unroll
-          for (int e = 0; e < 4; ++e) store_out(p.Y, p.ydtype, o + e, hv[e]);
         }
       }
     }
   }
+
+#pragma unroll
+  for (int mb = 0; mb < MB; ++mb) {
+    const int m = 16 * mb + pl;
+    const int32_t n = n0 + 16 * wave + 4 * G;
+    if (m >= p.M || n >= nend) continue;
+    f32x4_t v = z[mb];
+    if (p.bias) {
+      const float4 bv = *reinterpret_cast<const float4*>(p.bias + n);
+      v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
+    }
+    const int64_t o = static_cast<int64_t>(m) * p.N + n;
+    if (p.mode == 0) {
+      uint2 w;
+      w.x = f32_to_bf16(act_apply(p.act, v[0])) | (static_cast<uint32_t>(f32_to_bf16(act_apply(p.act, v[1]))) << 16);
+      w.y = f32_to_bf16(act_apply(p.act, v[2])) | (static_cast<uint32_t>(f32_to_bf16(act_apply(p.act, v[3]))) << 16);
+      *reinterpret_cast<uint2*>(p.out_bf16 + o) = w;
+      continue;
+    }
+    float hv[4] = {0.f, 0.f, 0.f, 0.f};
+    if (p.residual) {
+      if (p.h_init) {
+        const uint2 hi4 = *reinterpret_cast<const uint2*>(p.h_init + o);
+        hv[0] = bf16_to_f32(hi4.x & 0xffffu); hv[1] = bf16_to_f32(hi4.x >> 16);
+        hv[2] = bf16_to_f32(hi4.y & 0xffffu); hv[3] = bf16_to_f32(hi4.y >> 16);
+      } else {
+        const float4 hp = *reinterpret_cast<const float4*>(p.h_in + o);
+        hv[0] = hp.x; hv[1] = hp.y; hv[2] = hp.z; hv[3] = hp.w;
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < 4; ++e) hv[e] += v[e];
+    if (p.h_out) *reinterpret_cast<float4*>(p.h_out + o) = make_float4(hv[0], hv[1], hv[2], hv[3]);
+    if (p.out_bf16) {
+      uint2 w;
+      w.x = f32_to_bf16(hv[0]) | (static_cast<uint32_t>(f32_to_bf16(hv[1])) << 16);
+      w.y = f32_to_bf16(hv[2]) | (static_cast<uint32_t>(f32_to_bf16(hv[3])) << 16);
+      *reinterpret_cast<uint2*>(p.out_bf16 + o) = w;
+    }
+    if (p.Y) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) store_out(p.Y, p.ydtype, o + e, hv[e]);
+    }
+  }
+}
+
+template <int MB>
+hipError_t launch_mb(const DecodePhase& p, hipStream_t stream) {
+  // the slots, reused for the waves' sums
+  constexpr size_t smem =
+      std::max<size_t>(4 * wave_slots(MB) * (kSliceBytes + MB * 1024), static_cast<size_t>(4 * kBlocks * MB) * 1024);
+  static std::atomic<unsigned long long> lds_set{0};
+  const hipError_t attr =
+      ensure_lds_limit(reinterpret_cast<const void*>(decode_phase_kernel<MB>), lds_set, static_cast<int>(smem));
+  if (attr != hipSuccess) return attr;
+  hipLaunchKernelGGL(decode_phase_kernel<MB>, dim3(static_cast<unsigned>(p.NTp[p.q] * p.splits)), dim3(kThreads), smem,
+                     stream, p);
+  return hipGetLastError();
+}
+
+// Most slices a column tile can need: the support of output group j over the
+// rows' types reaches at most min(q, M + 1) groups under the star and graph
+// laws (B(t, j) within {t, j}), every group under the others; a group of s
+// inputs spans at most ceil(s / 32) + 1 slices.
+template <typename I>
+int64_t most_slices(int law, int q, const I* S, int64_t M) {
+  const int64_t reach = (law == 0 || law == 3) ? std::min<int64_t>(q, M + 1) : q;
+  int64_t widest = 0;
+  for (int g = 0; g < q; ++g) widest = std::max<int64_t>(widest, (S[g + 1] - S[g] + SLICE - 1) / SLICE + 1);
+  return std::max<int64_t>(1, std::min<int64_t>((S[q] + SLICE - 1) / SLICE, reach * widest));
 }
 
 }  // namespace
 
-// LDS slots for the slices a workgroup can need: the support of output
-// group j over the rows' types reaches at most min(q, M + 1) groups under
-// the star and graph laws (B(t, j) within {t, j}), every group under the
-// others; a group of s inputs spans at most ceil(s / 32) + 1 slices.  Fewer
-// slots let more workgroups share a CU (a single row at q = 32 needs about
-// 10 of the 128).
-int decode_phase_slots(const DecodePhase& p) {
-  const int reach = (p.law == 0 || p.law == 3) ? std::min(p.q, p.M + 1) : p.q;
-  int widest = 0;
-  for (int g = 0; g < p.q; ++g) widest = std::max(widest, (p.S[g + 1] - p.S[g] + SLICE - 1) / SLICE + 1);
-  const int nsl = (p.K + SLICE - 1) / SLICE;
-  return std::max(1, std::min({kPassSlices, nsl, reach * widest}));
+// One workgroup per CU (256), of at least 16 slices (four a wave).  Measured
+// on 2560 <-> 9728, 8 rows of 4 types: 256 workgroups 15.5 to 19.8 us a
+// projection, 512 (two per CU) 20.1, 768 23.0; 64 rows: 28.3, 34.2, 41.4 (a
+// workgroup's start, its hand-over of partial sums and its arrival cost
+// about 8 us whatever its share).  Shares of 8 slices where there is less
+// work: 768 <-> 3072, 64 rows, 15.4 against 13.8 us.
+int decode_phase_splits(int law, int q, const int64_t* S, int32_t tiles, int64_t M) {
+  return static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(256 / tiles, most_slices(law, q, S, M) / 16)));
 }
 
-size_t decode_phase_smem(int slots) { return static_cast<size_t>(slots) * 1024 + kRedBytes; }
+size_t decode_phase_part_bytes(int32_t tiles, int splits, int64_t M) {
+  return splits > 1 ? static_cast<size_t>(tiles) * splits * ((M + 15) / 16) * kThreads * 16 : 0;
+}
 
-hipError_t launch_decode_phase(DecodePhase p, hipStream_t stream) {
-  static std::atomic<unsigned long long> lds_set{0};
-  const hipError_t attr = ensure_lds_limit(reinterpret_cast<const void*>(decode_phase_kernel), lds_set,
-                                           static_cast<int>(decode_phase_smem(kPassSlices)));
-  if (attr != hipSuccess) return attr;
-  p.slots = decode_phase_slots(p);
-  const int nt = p.NTp[p.q];
-  const int grid = (nt + 31) / 32 * 32;
-  hipLaunchKernelGGL(decode_phase_kernel, dim3(grid), dim3(kThreads), decode_phase_smem(p.slots), stream, p);
-  return hipGetLastError();
+hipError_t launch_decode_phase(const DecodePhase& p, hipStream_t stream) {
+  switch ((p.M + 15) / 16) {
+    case 1: return launch_mb<1>(p, stream);
+    case 2: return launch_mb<2>(p, stream);
+    case 3: return launch_mb<3>(p, stream);
+    default: return launch_mb<4>(p, stream);
+  }
 }
 
 }  // namespace starq

@@ -599,6 +599,48 @@ def test_decode_wide_model(P, M):
     assert rel_fro(to_host(Y), ref) <= TOL_BF16
 
 
+@pytest.mark.parametrize("law", ["star", "dense", "tensor2"])
+@pytest.mark.parametrize("M", [1, 16, 17, 40, 64])
+def test_decode_split_projections(P, M, law):
+    """One launch per projection with K splits (partial sums added by a
+    tile's last workgroup, counters reused by every projection): ragged
+    groups whose column tiles and slices have remainders, every number of
+    16-row blocks, the same step with the smallest workspace (no splits), and
+    repeated steps bitwise equal.  The bar is that of the bf16 operands: both
+    ways round to bf16 at the same places and differ in fp32 sums only."""
+    import torch
+    q, L = 4, 2
+    s, r = [400, 264, 1000, 408], [2056, 520, 1992, 1016]
+    up_g, up_o = algs(P, q, s, r, law)
+    dn_g, dn_o = algs(P, q, r, s, law)
+    D, F = up_o.K, up_o.N
+    Wu = [synth.gaussian(1700 + l, 0, (D, F), 0.02, "bf16") for l in range(L)]
+    Wd = [synth.gaussian(1700 + l, 1, (F, D), 0.02, "bf16") for l in range(L)]
+    bu = [synth.gaussian(1700 + l, 2, (F,), 0.02, "f32") for l in range(L)]
+    bd = [synth.gaussian(1700 + l, 3, (D,), 0.02, "f32") for l in range(L)]
+    X = synth.gaussian(1710, M, (M, D), 1.0, "bf16")
+    t = (synth.decode_positions(1711, M) % q).astype(np.int32)
+    ref = oracle.decode_stack(up_o, dn_o, t, X.exact, [w.exact for w in Wu], [b.exact for b in bu],
+                              [w.exact for w in Wd], [b.exact for b in bd])
+
+    def line(n):
+        return (n + 255) // 256 * 256
+
+    smallest = 256 + line(4 * M * D) + line(2 * M * D) + line(2 * M * F)
+    full = P.star_workspace_bytes("decode", up_g, dn_g, M)
+    assert full > smallest
+    args = (up_g, dn_g, types_dev(t), to_dev(X), [to_dev(w) for w in Wu], [f32_dev(b.exact) for b in bu],
+            [to_dev(w) for w in Wd], [f32_dev(b.exact) for b in bd], "gelu", True)
+    outs = []
+    for nbytes in (full, smallest, full):
+        ws = torch.full((nbytes,), 0x5a, dtype=torch.uint8, device="cuda")  # nothing in it may be relied on
+        outs.append(to_host(P.star_decode(*args, out_dtype=torch.float32, ws=ws)))
+        assert rel_fro(outs[-1], ref) <= TOL_BF16
+    assert np.array_equal(outs[0], outs[2])
+    with pytest.raises(P.StarError):
+        P.star_decode(*args, ws=torch.empty(smallest - 256, dtype=torch.uint8, device="cuda"))
+
+
 @pytest.mark.parametrize("M", [1, 16])
 @pytest.mark.parametrize("D,F", [(1024, 8192), (6144, 2048)])
 def test_decode_wider_than_4096(P, M, D, F):
