@@ -356,15 +356,15 @@ star_status star_proj_bwd_weight_planned(const star_algebra *alg, int64_t M, con
 /* Tile size of the forward product for bf16 operands (Sec. "Kernel Scaling
  * on Transformer Shapes": the algebraic kernel's tile is calibrated per
  * shape).  STAR_TILES_AUTO, the default, takes tiles of 64 rows x 128
- * columns when the 256 x 256 tiles would be at most three quarters full
+ * columns when the large tiles would be at most three quarters full
  * (rows taken as spread evenly over the types) and a tile contracts over
  * fewer than 1024 input features on average (K for the dense law, two
- * groups' worth otherwise), or when they would be fewer than 128; else
- * tiles of 256 rows x 256 columns, or x 192 columns (star and dense laws)
- * where those pad fewer output columns (groups 384 wide) and an estimate of
- * the persistent kernel's tile deal favours them.  STAR_TILES_WIDE (256 x
- * 256), STAR_TILES_WIDE192 (256 x 192 for the star and dense laws, 256 x
- * 256 for the others) and STAR_TILES_SMALL force one size.  Input groups
+ * groups' worth otherwise), or when they would be fewer than 128.  The
+ * large tiles are 256 rows x 256 columns, or x 192 columns (not the graph
+ * law) where those pad fewer output columns (groups 192 or 384 wide) and an
+ * estimate of the persistent kernel's tile deal favours them.
+ * STAR_TILES_WIDE (256 x 256), STAR_TILES_WIDE192 (256 x 192; 256 x 256 for
+ * the graph law) and STAR_TILES_SMALL force one size.  Input groups
  * narrower than 64 always take the small tiles, fp32 operands always their
  * own kernel.  Applies to star_proj_fwd, star_proj_fwd_planned and the
  * projections of star_ffn_fwd.  Process-wide (every device and stream),

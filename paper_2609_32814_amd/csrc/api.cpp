@@ -158,8 +158,8 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
   return n;
 }
 
-// Column-tile width of the pipelined bf16 kernel: 256, or 192 (star and
-// dense laws) where the launch's estimated makespan is shorter, a 192-wide
+// Column-tile width of the pipelined bf16 kernel: 256, or 192 (not the
+// graph law) where the launch's estimated makespan is shorter, a 192-wide
 // K step counted as 0.9 of a 256-wide one (its copies and per-step costs do
 // not shrink with its MFMAs).  The estimate deals the two passes' tiles (K
 // steps each, in the kernel's order, rows taken as spread evenly over the
@@ -169,7 +169,10 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
 // measured pairs: 8192 x 768 -> 3072 at q = 2 (192: 512 tiles, one long and
 // one short per CU), the 384-wide groups of 16384 x 3072 -> 768 (192: no
 // padding), and the weight gradient 768 x 3072 over 16384 rows (256: at 192
-// the split count drops to 4 and the diagonal tiles run long).
+// the split count drops to 4 and the diagonal tiles run long).  The tensor
+// law's 192- and 384-wide groups take them for the same reason (16384 rows,
+// 768 <-> 1536, q = 4: activation gradients 59 and 67 -> 52 and 58 us,
+// weight gradient 98 -> 87 us).
 double deal_makespan(const std::vector<int32_t>* passes, double epi) {
   constexpr int kGrid = 256, kSlots = kGrid / 8;
   double worst = 0.0;
@@ -200,10 +203,16 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
     const int64_t ns = nsplit_rule(mt * col_tiles(a, true, tn), M);
     for (int i = 0; i < q; ++i)
       for (int j = 0; j < q; ++j) {
-        const bool diag = i == j || a.law == STAR_LAW_DENSE;
-        const int st = steps_of(((diag ? M : per) + ns - 1) / ns);
-        passes[i == j ? 0 : 1].insert(passes[i == j ? 0 : 1].end(), tiles_of(a.s(i), tm) * tiles_of(a.r(j), tn) * ns,
-                                      st);
+        int64_t rows = i == j || a.law == STAR_LAW_DENSE ? M : per;
+        bool first = i == j;
+        if (a.law == STAR_LAW_TENSOR2) {
+          int n = 0;  // the types whose support pairs the two groups
+          for (int x = 0; x < q; ++x) n += host_in_support(a, x, j, i) ? 1 : 0;
+          rows = n * per;
+          first = 2 * n > q;
+        }
+        const int st = steps_of((rows + ns - 1) / ns);
+        passes[first ? 0 : 1].insert(passes[first ? 0 : 1].end(), tiles_of(a.s(i), tm) * tiles_of(a.r(j), tn) * ns, st);
       }
     return deal_makespan(passes, 1.0 * tm * tn / (256 * 256));
   }
@@ -214,6 +223,17 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
       for (int j = 0; j < q; ++j) {
         const int ct = tiles_of(fwd ? a.r(j) : a.s(j), tn);
         int st;
+        if (a.law == STAR_LAW_TENSOR2) {
+          int n = 0;
+          st = 0;
+          for (int x = 0; x < q; ++x)
+            if (fwd ? host_in_support(a, i, j, x) : host_in_support(a, i, x, j)) {
+              st += steps_of(fwd ? a.s(x) : a.r(x));
+              ++n;
+            }
+          passes[2 * n > q ? 0 : 1].insert(passes[2 * n > q ? 0 : 1].end(), ct, st);
+          continue;
+        }
         if (a.law == STAR_LAW_DENSE) st = steps_of(fwd ? a.K() : a.N());
         else if (fwd) st = steps_of(a.s(j)) + (j != i ? steps_of(a.s(i)) : 0);
         else st = j == i ? steps_of(a.N()) : steps_of(a.r(j));
@@ -234,7 +254,7 @@ int padded_cols(const Alg& a, bool over_r, int tn) {
   return static_cast<int>(col_tiles(a, over_r, tn) * tn);
 }
 int async_tile_n(const Alg& a, int mode, int64_t M, bool act) {
-  if (a.law != STAR_LAW_STAR && a.law != STAR_LAW_DENSE) return 256;
+  if (a.law == STAR_LAW_GRAPH) return 256;
   const bool over_r = mode != kModeBwdData;
   if (padded_cols(a, over_r, 192) >= padded_cols(a, over_r, 256)) return 256;
   return 0.9 * async_makespan(a, mode, M, 256, 192, act) < async_makespan(a, mode, M, 256, 256, act) ? 192 : 256;
@@ -247,7 +267,7 @@ struct TileShape {
   int tm, tn;
 };
 TileShape async_tiles_weight(const Alg& a, int64_t M) {
-  if (a.law != STAR_LAW_STAR && a.law != STAR_LAW_DENSE) return {256, 256};
+  if (a.law == STAR_LAW_GRAPH) return {256, 256};
   auto padded = [&](int tm, int tn) {
     int64_t rows = 0;
     for (int g = 0; g < a.q; ++g) rows += static_cast<int64_t>(tiles_of(a.s(g), tm)) * tm;
@@ -473,12 +493,16 @@ star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_E
 // operands the register-staged one.  `upper` bounds the number of tiles of
 // the register-staged kernel.
 // The forward takes the small-tile kernel (64 rows x 128 columns) when the
-// wide kernel's 256 x 256 tiles would be at most three quarters full (rows
-// taken as spread evenly over the types; a group's last column tile counts
-// its empty columns) or too few to fill the chip, and when an input group is
-// narrower than 64 (a 64-wide K step would span groups).  The bar was set
-// by timing both kernels on the projection shapes of the paper's kernel
-// study (M = 512, 2048, 8192; q = 4 to 64).
+// wide kernel's tiles (256 x 256, or 256 x 192 where async_tile_n takes
+// those) would be at most three quarters full (rows taken as spread evenly
+// over the types; a group's last column tile counts its empty columns) or
+// too few to fill the chip, and when an input group is narrower than 64 (a
+// 64-wide K step would span groups).  The bar was set by timing both kernels
+// on the projection shapes of the paper's kernel study (M = 512, 2048, 8192;
+// q = 4 to 64).  The fill is that of the tiles that would run: groups 384
+// wide fill 192-wide tiles, and judged by 256-wide ones 16384 x 768 -> 1536
+// took the small tiles (star, q = 4: 47.6 against 34.6 us; tensor law
+// 1536 -> 768: 77.5 against 54.5 us).
 std::atomic<int> g_fwd_tiles{STAR_TILES_AUTO};
 
 bool use_narrow_fwd(const GemmParams& p) {
@@ -490,14 +514,15 @@ bool use_narrow_fwd(const GemmParams& p) {
   if (static_cast<int64_t>(p.M) < p.q) return true;
   const double m = static_cast<double>(p.M) / p.q;  // rows per type
   const double row_tiles = std::ceil(m / 256.0);
+  const int tn = async_tile_n(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE);
   double cols = 0.0, col_tiles = 0.0;
   for (int g = 0; g < p.q; ++g) {
     const int w = p.R[g + 1] - p.R[g];
     cols += w;
-    col_tiles += (w + 255) / 256;
+    col_tiles += (w + tn - 1) / tn;
   }
   if (col_tiles == 0.0) return true;
-  const double fill = (m / (256.0 * row_tiles)) * (cols / (256.0 * col_tiles));
+  const double fill = (m / (256.0 * row_tiles)) * (cols / (tn * col_tiles));
   // A tile's mean contraction: K for the dense law, about two groups' worth
   // otherwise.  Over 1024 or more features the 256 x 256 tiles run their
   // MFMAs at a higher rate than the small tiles lose to padding (measured:
@@ -548,7 +573,7 @@ hipError_t launch_proj_gemm(int mode, const GemmParams& p, hipStream_t stream) {
     if (mode == kModeFwd) {
       const int forced = g_fwd_tiles.load(std::memory_order_relaxed);
       if (forced == STAR_TILES_WIDE) tn = 256;
-      if (forced == STAR_TILES_WIDE192) tn = p.law == STAR_LAW_STAR || p.law == STAR_LAW_DENSE ? 192 : 256;
+      if (forced == STAR_TILES_WIDE192) tn = p.law == STAR_LAW_GRAPH ? 256 : 192;
     }
     pa.tile_n = tn;
     pa.NTp[0] = 0;

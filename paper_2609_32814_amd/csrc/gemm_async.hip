@@ -788,11 +788,11 @@ hipError_t launch_one(const GemmParams& p, int64_t upper, int cus, hipStream_t s
   return hipGetLastError();
 }
 
-// the 192-wide and 192-high tiles are built for the star and dense laws
-// only, the 192-high ones for the weight gradient
+// the 192-wide tiles are built for every law but the graph law, the
+// 192-high ones for the weight gradient
 template <int MODE, int LAW, int ACT>
 hipError_t launch_tn(const GemmParams& p, int64_t upper, int cus, hipStream_t stream) {
-  if constexpr (LAW <= 1) {
+  if constexpr (LAW <= 2) {
     if (p.tile_m == 256 && p.tile_n == 192) return launch_one<MODE, LAW, ACT, 256, 192>(p, upper, cus, stream);
     if constexpr (MODE == kModeBwdWeight) {
       if (p.tile_m == 192 && p.tile_n == 256) return launch_one<MODE, LAW, ACT, 192, 256>(p, upper, cus, stream);

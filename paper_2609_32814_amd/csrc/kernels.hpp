@@ -48,7 +48,7 @@ struct GemmParams {
   float* dbias_part;  // [nsplit][N] when nsplit > 1
   int32_t nsplit;
   // bf16 pipelined kernel: rows and columns of a C tile (256 x 256, 256 x
-  // 192 for the star and dense laws, 192 x 256 for their weight gradient);
+  // 192 except for the graph law, 192 x 256 for the weight gradient);
   // p.NTp counts column tiles of that width, p.MTp row tiles of that height
   int32_t tile_m, tile_n;
   // law 3 (graph algebra): bit j of adj[i] marks the edge i -> j, bit i of

@@ -364,6 +364,38 @@ def test_bwd_weight_parity(P, law, dtype, q, s, r, M):
     assert np.array_equal(to_host(dW2), to_host(dW)) and np.array_equal(to_host(db2), to_host(db))
 
 
+@pytest.mark.parametrize("law", ["tensor2", "graph"])
+@pytest.mark.parametrize("s,r", [([192] * 4, [384] * 4), ([384, 192, 576, 192], [192, 384, 200, 392])])
+def test_192_wide_tiles_tensor_law(P, law, s, r):
+    """The tensor law's products on tiles 192 wide (forward, activation
+    gradient) and 192 high (weight gradient), which its 192- and 384-wide
+    groups select (the graph law keeps 256 x 256), whole and with remainders."""
+    import torch
+    edges = [[int(i != j and (i + j) % 2) for j in range(4)] for i in range(4)] if law == "graph" else None
+    ga = P.Algebra(4, s, r, law, edges)
+    oa = oracle.Alg(4, tuple(s), tuple(r), law, edges) if edges else oracle.Alg(4, tuple(s), tuple(r), law)
+    M = 1500
+    X = synth.gaussian(480, 0, (M, oa.K), 1.0, "bf16")
+    W = synth.gaussian(480, 1, (oa.K, oa.N), 0.05, "bf16")
+    dY = synth.gaussian(480, 2, (M, oa.N), 1.0, "bf16")
+    Zp = synth.gaussian(480, 3, (M, oa.K), 1.0, "bf16")
+    t = np.random.default_rng(481).integers(0, 4, M).astype(np.int32)
+    td = types_dev(t)
+    prev = P.star_set_fwd_tiles("wide192")
+    try:
+        Y = P.star_proj_fwd(ga, td, to_dev(X), to_dev(W), out_dtype=torch.float32)
+    finally:
+        P.star_set_fwd_tiles(prev)
+    assert rel_fro(to_host(Y), oracle.proj_fwd(oa, t, X.exact, W.exact)[0]) <= TOL_BF16
+    dX = P.star_proj_bwd_data(ga, td, to_dev(dY), to_dev(W), Z_prev=to_dev(Zp), act_prev="gelu",
+                              out_dtype=torch.float32)
+    ref = oracle.proj_bwd_data(oa, t, dY.exact, W.exact, Zprev=Zp.exact, act_prev="gelu")
+    assert rel_fro(to_host(dX), ref) <= TOL_BF16
+    dW, db = P.star_proj_bwd_weight(ga, td, to_dev(X), to_dev(dY))
+    rW, rb = oracle.proj_bwd_weight(oa, t, X.exact, dY.exact)
+    assert rel_fro(to_host(dW), rW) <= TOL_BF16 and rel_fro(to_host(db), rb) <= TOL_BF16
+
+
 @pytest.mark.parametrize("r", [[384, 392], [1024, 1032]])
 def test_bwd_weight_out_of_range_types_left_out(P, r):
     """Rows whose type is outside [0, q) are left out of the weight and bias
