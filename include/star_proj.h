@@ -185,7 +185,9 @@ star_status star_proj_bwd_data(const star_algebra *alg, int64_t M, const int32_t
  *   dY     device [M, N], dtype dyt == xt
  *   dW     device float[K, N]
  *   dbias  device float[N] or NULL
- *   ws     at least star_workspace_bytes(STAR_OP_BWD_WEIGHT, alg, NULL, M) bytes
+ *   ws     star_workspace_bytes(STAR_OP_BWD_WEIGHT, alg, NULL, M) bytes, most of
+ *          them partial sums of row ranges; where bf16 operands want more of
+ *          those than fp32 ones, less room means fewer ranges
  */
 star_status star_proj_bwd_weight(const star_algebra *alg, int64_t M, const int32_t *row_type,
                                  const void *X, star_dtype xt, const void *dY, star_dtype dyt,

@@ -142,15 +142,6 @@ int bwd_weight_nsplit(const Alg& a, int64_t M) {
   return static_cast<int>(std::max<int64_t>(ns, 1));
 }
 
-// Weight gradient with bf16 operands (pipelined kernel, 256-row tiles of
-// tn columns): the same rule on its own tile count.
-int64_t nsplit_rule(int64_t base, int64_t M) {
-  int64_t ns = (256 + base - 1) / base;
-  ns = std::min<int64_t>(ns, 8);
-  ns = std::min<int64_t>(ns, std::max<int64_t>(1, M / 1024));
-  return std::max<int64_t>(ns, 1);
-}
-
 // Column tiles of width tn over the output groups (r) or the input groups.
 int64_t col_tiles(const Alg& a, bool over_r, int tn) {
   int64_t n = 0;
@@ -173,10 +164,10 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
 // law's 192- and 384-wide groups take them for the same reason (16384 rows,
 // 768 <-> 1536, q = 4: activation gradients 59 and 67 -> 52 and 58 us,
 // weight gradient 98 -> 87 us).
-double deal_makespan(const std::vector<int32_t>* passes, double epi) {
+double deal_makespan(const std::vector<int32_t>* passes, double epi, int xcds = 8) {
   constexpr int kGrid = 256, kSlots = kGrid / 8;
   double worst = 0.0;
-  for (int x = 0; x < 8; ++x) {
+  for (int x = 0; x < xcds; ++x) {
     double load[kSlots] = {};
     int64_t v = 0;
     for (int ps = 0; ps < 2; ++ps) {
@@ -191,31 +182,11 @@ double deal_makespan(const std::vector<int32_t>* passes, double epi) {
   return worst;
 }
 int steps_of(int64_t w) { return static_cast<int>((w + 63) / 64); }
-// mode: the kernel's (forward, activation gradient, weight gradient); tm
-// the tile height (the weight gradient's, over the input groups)
-double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act) {
+// mode: the kernel's (forward, activation gradient)
+double async_makespan(const Alg& a, int mode, int64_t M, int tn, bool act) {
   std::vector<int32_t> passes[2];
   const int q = a.q;
   const int64_t per = (M + q - 1) / q;  // rows of a type
-  if (mode == kModeBwdWeight) {
-    int64_t mt = 0;
-    for (int g = 0; g < q; ++g) mt += tiles_of(a.s(g), tm);
-    const int64_t ns = nsplit_rule(mt * col_tiles(a, true, tn), M);
-    for (int i = 0; i < q; ++i)
-      for (int j = 0; j < q; ++j) {
-        int64_t rows = i == j || a.law == STAR_LAW_DENSE ? M : per;
-        bool first = i == j;
-        if (a.law == STAR_LAW_TENSOR2) {
-          int n = 0;  // the types whose support pairs the two groups
-          for (int x = 0; x < q; ++x) n += host_in_support(a, x, j, i) ? 1 : 0;
-          rows = n * per;
-          first = 2 * n > q;
-        }
-        const int st = steps_of((rows + ns - 1) / ns);
-        passes[first ? 0 : 1].insert(passes[first ? 0 : 1].end(), tiles_of(a.s(i), tm) * tiles_of(a.r(j), tn) * ns, st);
-      }
-    return deal_makespan(passes, 1.0 * tm * tn / (256 * 256));
-  }
   const int rt = tiles_of(per, kTileM);
   const bool fwd = mode == kModeFwd;
   for (int i = 0; i < q; ++i)
@@ -257,39 +228,104 @@ int async_tile_n(const Alg& a, int mode, int64_t M, bool act) {
   if (a.law == STAR_LAW_GRAPH) return 256;
   const bool over_r = mode != kModeBwdData;
   if (padded_cols(a, over_r, 192) >= padded_cols(a, over_r, 256)) return 256;
-  return 0.9 * async_makespan(a, mode, M, 256, 192, act) < async_makespan(a, mode, M, 256, 256, act) ? 192 : 256;
+  return 0.9 * async_makespan(a, mode, M, 192, act) < async_makespan(a, mode, M, 256, act) ? 192 : 256;
 }
-// Weight gradient: 256 x 256, 256 x 192 (columns over 384-wide output
-// groups) or 192 x 256 (rows over 384-wide input groups), the one that pads
-// the fewest dW cells, if the deal estimate agrees (a smaller tile counted
-// as 0.9 of a 256 x 256 one per step).
-struct TileShape {
-  int tm, tn;
+// Weight gradient: the tile shape (256 x 256, 256 x 192 for output groups
+// that 192 fits better, 192 x 256 for such input groups) and the number of
+// row ranges that the contractions of each pass are cut into.
+struct WeightPlan {
+  int tm = 256, tn = 256;
+  int nsplit = 1, nsplit1 = 1;
 };
-TileShape async_tiles_weight(const Alg& a, int64_t M) {
-  if (a.law == STAR_LAW_GRAPH) return {256, 256};
+// The row types that the weight gradient of block (i, j) contracts over.
+int weight_types(const Alg& a, int i, int j) {
+  if (a.law == STAR_LAW_DENSE) return a.q;
+  if (a.law == STAR_LAW_STAR) return i == j ? a.q : 1;
+  if (a.law == STAR_LAW_GRAPH)
+    return i == j ? 1 + __builtin_popcountll(a.adj_in[j] & ~(1ull << j)) : static_cast<int>((a.adj[i] >> j) & 1ull);
+  int n = 0;
+  for (int x = 0; x < a.q; ++x) n += host_in_support(a, x, j, i) ? 1 : 0;
+  return n;
+}
+bool weight_first_pass(const Alg& a, int i, int j, int types) {
+  if (a.law == STAR_LAW_DENSE) return true;
+  if (a.law == STAR_LAW_TENSOR2) return 2 * types > a.q;
+  if (a.law == STAR_LAW_GRAPH) return types >= 2;
+  return i == j;
+}
+// Splits are chosen for the shortest estimated deal (deal_makespan, steps of
+// 64 rows) plus the partial sums: every item writes a tile of them and a
+// second kernel reads them all.  A block of pass 1 contracts over at most c1
+// of the q types, so it gets that share of pass 0's splits and the items of
+// both passes come out about as long: with one count for all, 16384 rows of
+// q = 4 types, 768 x 1536, ran 64 items of 32 steps beside 192 of 8 (star)
+// and took as long as the dense product with twice the work.  What a split
+// costs, in steps of about 1.8 us: kItem for its tile of partials (written
+// by all CUs at once), and the bytes the second kernel reads at 4.5 TB/s.
+WeightPlan weight_plan_shape(const Alg& a, int64_t M, int tm, int tn, int most, double* cost) {
+  int64_t count[2][kMaxQGroups + 1] = {};  // tiles per pass and number of types
+  double cells[2] = {};                    // dW cells per pass
+  int c1 = 1;
+  for (int i = 0; i < a.q; ++i)
+    for (int j = 0; j < a.q; ++j) {
+      const int n = weight_types(a, i, j), ps = weight_first_pass(a, i, j, n) ? 0 : 1;
+      count[ps][n] += static_cast<int64_t>(tiles_of(a.s(i), tm)) * tiles_of(a.r(j), tn);
+      cells[ps] += static_cast<double>(a.s(i)) * a.r(j);
+      if (ps == 1) c1 = std::max(c1, n);
+    }
+  constexpr double kItem = 4.0, kStepUs = 1.8, kReadBytesUs = 4.5e6;
+  const double rate = tm == 256 && tn == 256 ? 1.0 : 0.9;  // of a smaller tile's step
+  WeightPlan best{tm, tn, 1, 1};
+  *cost = 0.0;
+  for (int ns = 1; ns <= most; ++ns) {
+    const int ns1 = a.law == STAR_LAW_DENSE ? ns : std::max(1, (ns * c1 + a.q - 1) / a.q);
+    std::vector<int32_t> passes[2];
+    for (int ps = 0; ps < 2; ++ps) {
+      const int s = ps == 0 ? ns : ns1;
+      for (int n = a.q; n >= 0; --n) {
+        const int64_t rows = (M * n / a.q + s - 1) / s;
+        passes[ps].insert(passes[ps].end(), static_cast<size_t>(count[ps][n] * s), steps_of(rows));
+      }
+    }
+    const double read = ns > 1 ? (cells[0] * ns + cells[1] * ns1) * 4.0 / kReadBytesUs / kStepUs : 0.0;
+    // (the first XCD's share of a pass is its longest items)
+    const double c = rate * deal_makespan(passes, ns > 1 ? kItem : 1.0, 1) + read;
+    if (ns == 1 || c < *cost) {
+      *cost = c;
+      best.nsplit = ns;
+      best.nsplit1 = ns1;
+    }
+  }
+  return best;
+}
+// most: splits at most (rows per split >= 1024 in any case)
+WeightPlan weight_plan(const Alg& a, int64_t M, int most = 16) {
+  most = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(most, M / 1024)));
   auto padded = [&](int tm, int tn) {
     int64_t rows = 0;
     for (int g = 0; g < a.q; ++g) rows += static_cast<int64_t>(tiles_of(a.s(g), tm)) * tm;
     return rows * padded_cols(a, true, tn);
   };
-  const double base = async_makespan(a, kModeBwdWeight, M, 256, 256, false);
-  TileShape best{256, 256};
-  int64_t best_pad = padded(256, 256);
-  for (const TileShape c : {TileShape{256, 192}, TileShape{192, 256}}) {
-    const int64_t pad = padded(c.tm, c.tn);
-    if (pad < best_pad && 0.9 * async_makespan(a, kModeBwdWeight, M, c.tm, c.tn, false) < base) {
-      best = c;
-      best_pad = pad;
+  double cost = 0.0;
+  WeightPlan best = weight_plan_shape(a, M, 256, 256, most, &cost);
+  if (a.law == STAR_LAW_GRAPH) return best;
+  const int64_t pad = padded(256, 256);
+  for (const auto& s : {std::pair<int, int>{256, 192}, std::pair<int, int>{192, 256}}) {
+    if (padded(s.first, s.second) >= pad) continue;
+    double c = 0.0;
+    const WeightPlan w = weight_plan_shape(a, M, s.first, s.second, most, &c);
+    if (c < cost) {
+      cost = c;
+      best = w;
     }
   }
   return best;
 }
-int bwd_weight_nsplit_async(const Alg& a, int64_t M) {
-  const TileShape ts = async_tiles_weight(a, M);
-  int64_t mt = 0;
-  for (int g = 0; g < a.q; ++g) mt += tiles_of(a.s(g), ts.tm);
-  return static_cast<int>(nsplit_rule(mt * col_tiles(a, true, ts.tn), M));
+
+int64_t widest_output(const Alg& a) {
+  int64_t w = 0;
+  for (int g = 0; g < a.q; ++g) w = std::max(w, a.r(g));
+  return w;
 }
 
 constexpr int kColSumChunks = 64;  // row chunks of the bias-gradient column sums
@@ -301,11 +337,11 @@ struct BwdWs {
   PlanWs plan;
   int nsplit = 1;
   size_t partial = 0, dbias_part = 0;
-  int nsplit_a = 1;
+  WeightPlan wp;
   size_t partial_a = 0, colsum = 0;
   size_t end = 0;
 };
-BwdWs bwd_weight_layout(const Alg& a, int64_t M) {
+BwdWs bwd_weight_layout(const Alg& a, int64_t M, const WeightPlan& wp) {
   BwdWs w;
   w.plan = plan_layout(M, a.q);
   w.nsplit = bwd_weight_nsplit(a, M);
@@ -317,15 +353,26 @@ BwdWs bwd_weight_layout(const Alg& a, int64_t M) {
     cur = align_up(cur + sizeof(float) * static_cast<size_t>(w.nsplit) * a.N());
   }
   const size_t end32 = cur;
-  w.nsplit_a = bwd_weight_nsplit_async(a, M);
+  w.wp = wp;
   cur = w.plan.end;
-  if (w.nsplit_a > 1) {
+  if (wp.nsplit > 1) {
     w.partial_a = cur;
-    cur = align_up(cur + sizeof(float) * static_cast<size_t>(w.nsplit_a) * a.K() * a.N());
+    cur = align_up(cur + sizeof(float) * static_cast<size_t>(a.K()) *
+                             (static_cast<size_t>(wp.nsplit1) * a.N() +
+                              static_cast<size_t>(wp.nsplit - wp.nsplit1) * widest_output(a)));
   }
   w.colsum = cur;
   cur = align_up(cur + sizeof(float) * static_cast<size_t>(kColSumChunks) * a.N());
   w.end = std::max(end32, cur);
+  return w;
+}
+
+// The layout with the splits that run best, or with as many as fit in
+// `room` bytes.
+BwdWs bwd_weight_fit(const Alg& a, int64_t M, size_t room) {
+  BwdWs w = bwd_weight_layout(a, M, weight_plan(a, M));
+  for (int most = w.wp.nsplit - 1; w.end > room && most >= 1; --most)
+    w = bwd_weight_layout(a, M, weight_plan(a, M, most));
   return w;
 }
 
@@ -465,7 +512,7 @@ void fill_common(GemmParams& p, const Alg& a, int64_t M, int elem, const int32_t
     p.adj[g] = a.adj[g];
     p.adj_in[g] = a.adj_in[g];
   }
-  p.nsplit = 1;
+  p.nsplit = p.nsplit1 = 1;
 }
 
 // the law and group widths of a parameter block, for host-side tile choices
@@ -514,22 +561,27 @@ bool use_narrow_fwd(const GemmParams& p) {
   if (static_cast<int64_t>(p.M) < p.q) return true;
   const double m = static_cast<double>(p.M) / p.q;  // rows per type
   const double row_tiles = std::ceil(m / 256.0);
-  const int tn = async_tile_n(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE);
-  double cols = 0.0, col_tiles = 0.0;
-  for (int g = 0; g < p.q; ++g) {
-    const int w = p.R[g + 1] - p.R[g];
-    cols += w;
-    col_tiles += (w + tn - 1) / tn;
-  }
-  if (col_tiles == 0.0) return true;
-  const double fill = (m / (256.0 * row_tiles)) * (cols / (tn * col_tiles));
   // A tile's mean contraction: K for the dense law, about two groups' worth
-  // otherwise.  Over 1024 or more features the 256 x 256 tiles run their
-  // MFMAs at a higher rate than the small tiles lose to padding (measured:
-  // 16384 rows, 3072 -> 768 at q = 2, three quarters filled, is 30 % faster
-  // on them).
+  // otherwise.  Over 1024 or more features the large tiles run their MFMAs at
+  // a higher rate than the small tiles lose to padding (measured: 16384 rows,
+  // 3072 -> 768 at q = 2, three quarters filled, is 30 % faster on them).
   const double kc = p.law == STAR_LAW_DENSE ? p.K : std::min<double>(p.K, 2.0 * p.K / p.q);
-  return (fill <= 0.75 && kc < 1024.0) || p.q * row_tiles * col_tiles < 128.0;
+  auto narrow = [&](int tn) {
+    double cols = 0.0, col_tiles = 0.0;
+    for (int g = 0; g < p.q; ++g) {
+      const int w = p.R[g + 1] - p.R[g];
+      cols += w;
+      col_tiles += (w + tn - 1) / tn;
+    }
+    if (col_tiles == 0.0) return true;
+    const double fill = (m / (256.0 * row_tiles)) * (cols / (tn * col_tiles));
+    return (fill <= 0.75 && kc < 1024.0) || p.q * row_tiles * col_tiles < 128.0;
+  };
+  // (the estimate behind async_tile_n costs host time: asked only where the
+  // two widths disagree)
+  const bool n256 = narrow(256), n192 = narrow(192);
+  if (n256 == n192) return n256;
+  return async_tile_n(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE) == 192 ? n192 : n256;
 }
 
 // The small-tile forward: column tiles per output group, then the launch.
@@ -669,7 +721,7 @@ size_t star_workspace_bytes(int32_t op, const star_algebra* alg, const star_alge
     case STAR_OP_FFN_FWD:
       return plan_layout(M, a.q).end;
     case STAR_OP_BWD_WEIGHT:
-      return bwd_weight_layout(a, M).end;
+      return bwd_weight_fit(a, M, SIZE_MAX).end;
     case STAR_OP_DECODE: {
       Alg d;
       if (parse_alg(alg2, d) != STAR_OK) return 0;
@@ -856,7 +908,7 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
   if ((X && !aligned16(X)) || (dY && !aligned16(dY)) || !aligned16(dW) ||
       (dbias && !aligned4(dbias)) || (plan && !aligned16(plan)))
     return STAR_ERR_ALIGN;
-  const BwdWs bw = bwd_weight_layout(a, M);
+  const BwdWs bw = bwd_weight_fit(a, M, ws_bytes);
   const bool pipelined = xt == STAR_BF16;
   const bool need_ws = pipelined || bw.nsplit > 1 || (a.law == STAR_LAW_GRAPH && dbias);
   if (need_ws && M > 0 && (!ws || ws_bytes < bw.end)) return STAR_ERR_WORKSPACE;
@@ -875,20 +927,23 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
   if (pipelined) {
     // every tile contracts over a range of type-sorted positions; the
     // kernel reads the rows of X and dY at those positions through perm
-    const TileShape ts = async_tiles_weight(a, M);
-    p.tile_m = ts.tm;
-    p.tile_n = ts.tn;
+    p.tile_m = bw.wp.tm;
+    p.tile_n = bw.wp.tn;
     fill_tiles(p.NTp, a.R, a.q, p.tile_n);
     fill_tiles(p.MTp, a.S, a.q, p.tile_m);
     p.A = X;
     p.B = dY;
     p.dW = dW;
-    p.nsplit = bw.nsplit_a;
-    if (bw.nsplit_a > 1) p.partial = at<float>(ws, bw.partial_a);
+    p.nsplit = bw.wp.nsplit;
+    p.nsplit1 = bw.wp.nsplit1;
+    p.rmax = static_cast<int32_t>(widest_output(a));
+    if (p.nsplit > 1) p.partial = at<float>(ws, bw.partial_a);
     const int64_t upper = static_cast<int64_t>(p.MTp[a.q]) * p.NTp[a.q] * p.nsplit;
     st = hip_status(launch_gemm_async(kModeBwdWeight, p, upper, cu_count(), stream));
-    if (st == STAR_OK && bw.nsplit_a > 1)
-      st = hip_status(launch_sum_partials(p.partial, p.nsplit, static_cast<int64_t>(p.K) * p.N, dW, stream));
+    if (st == STAR_OK && p.nsplit > 1)
+      st = hip_status(p.nsplit == p.nsplit1
+                          ? launch_sum_partials(p.partial, p.nsplit, static_cast<int64_t>(p.K) * p.N, dW, stream)
+                          : launch_block_reduce(p, stream));
     if (st != STAR_OK || !dbias) return st;
     // dbias = column sums of dY over the rows of valid type, in fixed chunks
     const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
@@ -904,7 +959,7 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
   // the graph law's diagonal tiles do not contract over every row, so its
   // bias gradient is summed apart (below)
   p.dbias = a.law == STAR_LAW_GRAPH ? nullptr : dbias;
-  p.nsplit = bw.nsplit;
+  p.nsplit = p.nsplit1 = bw.nsplit;
   if (bw.nsplit > 1) {
     p.partial = at<float>(ws, bw.partial);
     p.dbias_part = at<float>(ws, bw.dbias_part);
@@ -933,7 +988,7 @@ star_status star_proj_bwd_weight(const star_algebra* alg, int64_t M, const int32
   if ((X && !aligned16(X)) || (dY && !aligned16(dY)) || !aligned16(dW) ||
       (dbias && !aligned4(dbias)))
     return STAR_ERR_ALIGN;
-  const BwdWs bw = bwd_weight_layout(a, M);
+  const BwdWs bw = bwd_weight_fit(a, M, ws_bytes);
   if (!ws || ws_bytes < bw.end) return STAR_ERR_WORKSPACE;
   if (!aligned16(ws)) return STAR_ERR_ALIGN;
   if (M > 0) {

@@ -444,6 +444,50 @@ __global__ void split_reduce_kernel(const float* __restrict__ part, int nsplit, 
   }
 }
 
+// The same for partials whose blocks have a pass's number of splits each:
+// a workgroup takes 1024 consecutive columns of one row of dW (its input
+// group is uniform), a thread four of them (one output group: widths are
+// multiples of 8).
+template <int LAW>
+__global__ __launch_bounds__(256) void block_reduce_kernel(const GemmParams p) {
+  const int32_t k = blockIdx.y + blockIdx.z * gridDim.y;
+  const int32_t n = (blockIdx.x * 256 + threadIdx.x) * 4;
+  if (k >= p.K || n >= p.N) return;
+  int i = 0, j = 0;
+  while (k >= p.S[i + 1]) ++i;
+  for (int lo = 0, hi = p.q - 1; lo < hi;) {  // the last group that starts at or before n
+    const int mid = (lo + hi + 1) >> 1;
+    if (n >= p.R[mid]) lo = mid;
+    else hi = mid - 1;
+    j = lo;
+  }
+  bool first;  // pass 0
+  if constexpr (LAW == 2) first = tensor_in_pass(p, sel_for(kModeBwdWeight, LAW, 0), i, j);
+  else if constexpr (LAW == 3) first = graph_in_pass(p, sel_for(kModeBwdWeight, LAW, 0), i, j);
+  else first = i == j;
+  const int ns = first ? p.nsplit : p.nsplit1;
+  const int64_t at = static_cast<int64_t>(k) * p.N + n, kn = static_cast<int64_t>(p.K) * p.N;
+  // the further splits of pass 0
+  const float* more = p.partial + p.nsplit1 * kn + static_cast<int64_t>(k) * p.rmax + n - p.R[j];
+  auto part = [&](int s) {
+    return s < p.nsplit1 ? p.partial + s * kn + at : more + static_cast<int64_t>(s - p.nsplit1) * p.K * p.rmax;
+  };
+  float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+  for (int s0 = 0; s0 < ns; s0 += 8) {
+    float4 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+      v[u] = s0 + u < ns ? *reinterpret_cast<const float4*>(part(s0 + u)) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      if (s0 + u < ns) {
+        acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w;
+      }
+    }
+  }
+  *reinterpret_cast<float4*>(p.dW + at) = acc;
+}
+
 __global__ void fill_zero_kernel(float* __restrict__ dst, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x)
@@ -502,6 +546,17 @@ hipError_t launch_sum_partials(const float* part, int n_parts, int64_t n, float*
                                hipStream_t stream) {
   const int blocks = static_cast<int>(std::min<int64_t>(2048, (n / 4 + 255) / 256 + 1));
   hipLaunchKernelGGL(split_reduce_kernel, dim3(blocks), dim3(256), 0, stream, part, n_parts, n, out);
+  return hipGetLastError();
+}
+
+hipError_t launch_block_reduce(const GemmParams& p, hipStream_t stream) {
+  const unsigned gy = static_cast<unsigned>(std::min(p.K, 32768));
+  const dim3 grid((p.N + 1023) / 1024, gy, (p.K + gy - 1) / gy);
+  switch (p.law) {
+    case 2: hipLaunchKernelGGL(block_reduce_kernel<2>, grid, dim3(256), 0, stream, p); break;
+    case 3: hipLaunchKernelGGL(block_reduce_kernel<3>, grid, dim3(256), 0, stream, p); break;
+    default: hipLaunchKernelGGL(block_reduce_kernel<0>, grid, dim3(256), 0, stream, p); break;
+  }
   return hipGetLastError();
 }
 

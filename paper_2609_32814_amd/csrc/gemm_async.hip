@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   constexpr int MI = L::MI, NI = L::NI, TMW = L::TMW, TNW = L::TNW;
   extern __shared__ __attribute__((aligned(16))) char smem[];
   // row tiles per class: [0] BM rows, [1] BM / 2 rows (weight gradient:
-  // row tiles x splits, both)
+  // row tiles x splits of pass 0 and of pass 1)
   __shared__ int32_t units_s[2][kMaxQGroups];
   __shared__ int32_t offs_s[kMaxQGroups + 1];
   // tile prefix sums per class: pass 0, pass 1, pass 1 in half-height tiles
@@ -182,7 +182,9 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   __syncthreads();
   for (int i = threadIdx.x; i < q; i += kThreads) {
     if constexpr (MODE == kModeBwdWeight) {
-      units_s[0][i] = units_s[1][i] = (p.MTp[i + 1] - p.MTp[i]) * p.nsplit;  // row tiles of K group i x splits
+      // row tiles of K group i x splits, per pass
+      units_s[0][i] = (p.MTp[i + 1] - p.MTp[i]) * p.nsplit;
+      units_s[1][i] = (p.MTp[i + 1] - p.MTp[i]) * p.nsplit1;
     } else {
       // row tiles of type class i
       units_s[0][i] = (offs_s[i + 1] - offs_s[i] + BM - 1) / BM;
@@ -196,7 +198,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     int32_t run = 0;
     for (int i = 0; i < q; ++i) {
       pfx_s[threadIdx.x][i] = run;
-      run += units_s[threadIdx.x == 2 ? 1 : 0][i] * ncols_sel(p, sel, i);
+      run += units_s[threadIdx.x == 2 || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0][i] * ncols_sel(p, sel, i);
     }
     pfx_s[threadIdx.x][q] = run;
   }
@@ -253,19 +255,20 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     int cls = 0;
     while (logical >= pf[cls + 1]) ++cls;
     const bool hh = ps == 1 && half1;
+    const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
     t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
-                                     units_s[hh ? 1 : 0][cls], offs_s, hh ? BM / 2 : TM);
+                                     units_s[un][cls], offs_s, hh ? BM / 2 : TM);
     return true;
   };
 
   // weight gradient: a split whose row range is empty contributes zeros
   auto zero_tile = [&](const Tile& t) {
-    float* out = p.nsplit > 1 ? p.partial + static_cast<int64_t>(t.split) * p.K * p.N : p.dW;
+    const SumsAt out = sums_at(p, t);
     for (int idx = threadIdx.x; idx < TM * TN / 4; idx += kThreads) {
       const int32_t r = t.rstart + idx / (TN / 4);
       const int32_t c = t.cstart + (idx % (TN / 4)) * 4;
       if (r < t.rend && c < t.cend)
-        *reinterpret_cast<float4*>(out + static_cast<int64_t>(r) * p.N + c) = make_float4(0.f, 0.f, 0.f, 0.f);
+        *reinterpret_cast<float4*>(out.base + r * out.ld + c) = make_float4(0.f, 0.f, 0.f, 0.f);
     }
   };
 
@@ -641,11 +644,11 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     // ---- epilogue of tile ct ----
     if constexpr (MODE == kModeBwdWeight) {
       // dW rows k (C rows) x 4 consecutive columns n per lane group
-      float* out = p.nsplit > 1 ? p.partial + static_cast<int64_t>(ct.split) * p.K * p.N : p.dW;
+      const SumsAt out = sums_at(p, ct);
 #pragma unroll
       for (int mi = 0; mi < MI; ++mi) {
         const int32_t k = ct.rstart + wm * TMW + mi * 32 + lr;
-        float* yr = out + static_cast<int64_t>(k) * p.N + ct.cstart + wn * TNW + 4 * lh;
+        float* yr = out.base + k * out.ld + ct.cstart + wn * TNW + 4 * lh;
 #pragma unroll
         for (int ni = 0; ni < NI; ++ni)
 #pragma unroll

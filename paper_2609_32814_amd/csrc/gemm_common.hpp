@@ -130,6 +130,13 @@ __device__ __forceinline__ bool tensor_in_pass(const GemmParams& p, int sel, int
   return pass == 0 ? wide : !wide;
 }
 
+// the pass of a selector
+__device__ __forceinline__ int pass_of(int mode, int sel) {
+  if (sel >= kSelGraph) return (sel - kSelGraph) & 1;
+  if (sel >= kSelTensor) return (sel - kSelTensor) & 1;
+  return sel == (mode == kModeFwd ? kSelOnly : kSelExcept) ? 1 : 0;
+}
+
 __device__ __forceinline__ int ncols_sel(const GemmParams& p, int sel, int i) {
   const int nti = p.NTp[i + 1] - p.NTp[i];
   const int nt = p.NTp[p.q];
@@ -226,6 +233,7 @@ template <int MODE, int LAW, int BN, int BK>
 __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls, int32_t u,
                                           int32_t units, const int32_t* offs, int bm = BM) {
   Tile t;
+  const int32_t nsplit = pass_of(MODE, sel) == 0 ? p.nsplit : p.nsplit1;
   // Forward and activation gradient: column tiles vary fastest, so that the
   // tiles of one XCD chunk cover a few row tiles across all their column
   // tiles (their rows stay in that XCD's L2 while the weights stream).
@@ -280,8 +288,8 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
       t.seg0_lo = p.R[cg]; t.seg0_hi = p.R[cg + 1];
     }
   } else {
-    t.mt = ru / p.nsplit;
-    t.split = ru % p.nsplit;
+    t.mt = ru / nsplit;
+    t.split = ru % nsplit;
     t.cstart = p.R[cg] + nt * BN;
     t.cend = p.R[cg + 1];
     t.rstart = p.S[cls] + t.mt * bm;
@@ -302,7 +310,7 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
       a0 = 0; a1 = offs[p.q];
     }
     const int32_t len0 = a1 - a0, len = len0 + (b1 - b0);
-    const int32_t cs = (len + p.nsplit - 1) / p.nsplit;
+    const int32_t cs = (len + nsplit - 1) / nsplit;
     const int32_t c0 = min(len, t.split * cs), c1 = min(len, c0 + cs);
     t.seg0_lo = a0 + min(c0, len0);
     t.seg0_hi = a0 + min(c1, len0);
@@ -326,7 +334,7 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
         total += bound(x + 1) - bound(x);
       }
       if (MODE == kModeBwdWeight) {
-        const int32_t cs = (total + p.nsplit - 1) / p.nsplit;
+        const int32_t cs = (total + nsplit - 1) / nsplit;
         c0 = min(total, t.split * cs);
         c1 = min(total, c0 + cs);
       } else {
@@ -355,6 +363,19 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
   for (int k = 0; k < static_cast<int>(sizeof(Tile) / sizeof(int32_t)); ++k)
     f[k] = __builtin_amdgcn_readfirstlane(f[k]);
   return t;
+}
+
+// Where a weight-gradient tile's sums go: the element of row k and column n
+// of dW is at base[k ld + n].
+struct SumsAt {
+  float* base;
+  int64_t ld;
+};
+__device__ __forceinline__ SumsAt sums_at(const GemmParams& p, const Tile& t) {
+  if (p.nsplit <= 1) return {p.dW, p.N};
+  const int64_t kn = static_cast<int64_t>(p.K) * p.N;
+  if (t.split < p.nsplit1) return {p.partial + t.split * kn, p.N};
+  return {p.partial + p.nsplit1 * kn + static_cast<int64_t>(t.split - p.nsplit1) * p.K * p.rmax - p.R[t.cg], p.rmax};
 }
 
 // K range of step st of tile t: [lo, ...) with the end of its segment in hi

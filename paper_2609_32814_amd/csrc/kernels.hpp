@@ -44,9 +44,15 @@ struct GemmParams {
   // BWD_WEIGHT outputs
   float* dW;
   float* dbias;
-  float* partial;     // [nsplit][K][N] when nsplit > 1
+  // nsplit > 1: [nsplit1][K][N], then [nsplit - nsplit1][K][rmax] for the
+  // further splits of pass 0 (diagonal blocks all, for the laws whose passes
+  // differ: a row's columns are those of its own group; rmax the widest)
+  float* partial;
+  int32_t rmax;
   float* dbias_part;  // [nsplit][N] when nsplit > 1
-  int32_t nsplit;
+  // BWD_WEIGHT: row ranges that a contraction is cut into, for the tiles of
+  // pass 0 (the contractions over more row types) and of pass 1
+  int32_t nsplit, nsplit1;
   // bf16 pipelined kernel: rows and columns of a C tile (256 x 256, 256 x
   // 192 except for the graph law, 192 x 256 for the weight gradient);
   // p.NTp counts column tiles of that width, p.MTp row tiles of that height
@@ -127,6 +133,9 @@ hipError_t launch_swiglu_bwd(int64_t n, int elem, const void* dh, const void* zg
                              void* dzu, hipStream_t stream);
 hipError_t launch_add(int64_t n, int elem, const void* a, const void* b, void* out, hipStream_t stream);
 hipError_t launch_split_reduce(const GemmParams& p, hipStream_t stream);
+// dW = the sum of its blocks' partials, each block over its pass's splits
+// (p.nsplit > 1; blocks with one split are copied).
+hipError_t launch_block_reduce(const GemmParams& p, hipStream_t stream);
 // out[i] = sum over c < n_parts of part[c * n + i], in c order.
 hipError_t launch_sum_partials(const float* part, int n_parts, int64_t n, float* out,
                                hipStream_t stream);

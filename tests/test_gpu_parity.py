@@ -396,6 +396,39 @@ def test_192_wide_tiles_tensor_law(P, law, s, r):
     assert rel_fro(to_host(dW), rW) <= TOL_BF16 and rel_fro(to_host(db), rb) <= TOL_BF16
 
 
+@pytest.mark.parametrize("law,s,r", [
+    ("star", [136, 64, 200, 72], [96, 264, 64, 120]),
+    ("dense", [136, 64, 200, 72], [96, 264, 64, 120]),
+    ("tensor2", [136, 64, 200, 72], [96, 264, 64, 120]),
+    ("graph", [136, 64, 200, 72], [96, 264, 64, 120]),
+    ("star", [392, 264, 520, 384], [384, 520, 264, 400]),
+    ("tensor2", [392, 264, 520, 384], [384, 520, 264, 400]),
+])
+def test_bwd_weight_splits_per_pass(P, law, s, r):
+    """The blocks that contract over more row types are cut into more row
+    ranges than the others, the further ones' sums kept apart at the widest
+    group's width: ragged groups, and the smaller numbers of splits that a
+    smaller workspace leaves room for."""
+    import torch
+    edges = [[int(i != j and (i + j) % 2) for j in range(4)] for i in range(4)] if law == "graph" else None
+    M = 9001
+    ga = P.Algebra(4, s, r, law, edges)
+    oa = oracle.Alg(4, tuple(s), tuple(r), law, edges)
+    X = synth.gaussian(490, 0, (M, oa.K), 1.0, "bf16")
+    dY = synth.gaussian(490, 1, (M, oa.N), 1.0, "bf16")
+    t = np.random.default_rng(491).integers(0, 4, M).astype(np.int32)
+    rW, rb = oracle.proj_bwd_weight(oa, t, X.exact, dY.exact)
+    full = P.star_workspace_bytes("bwd_weight", ga, None, M)
+    wide = oa.K > 1024 and law == "star"  # the splits, not the fp32 path's workspace, set the size
+    for take in (0, 256, 4 * oa.K * oa.N) if wide else (0,):
+        ws = torch.full((full - take,), 0x7f, dtype=torch.uint8, device="cuda")
+        dW, db = P.star_proj_bwd_weight(ga, types_dev(t), to_dev(X), to_dev(dY), ws=ws)
+        assert rel_fro(to_host(dW), rW) <= TOL_BF16 and rel_fro(to_host(db), rb) <= TOL_BF16
+    with pytest.raises(P.StarError):
+        P.star_proj_bwd_weight(ga, types_dev(t), to_dev(X), to_dev(dY),
+                               ws=torch.empty(4 * M, dtype=torch.uint8, device="cuda"))
+
+
 @pytest.mark.parametrize("r", [[384, 392], [1024, 1032]])
 def test_bwd_weight_out_of_range_types_left_out(P, r):
     """Rows whose type is outside [0, q) are left out of the weight and bias
