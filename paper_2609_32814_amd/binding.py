@@ -132,6 +132,8 @@ class Algebra:
                             ctypes.cast(self._r, ctypes.POINTER(ctypes.c_int64)), LAWS[law],
                             ctypes.cast(self._e, ctypes.POINTER(ctypes.c_uint8)) if self._e is not None
                             else None)
+        self.ref = ctypes.byref(self._c)
+        self._K, self._N = sum(self.s), sum(self.r)
 
     @classmethod
     def equal(cls, q: int, K: int, N: int, law: str = "star", edges=None) -> "Algebra":
@@ -141,15 +143,11 @@ class Algebra:
 
     @property
     def K(self) -> int:
-        return sum(self.s)
+        return self._K
 
     @property
     def N(self) -> int:
-        return sum(self.r)
-
-    @property
-    def ref(self):
-        return ctypes.byref(self._c)
+        return self._N
 
     def with_law(self, law: str) -> "Algebra":
         return Algebra(self.q, self.s, self.r, law, self.edges)
@@ -163,12 +161,15 @@ class Algebra:
         return f"Algebra(q={self.q}, s={self.s}, r={self.r}, law={self.law!r})"
 
 
+# (plain integers: ctypes converts them by the declared argument types, and a
+# c_void_p object or a torch Stream object per argument took a third of the
+# 15 us that a call spent in Python)
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr()) if t is not None else None
+    return t.data_ptr() if t is not None else None
 
 
-def _stream(device) -> ctypes.c_void_p:
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+def _stream(device) -> int:
+    return torch._C._cuda_getCurrentRawStream(device.index)
 
 
 def _check(status: int, where: str):
@@ -195,6 +196,9 @@ def _need(t, name: str, shape, dtypes=None, device=None):
     """Checks a tensor argument before its pointer crosses the ABI: a device
     tensor of the expected shape and dtype, dense in row-major order (the
     library reads every buffer as a plain row-major array)."""
+    if (isinstance(t, torch.Tensor) and t.shape == shape and (dtypes is None or t.dtype in dtypes)
+            and t.is_contiguous() and (device is None or t.device == device)):
+        return t
     if t is None:
         raise ValueError(f"{name} is required")
     if not isinstance(t, torch.Tensor):
@@ -212,7 +216,7 @@ def _need(t, name: str, shape, dtypes=None, device=None):
 
 def _gpu(device):
     """Every tensor of a call sits on `device`; it must be a GPU."""
-    if torch.device(device).type != "cuda":
+    if device.type != "cuda":
         raise ValueError("the library takes GPU tensors only")
 
 
@@ -738,9 +742,7 @@ class AttnShape:
         self._c = _CAttnShape(self.batch, self.seq_len, self.n_heads, self.n_kv_heads, self.head_dim,
                               self.q, LAWS[law])
 
-    @property
-    def ref(self):
-        return ctypes.byref(self._c)
+        self.ref = ctypes.byref(self._c)
 
     def with_law(self, law: str) -> "AttnShape":
         return AttnShape(self.batch, self.seq_len, self.n_heads, self.n_kv_heads, self.head_dim, self.q, law)
