@@ -101,21 +101,27 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
 
-// LDS tiles of one 64-key step: a plane per 16-byte feature chunk, each
-// plane the chunk of the 64 key rows in row order (1 KB, exactly one
-// global-to-LDS copy with lane = row), padded to kPlane bytes so that the
-// transposing reads of neighbouring planes fall on different banks.  The key
-// tile holds only the chunks of the selected groups F(i, j), packed in
-// chunk order; the value tile holds every chunk.
+// LDS tiles of one 64-key step: the key rows and the value rows, whole, in
+// row order, filled by copies of 1 KB in which 8 (head width 64) or 16 lanes
+// read one row's line.  (One copy per 16-byte chunk, a lane per key row,
+// touched 64 lines of the caches in each copy: 2 x 2777 positions, 32 heads
+// of 128 over 8, star law 259 -> 247 us, dense 367 -> 316; 16 x 1536, 12
+// heads of 64, dense 141 -> 131 us, star unchanged at 128, bound by the
+// softmax's vector work.)  Chunk c of row r sits at chunk c ^ swizzle(r):
+// a 16-lane pass of the score step's reads (one chunk of 16 rows) and a
+// 32-lane pass of the transposing value reads (4 chunks of 4 rows) then each
+// cover all 64 banks.
+template <int DH>
+__device__ __forceinline__ int key_swz(int r) { return DH == 64 ? (r >> 1) & 7 : r & 15; }
+template <int DH>
+__device__ __forceinline__ int value_swz(int r) { return DH == 64 ? 4 * ((r >> 1) & 1) : 4 * (r & 3); }
 constexpr int kStepKeys = 64;
 // 64-key blocks over all types the forward can index (positions up to
 // kAttnFwdMaxSeq plus a partial block per type), rounded up to the 256 block
 // flags one pass of a 256-thread workgroup writes
 constexpr int kFwdMaxBlocks = (kAttnFwdMaxSeq / kStepKeys + 32 + 255) / 256 * 256;
-constexpr int kPlane = 1024 + 64;
-
 template <int DH>
-constexpr int fwd_tile_bytes() { return (DH / 8) * kPlane; }
+constexpr int fwd_tile_bytes() { return kStepKeys * DH * 2; }
 template <int DH>
 constexpr int fwd_smem() { return 2 * 2 * fwd_tile_bytes<DH>(); }  // two stages of (K, V)
 
@@ -133,17 +139,18 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
   constexpr int NT = NW * 64;
   constexpr int NCH = DH / 32;  // 32-feature output chunks
   constexpr int KS = DH / 16;   // 16-feature contraction steps over a head
-  constexpr int CPR = DH / 8;   // 16-byte chunks (planes) per row
+  constexpr int CPR = DH / 8;   // 16-byte chunks per row
+  constexpr int ROWB = DH * 2;  // bytes of a row
   constexpr int TILE = fwd_tile_bytes<DH>();
-  extern __shared__ __attribute__((aligned(16))) char tiles[];  // [stage][K, V][planes]
+  extern __shared__ __attribute__((aligned(16))) char tiles[];  // [stage][K, V][rows]
   __shared__ int32_t qpos_s[kBlockRows];
   __shared__ int32_t kpos_s[2][kStepKeys];
   __shared__ int32_t off_s[32 + 1];
   __shared__ int32_t nstep_s[32];
   __shared__ uint64_t bits_s[kFwdMaxBlocks / 64];
-  // per key type j: F(i, j) as a group mask, the selected chunks as a mask,
-  // their count, the score scale (bits), then the selected chunks in order
-  __shared__ uint32_t tab_s[32][4 + 16];
+  // per key type j: the selected chunks in rotated order as a mask, and the
+  // score scale (bits)
+  __shared__ uint32_t tab_s[32][2];
 
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -207,18 +214,10 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
     const int j = threadIdx.x;
     const uint32_t fm = attn_fmask(p.law, q, i, j);
     uint32_t csel = 0;  // selected chunks, rotated order
-    int n = 0;
-    for (int ar = 0; ar < q; ++ar) {
-      const int a = (ar + i) % q;
-      if ((fm >> a) & 1u) {
-        csel |= ((1u << cpg) - 1u) << (ar * cpg);
-        for (int c = 0; c < cpg; ++c) tab_s[j][4 + n++] = a * cpg + c;
-      }
-    }
-    tab_s[j][0] = fm;
-    tab_s[j][1] = csel;
-    tab_s[j][2] = n;
-    tab_s[j][3] = __float_as_uint(kLog2e * __builtin_amdgcn_rsqf(static_cast<float>(__popc(fm) * m)));
+    for (int ar = 0; ar < q; ++ar)
+      if ((fm >> ((ar + i) % q)) & 1u) csel |= ((1u << cpg) - 1u) << (ar * cpg);
+    tab_s[j][0] = csel;
+    tab_s[j][1] = __float_as_uint(kLog2e * __builtin_amdgcn_rsqf(static_cast<float>(__popc(fm) * m)));
   }
   const int32_t off0 = p.offsets[0], off1 = p.offsets[1];
   int32_t kp_cur = off0 + lane < off1 ? p.perm[off0 + lane] : 0x7fffffff;
@@ -274,10 +273,12 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
   // holds the 8 features at rotated position 16 ks + 8 lh of row lr of each
   // tile, i.e. offset o of rotated group a' (physical group (a' + i) mod q)
   uint4 qf[QT][KS];
+  int koff[KS];  // the same features of key row lr in a key tile
 #pragma unroll
   for (int ks = 0; ks < KS; ++ks) {
     const int fr = 16 * ks + 8 * lh;
     const int fphys = ((fr / m + i) % q) * m + fr % m;
+    koff[ks] = lr * ROWB + (((fphys >> 3) ^ key_swz<DH>(lr)) << 4);
 #pragma unroll
     for (int u = 0; u < QT; ++u) {
       qf[u][ks] = make_uint4(0, 0, 0, 0);
@@ -314,22 +315,23 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
     const int32_t k = offs(it.j) + kStepKeys * it.c + lane;
     return k < offs(it.j + 1) ? p.perm[k] : 0x7fffffff;
   };
-  // global-to-LDS copies of a step's key planes (selected chunks only) and
-  // value planes; lane = key row
+  // global-to-LDS copies of a step's key and value rows (kp: the position of
+  // key row `lane`)
   const void* zero = g_attn_zero;
-  auto issue = [&](const It& it, int32_t kp, int stage) {
+  constexpr int RPC = 64 / CPR;  // rows of a copy
+  auto issue = [&](int32_t kp, int stage) {
     char* Kt = tiles + stage * 2 * TILE;
-    char* Vt = Kt + TILE;
-    const int nsel = static_cast<int>(tab(it.j, 2));
-    const bool ok = kp < p.S;
-    const uint16_t* krow = Kg + static_cast<int64_t>(ok ? kp : 0) * ldk;
-    const uint16_t* vrow = Vg + static_cast<int64_t>(ok ? kp : 0) * ldk;
-    for (int k = wave; k < nsel; k += NW) {
-      const int c = static_cast<int>(tab(it.j, 4 + k));
-      dma16(ok ? static_cast<const void*>(krow + 8 * c) : zero, lds_addr(Kt + k * kPlane));
+#pragma unroll
+    for (int k = 0; k < kStepKeys / RPC / NW; ++k) {
+      const int cp = wave + NW * k;
+      const int row = cp * RPC + lane / CPR, c = lane % CPR;
+      const int32_t pos = __shfl(kp, row);
+      const bool ok = pos < p.S;
+      const int64_t at = static_cast<int64_t>(ok ? pos : 0) * ldk;
+      dma16(ok ? static_cast<const void*>(Kg + at + 8 * (c ^ key_swz<DH>(row))) : zero, lds_addr(Kt + cp * 1024));
+      dma16(ok ? static_cast<const void*>(Vg + at + 8 * (c ^ value_swz<DH>(row))) : zero,
+            lds_addr(Kt + TILE + cp * 1024));
     }
-    for (int c = wave; c < CPR; c += NW)
-      dma16(ok ? static_cast<const void*>(vrow + 8 * c) : zero, lds_addr(Vt + c * kPlane));
   };
 
   // online softmax state of the lane's query in each tile (shared with lane
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
   if (T > 0) {
     wait_vm_all();
     if (wave == 0) kpos_s[0][lane] = kp_cur;
-    issue(cur, kp_cur, 0);
+    issue(kp_cur, 0);
   }
   for (int32_t s = 0; s < T; ++s) {
     wait_vm_all();    // this step's copies and the next step's positions
@@ -365,16 +367,15 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
     advance(nn);
     if (s + 1 < T) {
       if (wave == 0) kpos_s[(s + 1) & 1][lane] = kp_nxt;
-      issue(nxt, kp_nxt, (s + 1) & 1);
+      issue(kp_nxt, (s + 1) & 1);
       kp_nxt = load_kp(nn);
     }
 
     const char* Kt = tiles + (s & 1) * 2 * TILE;
     const char* Vt = Kt + TILE;
     const int32_t* kps = kpos_s[s & 1];
-    // chunk c of the head is plane popc(csel below c) of the key tile
-    const uint32_t csel = tab(cur.j, 1);
-    const float scale = __uint_as_float(tab(cur.j, 3));
+    const uint32_t csel = tab(cur.j, 0);
+    const float scale = __uint_as_float(tab(cur.j, 1));
     // first and last keys of the two halves (uniform)
     const int32_t kf0 = __builtin_amdgcn_readfirstlane(kps[0]), kf1 = __builtin_amdgcn_readfirstlane(kps[32]);
     const int32_t kl0 = __builtin_amdgcn_readfirstlane(kps[31]), kl1 = __builtin_amdgcn_readfirstlane(kps[63]);
@@ -385,25 +386,17 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
       f32x16_t sc[QT][2];
 #pragma unroll
       for (int t = 0; t < 2; ++t) {
-        const char* Krow = Kt + (32 * t + lr) * 16;
-        // rotated step ks uses key planes popc(csel below 2 ks) + lh; step 0
-        // (the query's own group) is always selected and starts the sum
+        // rotated step 0 (the query's own group) is always selected and
+        // starts the sum
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
           if (ks > 0 && !((csel >> (2 * ks)) & 3u)) continue;
-          uint4 kf;
-          if constexpr (!M8) {
-            // m >= 16: a step's 16 features lie in one group
-            const int pl = __popc(csel & ((1u << (2 * ks)) - 1u)) + lh;
-            kf = *reinterpret_cast<const uint4*>(Krow + pl * kPlane);
-          } else {
-            // m = 8: the halves of a step are two groups; a lane whose group
-            // is not selected reads plane 0 and contributes zeros
-            const int c = 2 * ks + lh;
-            const bool on = (csel >> c) & 1u;
-            const int pl = on ? __popc(csel & ((1u << c) - 1u)) : 0;
-            kf = *reinterpret_cast<const uint4*>(Krow + pl * kPlane);
-            if (!on) kf = make_uint4(0, 0, 0, 0);
+          uint4 kf = *reinterpret_cast<const uint4*>(Kt + 32 * t * ROWB + koff[ks]);
+          // m >= 16: a step's 16 features lie in one group.  m = 8: its
+          // halves are two groups, and a lane whose group is not selected
+          // contributes zeros.
+          if constexpr (M8) {
+            if (!((csel >> (2 * ks + lh)) & 1u)) kf = make_uint4(0, 0, 0, 0);
           }
 #pragma unroll
           for (int u = 0; u < QT; ++u) {
@@ -496,9 +489,9 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
           // of key rows row0 and row0 + 8; lane pp receives feature
           // 32 c + 16 (g & 1) + pp of those 4 + 4 rows
           const int f = 32 * c + 16 * (g & 1) + 4 * qq;
-          const char* a0 = Vt + (f >> 3) * kPlane + row0 * 16 + ((f >> 2) & 1) * 8;
+          const char* a0 = Vt + row0 * ROWB + (((f >> 3) ^ value_swz<DH>(row0)) << 4) + ((f >> 2) & 1) * 8;
           const uint2 w0 = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a0)));
-          const uint2 w1 = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a0 + 8 * 16)));
+          const uint2 w1 = __builtin_bit_cast(uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a0 + 8 * ROWB)));
           const uint4 vf = make_uint4(w0.x, w0.y, w1.x, w1.y);
 #pragma unroll
           for (int u = 0; u < QT; ++u)
