@@ -361,10 +361,10 @@ star_status star_proj_bwd_weight_planned(const star_algebra *alg, int64_t M, con
  * columns when the large tiles would be at most three quarters full
  * (rows taken as spread evenly over the types) and a tile contracts over
  * fewer than 1024 input features on average (K for the dense law, two
- * groups' worth otherwise), or when they would be fewer than 128.  The
- * large tiles are 256 rows x 256 columns, or x 192 columns (not the graph
- * law) where those pad fewer output columns (groups 192 or 384 wide) and an
- * estimate of the persistent kernel's tile deal favours them.
+ * groups' worth otherwise), or when they would be too few.  The large tiles
+ * are 256 or 128 rows x 256 columns, or x 192 columns where those pad fewer
+ * output columns (groups 192 or 384 wide), by an estimate of the persistent
+ * kernel's tile deal (256 x 256 only for the graph law).
  * STAR_TILES_WIDE (256 x 256), STAR_TILES_WIDE192 (256 x 192; 256 x 256 for
  * the graph law) and STAR_TILES_SMALL force one size.  Input groups
  * narrower than 64 always take the small tiles, fp32 operands always their

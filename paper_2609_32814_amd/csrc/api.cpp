@@ -183,11 +183,11 @@ double deal_makespan(const std::vector<int32_t>* passes, double epi, int xcds = 
 }
 int steps_of(int64_t w) { return static_cast<int>((w + 63) / 64); }
 // mode: the kernel's (forward, activation gradient)
-double async_makespan(const Alg& a, int mode, int64_t M, int tn, bool act) {
+double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act) {
   std::vector<int32_t> passes[2];
   const int q = a.q;
   const int64_t per = (M + q - 1) / q;  // rows of a type
-  const int rt = tiles_of(per, kTileM);
+  const int rt = tiles_of(per, tm);
   const bool fwd = mode == kModeFwd;
   for (int i = 0; i < q; ++i)
     for (int u = 0; u < rt; ++u)
@@ -213,10 +213,10 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tn, bool act) {
         const int ps = a.law == STAR_LAW_DENSE ? 0 : (fwd ? (j != i ? 0 : 1) : (j == i ? 0 : 1));
         passes[ps].insert(passes[ps].end(), ct, st);
       }
-  const double epi = (act ? (fwd ? 3.0 : 2.0) : 1.0) * tn / 256;
+  const double epi = (act ? (fwd ? 3.0 : 2.0) : 1.0) * tn * tm / (256 * 256);
   return deal_makespan(passes, epi);
 }
-// The default takes 192 only where it pads fewer C columns as well: without
+// The tiles are 192 wide only where that pads fewer C columns as well: without
 // padding to remove, the 192-wide tiles' extra re-reads of the row tiles
 // (a third more column tiles per row tile) made them slower on row types in
 // short runs (192 rows: 78 against 63 us for the dense 8192 x 768 -> 3072),
@@ -224,12 +224,37 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tn, bool act) {
 int padded_cols(const Alg& a, bool over_r, int tn) {
   return static_cast<int>(col_tiles(a, over_r, tn) * tn);
 }
-int async_tile_n(const Alg& a, int mode, int64_t M, bool act) {
-  if (a.law == STAR_LAW_GRAPH) return 256;
+// 128-row tiles take about 0.7 of a 256-row tile's step (128 x 256: 0.75 of a
+// 256 x 256 one, 128 x 192: 0.65), so they pay where 256-row tiles leave CUs
+// without a tile or a long tile beside a short one: 8192 rows, q = 2, 3072 ->
+// 768 on 256 x 192 tiles is 64 tiles of 48 steps and 64 of 24 on 256 CUs (76
+// us; 58 on 128 x 192), its counterpart's activation gradient 72 and 58, the
+// dense 4096 x 2048 x 2048 55 and 48; with twice the rows every CU has a
+// tile and 256 rows stay faster (80 and 85 us).
+struct TileShape {
+  int tm, tn;
+};
+TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
   const bool over_r = mode != kModeBwdData;
-  if (padded_cols(a, over_r, 192) >= padded_cols(a, over_r, 256)) return 256;
-  return 0.9 * async_makespan(a, mode, M, 192, act) < async_makespan(a, mode, M, 256, act) ? 192 : 256;
+  const bool try192 =
+      a.law != STAR_LAW_GRAPH && padded_cols(a, over_r, 192) < padded_cols(a, over_r, 256);
+  TileShape best{256, 256};
+  double cost = async_makespan(a, mode, M, 256, 256, act);
+  auto consider = [&](int tm, int tn, double rate, double margin) {
+    const double c = rate * async_makespan(a, mode, M, tm, tn, act);
+    if (c < margin * cost) {
+      cost = c;
+      best = {tm, tn};
+    }
+  };
+  if (try192) consider(256, 192, 0.9, 1.0);
+  if (a.law != STAR_LAW_GRAPH) {
+    consider(128, 256, 0.75, 0.95);
+    if (try192) consider(128, 192, 0.65, best.tm == 128 ? 1.0 : 0.95);
+  }
+  return best;
 }
+
 // Weight gradient: the tile shape (256 x 256, 256 x 192 for output groups
 // that 192 fits better, 192 x 256 for such input groups) and the number of
 // row ranges that the contractions of each pass are cut into.
@@ -540,13 +565,17 @@ star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_E
 // operands the register-staged one.  `upper` bounds the number of tiles of
 // the register-staged kernel.
 // The forward takes the small-tile kernel (64 rows x 128 columns) when the
-// wide kernel's tiles (256 x 256, or 256 x 192 where async_tile_n takes
+// wide kernel's tiles (256 x 256, or 256 x 192 where async_tiles takes
 // those) would be at most three quarters full (rows taken as spread evenly
 // over the types; a group's last column tile counts its empty columns) or
-// too few to fill the chip, and when an input group is narrower than 64 (a
-// 64-wide K step would span groups).  The bar was set by timing both kernels
+// too few to fill the chip (128 of 256 rows, or 192 of 128 rows: 2048 rows,
+// q = 2, 768 -> 3072 has 96 and 192, 21 us on the latter and 24 on the small
+// tiles; 4096 rows, 3072 -> 768 has 64 and 128, 55 and 48 us), and when an
+// input group is narrower than 64 (a 64-wide K step would span groups).  The bar was set by timing both kernels
 // on the projection shapes of the paper's kernel study (M = 512, 2048, 8192;
-// q = 4 to 64).  The fill is that of the tiles that would run: groups 384
+// q = 4 to 64); from 200 tiles on, 128-row tiles filled to 0.6 are enough
+// (the small tiles run at half the rate: 13013 x 1792 -> 3584, q = 16, 120
+// against 82 us; 12544 x 1728 -> 576, tensor law, 92 against 54).  The fill is that of the tiles that would run: groups 384
 // wide fill 192-wide tiles, and judged by 256-wide ones 16384 x 768 -> 1536
 // took the small tiles (star, q = 4: 47.6 against 34.6 us; tensor law
 // 1536 -> 768: 77.5 against 54.5 us).
@@ -566,6 +595,7 @@ bool use_narrow_fwd(const GemmParams& p) {
   // a higher rate than the small tiles lose to padding (measured: 16384 rows,
   // 3072 -> 768 at q = 2, three quarters filled, is 30 % faster on them).
   const double kc = p.law == STAR_LAW_DENSE ? p.K : std::min<double>(p.K, 2.0 * p.K / p.q);
+  const double half_tiles = std::ceil(m / 128.0);
   auto narrow = [&](int tn) {
     double cols = 0.0, col_tiles = 0.0;
     for (int g = 0; g < p.q; ++g) {
@@ -575,13 +605,16 @@ bool use_narrow_fwd(const GemmParams& p) {
     }
     if (col_tiles == 0.0) return true;
     const double fill = (m / (256.0 * row_tiles)) * (cols / (tn * col_tiles));
-    return (fill <= 0.75 && kc < 1024.0) || p.q * row_tiles * col_tiles < 128.0;
+    const double half_fill = (m / (128.0 * half_tiles)) * (cols / (tn * col_tiles));
+    const bool many = p.law != STAR_LAW_GRAPH && half_fill >= 0.6 && p.q * row_tiles * col_tiles >= 200.0;
+    return (fill <= 0.75 && kc < 1024.0 && !many) ||
+           (p.q * row_tiles * col_tiles < 128.0 && (p.law == STAR_LAW_GRAPH || p.q * half_tiles * col_tiles < 192.0));
   };
-  // (the estimate behind async_tile_n costs host time: asked only where the
+  // (the estimate behind async_tiles costs host time: asked only where the
   // two widths disagree)
   const bool n256 = narrow(256), n192 = narrow(192);
   if (n256 == n192) return n256;
-  return async_tile_n(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE) == 192 ? n192 : n256;
+  return async_tiles(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE).tn == 192 ? n192 : n256;
 }
 
 // The small-tile forward: column tiles per output group, then the launch.
@@ -620,17 +653,18 @@ hipError_t launch_proj_gemm(int mode, const GemmParams& p, hipStream_t stream) {
   if (p.elem == 1) {
     GemmParams pa = p;
     const int32_t* G = (mode == kModeFwd) ? p.R : p.S;  // output column groups
-    int tn = async_tile_n(alg_of(p), mode, p.M, p.act != STAR_ACT_NONE);
-    pa.tile_m = kTileM;
+    TileShape ts = async_tiles(alg_of(p), mode, p.M, p.act != STAR_ACT_NONE);
     if (mode == kModeFwd) {
       const int forced = g_fwd_tiles.load(std::memory_order_relaxed);
-      if (forced == STAR_TILES_WIDE) tn = 256;
-      if (forced == STAR_TILES_WIDE192) tn = p.law == STAR_LAW_GRAPH ? 256 : 192;
+      if (forced == STAR_TILES_WIDE) ts = {kTileM, 256};
+      if (forced == STAR_TILES_WIDE192) ts = {kTileM, p.law == STAR_LAW_GRAPH ? 256 : 192};
     }
-    pa.tile_n = tn;
+    pa.tile_m = ts.tm;
+    pa.tile_n = ts.tn;
+    const int tn = ts.tn;
     pa.NTp[0] = 0;
     for (int g = 0; g < p.q; ++g) pa.NTp[g + 1] = pa.NTp[g] + (G[g + 1] - G[g] + tn - 1) / tn;
-    const int64_t rows_upper = static_cast<int64_t>(p.M) / kTileM + p.q;
+    const int64_t rows_upper = static_cast<int64_t>(p.M) / pa.tile_m + p.q;
     return launch_gemm_async(mode, pa, rows_upper * pa.NTp[p.q], cu_count(), stream);
   }
   return launch_gemm(mode, p, stream);

@@ -118,10 +118,11 @@ __device__ __forceinline__ bool wave_rows_live(int row0, int32_t nrows) {
 // Tile shapes: TM rows x TN columns, 8 wavefronts.  256 x 256: waves 2 x 4
 // of 128 x 64; 256 x 192: waves 4 x 2 of 64 x 96 (groups 384 or 1536 wide
 // take whole tiles); 192 x 256 (weight gradient only, rows over 384-wide
-// input groups): waves 2 x 4 of 96 x 64.  The LDS tiles keep 256 rows and
+// input groups): waves 2 x 4 of 96 x 64; 128 x 256 and 128 x 192 (the other
+// products): waves 2 x 4 of 64 x 64 and 4 x 2 of 32 x 96.  The LDS tiles keep 256 rows and
 // 256 columns of room either way.
 template <int TM, int TN> struct Lay {
-  static_assert((TM == 256 && (TN == 256 || TN == 192)) || (TM == 192 && TN == 256), "tile shape");
+  static_assert(((TM == 256 || TM == 128) && (TN == 256 || TN == 192)) || (TM == 192 && TN == 256), "tile shape");
   static constexpr int WNW = TN == 256 ? 4 : 2;  // waves along N
   static constexpr int WMW = kWaves / WNW;        // waves along M
   static constexpr int TMW = TM / WMW;            // rows of a wave
@@ -153,7 +154,7 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
 
 template <int MODE, int LAW, int ACT, int TM, int TN>
 __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const GemmParams p) {
-  static_assert(MODE == kModeBwdWeight || TM == BM, "tiles of fewer rows: weight gradient only");
+  static_assert(MODE == kModeBwdWeight ? TM != 128 : TM != 192, "192 rows: weight gradient only; 128: the others");
   using L = Lay<TM, TN>;
   constexpr int MI = L::MI, NI = L::NI, TMW = L::TMW, TNW = L::TNW;
   extern __shared__ __attribute__((aligned(16))) char smem[];
@@ -187,8 +188,8 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
       units_s[1][i] = (p.MTp[i + 1] - p.MTp[i]) * p.nsplit1;
     } else {
       // row tiles of type class i
-      units_s[0][i] = (offs_s[i + 1] - offs_s[i] + BM - 1) / BM;
-      units_s[1][i] = (offs_s[i + 1] - offs_s[i] + BM / 2 - 1) / (BM / 2);
+      units_s[0][i] = (offs_s[i + 1] - offs_s[i] + TM - 1) / TM;
+      units_s[1][i] = (offs_s[i + 1] - offs_s[i] + TM / 2 - 1) / (TM / 2);
     }
   }
   __syncthreads();
@@ -214,7 +215,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   const int32_t n0 = pfx_s[0][q], n1 = pfx_s[1][q], ng = static_cast<int32_t>(gridDim.x);
   const int32_t whole_max = n1 > 2 * (ng - n0) ? 3 : 2;  // in pass-1 tiles
   const bool half1 =
-      MODE != kModeBwdWeight && LAW == 0 &&
+      MODE != kModeBwdWeight && TM == BM && LAW == 0 &&
       __builtin_amdgcn_readfirstlane(n1 > 0 && n0 <= ng && n0 + n1 > ng &&
                                      2 * (whole_max * ng - 2 * n0 - n1) >= ng) != 0;
   const int p1 = half1 ? 2 : 1;  // the prefix sums pass 1 uses
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     const bool hh = ps == 1 && half1;
     const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
     t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
-                                     units_s[un][cls], offs_s, hh ? BM / 2 : TM);
+                                     units_s[un][cls], offs_s, hh ? TM / 2 : TM);
     return true;
   };
 
@@ -458,6 +459,8 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     if constexpr (MODE == kModeBwdWeight) {
       g = rl[j] >= 0 ? static_cast<const void*>(Ag + static_cast<int64_t>(rl[j]) * p.K + wa_col) : zero;
     } else {
+      // (rows past the tile height are not copied)
+      if (j >= TM / 64) return;
       const bool ok = 8 * fa_chunk < klen;
       g = ok ? static_cast<const void*>(astep + static_cast<uint64_t>(aoff[j]) * 16) : zero;
     }
@@ -625,7 +628,8 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
             for (int x = 0; x < MI * NI; ++x) {
               if constexpr (decltype(on)::value)
                 mma(acc[x / NI][x % NI], fb[rs & 1][x % NI], fa[rs & 1][x / NI], uint16_t());
-              if (x == 1 || x == 3) {
+              constexpr int kB = MI * NI > 3 ? 3 : MI * NI - 1;
+              if (x == 1 || x == kB) {
                 __builtin_amdgcn_sched_barrier(0);
                 if (x == 1) copy_a(rs); else copy_b(rs);
                 __builtin_amdgcn_sched_barrier(0);
@@ -791,15 +795,19 @@ hipError_t launch_one(const GemmParams& p, int64_t upper, int cus, hipStream_t s
   return hipGetLastError();
 }
 
-// the 192-wide tiles are built for every law but the graph law, the
-// 192-high ones for the weight gradient
+// tiles other than 256 x 256 are built for every law but the graph law
 template <int MODE, int LAW, int ACT>
 hipError_t launch_tn(const GemmParams& p, int64_t upper, int cus, hipStream_t stream) {
   if constexpr (LAW <= 2) {
     if (p.tile_m == 256 && p.tile_n == 192) return launch_one<MODE, LAW, ACT, 256, 192>(p, upper, cus, stream);
     if constexpr (MODE == kModeBwdWeight) {
       if (p.tile_m == 192 && p.tile_n == 256) return launch_one<MODE, LAW, ACT, 192, 256>(p, upper, cus, stream);
+    } else {
+      if (p.tile_m == 128 && p.tile_n == 192) return launch_one<MODE, LAW, ACT, 128, 192>(p, upper, cus, stream);
     }
+  }
+  if constexpr (MODE != kModeBwdWeight && LAW <= 2) {
+    if (p.tile_m == 128 && p.tile_n == 256) return launch_one<MODE, LAW, ACT, 128, 256>(p, upper, cus, stream);
   }
   if (p.tile_m != 256 || p.tile_n != 256) return hipErrorInvalidValue;
   return launch_one<MODE, LAW, ACT, 256, 256>(p, upper, cus, stream);

@@ -53,8 +53,9 @@ struct GemmParams {
   // BWD_WEIGHT: row ranges that a contraction is cut into, for the tiles of
   // pass 0 (the contractions over more row types) and of pass 1
   int32_t nsplit, nsplit1;
-  // bf16 pipelined kernel: rows and columns of a C tile (256 x 256, 256 x
-  // 192 except for the graph law, 192 x 256 for the weight gradient);
+  // bf16 pipelined kernel: rows and columns of a C tile (256 x 256; except
+  // for the graph law also 256 x 192, and 192 x 256 for the weight gradient
+  // or 128 x 256 and 128 x 192 for the other products);
   // p.NTp counts column tiles of that width, p.MTp row tiles of that height
   int32_t tile_m, tile_n;
   // law 3 (graph algebra): bit j of adj[i] marks the edge i -> j, bit i of

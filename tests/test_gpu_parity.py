@@ -429,6 +429,36 @@ def test_bwd_weight_splits_per_pass(P, law, s, r):
                                ws=torch.empty(4 * M, dtype=torch.uint8, device="cuda"))
 
 
+@pytest.mark.parametrize("law,s,r,M", [
+    ("star", [384, 384], [512, 264], 701),       # 128 x 192 (activation gradient)
+    ("dense", [520, 256], [512, 264], 701),      # 128 x 256
+    ("tensor2", [192, 384, 200, 192], [256, 64, 72, 128], 1031),
+    ("star", [520, 512], [1536, 1544], 1601),    # the forward too
+    ("dense", [384, 776], [1152, 392], 1601),
+])
+def test_128_row_tiles(P, law, s, r, M):
+    """The tiles of 128 rows that forward and activation gradient take where
+    256-row ones leave CUs without a tile: ragged rows, groups, K steps."""
+    import torch
+    q = len(s)
+    ga, oa = algs(P, q, s, r, law)
+    X = synth.gaussian(495, 0, (M, oa.K), 1.0, "bf16")
+    W = synth.gaussian(495, 1, (oa.K, oa.N), 0.05, "bf16")
+    dY = synth.gaussian(495, 2, (M, oa.N), 1.0, "bf16")
+    Zp = synth.gaussian(495, 3, (M, oa.K), 1.0, "bf16")
+    b = synth.gaussian(495, 4, (oa.N,), 0.5, "f32")
+    t = np.random.default_rng(496).integers(0, q, M).astype(np.int32)
+    td = types_dev(t)
+    Y, Z = P.star_proj_fwd(ga, td, to_dev(X), to_dev(W), f32_dev(b.exact), "gelu", Z_out=True)
+    rY, rZ, _, _ = oracle.proj_fwd(oa, t, X.exact, W.exact, b.exact, "gelu", want_z=True)
+    assert rel_fro(to_host(Y), rY) <= TOL_BF16 and rel_fro(to_host(Z), rZ) <= TOL_BF16
+    for act in ("none", "gelu"):
+        dX = P.star_proj_bwd_data(ga, td, to_dev(dY), to_dev(W), Z_prev=None if act == "none" else to_dev(Zp),
+                                  act_prev=act, out_dtype=torch.float32)
+        ref = oracle.proj_bwd_data(oa, t, dY.exact, W.exact, Zprev=None if act == "none" else Zp.exact, act_prev=act)
+        assert rel_fro(to_host(dX), ref) <= TOL_BF16
+
+
 @pytest.mark.parametrize("r", [[384, 392], [1024, 1032]])
 def test_bwd_weight_out_of_range_types_left_out(P, r):
     """Rows whose type is outside [0, q) are left out of the weight and bias
