@@ -220,7 +220,11 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
 // padding to remove, the 192-wide tiles' extra re-reads of the row tiles
 // (a third more column tiles per row tile) made them slower on row types in
 // short runs (192 rows: 78 against 63 us for the dense 8192 x 768 -> 3072),
-// even where the deal favours them (1024-row runs: 57 against 63 us).
+// even where the deal favours them (1024-row runs: 57 against 63 us).  The
+// star law's forward takes them at equal padding too: its types alternate
+// (8192 x 768 -> 3072 with GELU, q = 2: cyclic types 50.7 against 55.0 us,
+// 192-row runs 62.8 and 63.8; at 4096 rows 31.8 against 35.6, and 38 with
+// unequal counts that add a row tile).
 int padded_cols(const Alg& a, bool over_r, int tn) {
   return static_cast<int>(col_tiles(a, over_r, tn) * tn);
 }
@@ -236,8 +240,9 @@ struct TileShape {
 };
 TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
   const bool over_r = mode != kModeBwdData;
-  const bool try192 =
-      a.law != STAR_LAW_GRAPH && padded_cols(a, over_r, 192) < padded_cols(a, over_r, 256);
+  const int pad192 = padded_cols(a, over_r, 192), pad256 = padded_cols(a, over_r, 256);
+  const bool try192 = a.law != STAR_LAW_GRAPH &&
+                      (pad192 < pad256 || (pad192 == pad256 && a.law == STAR_LAW_STAR && mode == kModeFwd));
   TileShape best{256, 256};
   double cost = async_makespan(a, mode, M, 256, 256, act);
   auto consider = [&](int tm, int tn, double rate, double margin) {
