@@ -347,6 +347,15 @@ star_status star_proj_bwd_data_planned(const star_algebra *alg, int64_t M, const
                                        star_dtype wt, const void *Z_prev, star_act act_prev,
                                        void *dX, star_dtype dxt, hipStream_t stream);
 
+/* dX = dY1 *_q^T W1 + dY2 *_q^T W2 in one product, summed in fp32: the input
+ * gradient of two projections of one input (a gated FFN's gate and up maps).
+ * bf16 operands (STAR_ERR_DTYPE otherwise); layouts, dX and errors as
+ * star_proj_bwd_data_planned without Z_prev. */
+star_status star_proj_bwd_data_pair_planned(const star_algebra *alg, int64_t M, const void *plan,
+                                            const void *dY1, const void *W1, const void *dY2,
+                                            const void *W2, star_dtype dt, void *dX, star_dtype dxt,
+                                            hipStream_t stream);
+
 /* star_proj_bwd_weight with a prebuilt plan.  ws holds the split partial
  * sums: at least star_workspace_bytes(STAR_OP_BWD_WEIGHT, alg, NULL, M)
  * bytes (may be NULL when that size equals star_plan_bytes(q, M)). */

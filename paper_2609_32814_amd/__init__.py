@@ -10,7 +10,7 @@ ImportError if the library has not been built
 _EXPORTS = (
     "LIB_PATH", "Algebra", "StarError",
     "star_count_macs", "star_count_products", "star_decode", "star_ffn_bwd", "star_ffn_fwd",
-    "star_plan_bytes", "star_proj_bwd_data", "star_proj_bwd_data_planned",
+    "star_plan_bytes", "star_proj_bwd_data", "star_proj_bwd_data_planned", "star_proj_bwd_data_pair_planned",
     "star_proj_bwd_weight", "star_proj_bwd_weight_planned", "star_proj_fwd",
     "star_proj_fwd_planned", "star_status_string", "star_type_plan", "star_validate_types",
     "star_workspace_bytes", "star_swiglu_fwd", "star_swiglu_bwd", "star_add", "star_swiglu_ffn_fwd",

@@ -79,6 +79,7 @@ def _load() -> ctypes.CDLL:
     lib.star_type_plan.argtypes = [i32, i64, P, P, sz, P]
     lib.star_proj_fwd_planned.argtypes = [A, i64, P, P, E, P, E, P, E, P, P, E, P]
     lib.star_proj_bwd_data_planned.argtypes = [A, i64, P, P, E, P, E, P, E, P, E, P]
+    lib.star_proj_bwd_data_pair_planned.argtypes = [A, i64, P, P, P, P, P, E, P, E, P]
     lib.star_proj_bwd_weight_planned.argtypes = [A, i64, P, P, E, P, E, P, P, P, sz, P]
     lib.star_swiglu_fwd.argtypes = [i64, P, P, E, P, P]
     lib.star_swiglu_bwd.argtypes = [i64, P, P, P, E, P, P, P]
@@ -95,6 +96,7 @@ def _load() -> ctypes.CDLL:
     for name in ("star_proj_fwd", "star_proj_bwd_data", "star_proj_bwd_weight", "star_ffn_fwd",
                  "star_decode", "star_count_products", "star_count_macs", "star_validate_types",
                  "star_type_plan", "star_proj_fwd_planned", "star_proj_bwd_data_planned",
+                 "star_proj_bwd_data_pair_planned",
                  "star_proj_bwd_weight_planned", "star_swiglu_fwd", "star_swiglu_bwd", "star_add",
                  "star_decode_gated", "star_decode_status", "star_decode_noalloc", "star_attn_fwd",
                  "star_attn_decode", "star_swiglu_merged_fwd", "star_swiglu_up_fwd_planned"):
@@ -341,6 +343,25 @@ def star_proj_bwd_data_planned(alg: Algebra, plan: torch.Tensor, dY: torch.Tenso
     _check(LIB.star_proj_bwd_data_planned(alg.ref, M, _ptr(plan), _ptr(dY), _dt(dY), _ptr(W),
                                           _dt(W), _ptr(Z_prev), ACTS[act_prev], _ptr(dX),
                                           _dt(dX), _stream(dev)), "star_proj_bwd_data_planned")
+    return dX
+
+
+def star_proj_bwd_data_pair_planned(alg: Algebra, plan: torch.Tensor, dY1: torch.Tensor, W1: torch.Tensor,
+                                    dY2: torch.Tensor, W2: torch.Tensor, dX=None, out_dtype=None):
+    """dX = dY1 *_q^T W1 + dY2 *_q^T W2, one product (bf16 operands)."""
+    M, dev = _rows(dY1, "dY1", alg.N)
+    _need(dY1, "dY1", (M, alg.N), _BF16, dev)
+    _need(dY2, "dY2", (M, alg.N), _BF16, dev)
+    _need(W1, "W1", (alg.K, alg.N), _BF16, dev)
+    _need(W2, "W2", (alg.K, alg.N), _BF16, dev)
+    _need(plan, "plan", tuple(plan.shape), None, dev)
+    if dX is None:
+        dX = torch.empty((M, alg.K), dtype=out_dtype or dY1.dtype, device=dev)
+    _need(dX, "dX", (M, alg.K), _FLOATS, dev)
+    _gpu(dev)
+    _check(LIB.star_proj_bwd_data_pair_planned(alg.ref, M, _ptr(plan), _ptr(dY1), _ptr(W1), _ptr(dY2), _ptr(W2),
+                                               _dt(dY1), _ptr(dX), _dt(dX), _stream(dev)),
+           "star_proj_bwd_data_pair_planned")
     return dX
 
 
@@ -720,9 +741,12 @@ def star_swiglu_ffn_bwd(up: Algebra, down: Algebra, row_type: torch.Tensor, X: t
     dW_down, db_down = star_proj_bwd_weight_planned(down, plan, H, dY, ws=ws)
     dW_gate, db_gate = star_proj_bwd_weight_planned(up, plan, X, dZg, ws=ws)
     dW_up, db_up = star_proj_bwd_weight_planned(up, plan, X, dZu, ws=ws)
-    # the two input gradients in fp32, summed once
-    dX = star_proj_bwd_data_planned(up, plan, dZg, W_gate, out_dtype=torch.float32)
-    dX = star_add(dX, star_proj_bwd_data_planned(up, plan, dZu, W_up, out_dtype=torch.float32), out=dX)
+    # the two input gradients summed in fp32
+    if X.dtype == torch.bfloat16:
+        dX = star_proj_bwd_data_pair_planned(up, plan, dZg, W_gate, dZu, W_up, out_dtype=torch.float32)
+    else:
+        dX = star_proj_bwd_data_planned(up, plan, dZg, W_gate, out_dtype=torch.float32)
+        dX = star_add(dX, star_proj_bwd_data_planned(up, plan, dZu, W_up, out_dtype=torch.float32), out=dX)
     return dict(dX=dX, dZ_gate=dZg, dZ_up=dZu, dW_gate=dW_gate, db_gate=db_gate, dW_up=dW_up,
                 db_up=db_up, dW_down=dW_down, db_down=db_down)
 

@@ -910,6 +910,35 @@ star_status star_proj_bwd_data_planned(const star_algebra* alg, int64_t M, const
   return st;
 }
 
+star_status star_proj_bwd_data_pair_planned(const star_algebra* alg, int64_t M, const void* plan,
+                                            const void* dY1, const void* W1, const void* dY2,
+                                            const void* W2, star_dtype dt, void* dX, star_dtype dxt,
+                                            hipStream_t stream) {
+  Alg a;
+  star_status st = parse_alg(alg, a);
+  if (st != STAR_OK) return st;
+  if (M < 0 || M > kMaxDim) return STAR_ERR_SHAPE;
+  if (dt != STAR_BF16 || !valid_dtype(dxt)) return STAR_ERR_DTYPE;
+  if (M == 0) return STAR_OK;
+  if (!plan || !dY1 || !W1 || !dY2 || !W2 || !dX) return STAR_ERR_ARG;
+  for (const void* x : {plan, dY1, W1, dY2, W2, static_cast<const void*>(dX)})
+    if (!aligned16(x)) return STAR_ERR_ALIGN;
+  const PlanWs pw = plan_layout(M, a.q);
+  void* pl = const_cast<void*>(plan);
+  GemmParams p;
+  fill_common(p, a, M, 1, at<int32_t>(pl, pw.perm), at<int32_t>(pl, pw.offsets));
+  p.A = dY1;
+  p.B = W1;
+  p.A2 = dY2;
+  p.B2 = W2;
+  p.act = STAR_ACT_NONE;
+  p.Y = dX;
+  p.ydtype = dxt;
+  st = hip_status(launch_proj_gemm(kModeBwdData, p, stream));
+  if (st == STAR_OK && a.law == STAR_LAW_GRAPH) st = hip_status(launch_graph_fill(kModeBwdData, p, stream));
+  return st;
+}
+
 star_status star_proj_bwd_data(const star_algebra* alg, int64_t M, const int32_t* row_type,
                                const void* dY, star_dtype dyt, const void* W, star_dtype wt,
                                const void* Z_prev, star_act act_prev, void* dX, star_dtype dxt,

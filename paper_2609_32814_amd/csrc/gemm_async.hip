@@ -152,7 +152,9 @@ __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2_t){a, b}, bf16x2_t));
 }
 
-template <int MODE, int LAW, int ACT, int TM, int TN>
+// PAIR (activation gradient): a second product of the same shape in the same
+// tiles, the steps of the first and then those of the second.
+template <int MODE, int LAW, int ACT, int TM, int TN, bool PAIR>
 __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const GemmParams p) {
   static_assert(MODE == kModeBwdWeight ? TM != 128 : TM != 192, "192 rows: weight gradient only; 128: the others");
   using L = Lay<TM, TN>;
@@ -259,6 +261,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
     t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
                                      units_s[un][cls], offs_s, hh ? TM / 2 : TM);
+    if constexpr (PAIR) t.nsteps *= 2;
     return true;
   };
 
@@ -390,12 +393,14 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
       rows_from_lds = false;
       tile_ptrs();
     }
-    step_range<MODE, LAW, BK>(p, lt, offs_s, ls, sk0, skend);
+    const bool second = PAIR && ls >= (lt.nsteps >> 1);
+    step_range<MODE, LAW, BK>(p, lt, offs_s, second ? ls - (lt.nsteps >> 1) : ls, sk0, skend);
     klen = skend - sk0;
     if constexpr (kFast) {
-      astep = reinterpret_cast<const char*>(Ag + sk0);
-      bstep = MODE == kModeFwd ? reinterpret_cast<const char*>(Bg + static_cast<int64_t>(sk0) * p.N + lt.cstart)
-                               : reinterpret_cast<const char*>(Bg + sk0);
+      astep = reinterpret_cast<const char*>((second ? static_cast<const uint16_t*>(p.A2) : Ag) + sk0);
+      bstep = MODE == kModeFwd
+                  ? reinterpret_cast<const char*>(Bg + static_cast<int64_t>(sk0) * p.N + lt.cstart)
+                  : reinterpret_cast<const char*>((second ? static_cast<const uint16_t*>(p.B2) : Bg) + sk0);
       if (ls == 0) {
         if (wave < 4) {
           // row indices of the next tile
@@ -781,9 +786,12 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   wait_vm_all();
 }
 
-template <int MODE, int LAW, int ACT, int TM, int TN>
+template <int MODE, int LAW, int ACT, int TM, int TN, bool PAIR = false>
 hipError_t launch_one(const GemmParams& p, int64_t upper, int cus, hipStream_t stream) {
-  auto kern = star_gemm_async_kernel<MODE, LAW, ACT, TM, TN>;
+  if constexpr (MODE == kModeBwdData && ACT == kActNone && !PAIR) {
+    if (p.A2) return launch_one<MODE, LAW, ACT, TM, TN, true>(p, upper, cus, stream);
+  }
+  auto kern = star_gemm_async_kernel<MODE, LAW, ACT, TM, TN, PAIR>;
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t attr = ensure_lds_limit(reinterpret_cast<const void*>(kern), lds_set, SMEM);
   if (attr != hipSuccess) return attr;

@@ -33,6 +33,10 @@ struct GemmParams {
   int32_t MTp[kMaxQGroups + 1];  // BWD_WEIGHT: row tiles of C per input group, prefix
   const void* A;
   const void* B;
+  // BWD_DATA with bf16 operands, or null: a second product of the same shape
+  // that is added to the first (the contraction runs over both)
+  const void* A2;
+  const void* B2;
   // FWD epilogue
   const float* bias;
   int32_t act;

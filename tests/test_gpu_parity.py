@@ -459,6 +459,27 @@ def test_128_row_tiles(P, law, s, r, M):
         assert rel_fro(to_host(dX), ref) <= TOL_BF16
 
 
+@pytest.mark.parametrize("law", ["star", "dense", "tensor2", "graph"])
+@pytest.mark.parametrize("s,r,M", [([64, 72, 264, 40], [96, 64, 136, 200], 333),
+                                   ([192] * 4, [384] * 4, 6000)])
+def test_bwd_data_pair(P, law, s, r, M):
+    """Two activation gradients of one input in one product: the steps of the
+    second follow those of the first in every tile (small tiles of one or two
+    steps, and tiles of every pass), against the oracle's two."""
+    import torch
+    edges = [[int(i != j and (i + j) % 2) for j in range(4)] for i in range(4)] if law == "graph" else None
+    ga = P.Algebra(4, s, r, law, edges)
+    oa = oracle.Alg(4, tuple(s), tuple(r), law, edges)
+    t = np.random.default_rng(499).integers(0, 4, M).astype(np.int32)
+    plan = P.star_type_plan(4, types_dev(t))
+    d1, d2 = (synth.gaussian(498, k, (M, oa.N), 1.0, "bf16") for k in (0, 1))
+    W1, W2 = (synth.gaussian(498, k, (oa.K, oa.N), 0.05, "bf16") for k in (2, 3))
+    ref = oracle.proj_bwd_data(oa, t, d1.exact, W1.exact) + oracle.proj_bwd_data(oa, t, d2.exact, W2.exact)
+    for out in (torch.float32, torch.bfloat16):
+        dX = P.star_proj_bwd_data_pair_planned(ga, plan, to_dev(d1), to_dev(W1), to_dev(d2), to_dev(W2), out_dtype=out)
+        assert dX.dtype == out and rel_fro(to_host(dX), ref) <= TOL_BF16
+
+
 @pytest.mark.parametrize("r", [[384, 392], [1024, 1032]])
 def test_bwd_weight_out_of_range_types_left_out(P, r):
     """Rows whose type is outside [0, q) are left out of the weight and bias
