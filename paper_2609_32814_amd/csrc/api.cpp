@@ -1008,18 +1008,21 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
     if (p.nsplit > 1) p.partial = at<float>(ws, bw.partial_a);
     const int64_t upper = static_cast<int64_t>(p.MTp[a.q]) * p.NTp[a.q] * p.nsplit;
     st = hip_status(launch_gemm_async(kModeBwdWeight, p, upper, cu_count(), stream));
-    if (st == STAR_OK && p.nsplit > 1)
-      st = hip_status(p.nsplit == p.nsplit1
-                          ? launch_sum_partials(p.partial, p.nsplit, static_cast<int64_t>(p.K) * p.N, dW, stream)
-                          : launch_block_reduce(p, stream));
-    if (st != STAR_OK || !dbias) return st;
-    // dbias = column sums of dY over the rows of valid type, in fixed chunks
-    const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
-    float* cs = at<float>(ws, bw.colsum);
-    st = hip_status(launch_column_sum(static_cast<const uint16_t*>(dY), p.N, p.perm, p.offsets, a.q, p.M,
-                                      chunk, kColSumChunks, cs, stream));
     if (st != STAR_OK) return st;
-    return hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream));
+    // dbias = column sums of dY over the rows of valid type, in fixed chunks,
+    // added beside the partials of dW if there are any
+    float* cs = dbias ? at<float>(ws, bw.colsum) : nullptr;
+    if (dbias) {
+      const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
+      st = hip_status(launch_column_sum(static_cast<const uint16_t*>(dY), p.N, p.perm, p.offsets, a.q, p.M,
+                                        chunk, kColSumChunks, cs, stream));
+      if (st != STAR_OK) return st;
+    }
+    if (p.nsplit > 1) {
+      p.dbias = dbias;
+      return hip_status(launch_block_reduce(p, cs, kColSumChunks, stream));
+    }
+    return dbias ? hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream)) : STAR_OK;
   }
   p.A = X;
   p.B = dY;

@@ -139,12 +139,11 @@ hipError_t launch_swiglu_bwd(int64_t n, int elem, const void* dh, const void* zg
 hipError_t launch_add(int64_t n, int elem, const void* a, const void* b, void* out, hipStream_t stream);
 hipError_t launch_split_reduce(const GemmParams& p, hipStream_t stream);
 // dW = the sum of its blocks' partials, each block over its pass's splits
-// (p.nsplit > 1; blocks with one split are copied).
-hipError_t launch_block_reduce(const GemmParams& p, hipStream_t stream);
-// out[i] = sum over c < n_parts of part[c * n + i], in c order.
-hipError_t launch_sum_partials(const float* part, int n_parts, int64_t n, float* out,
-                               hipStream_t stream);
-// The same for few outputs (a bias gradient's n columns) over many parts:
+// (p.nsplit > 1; blocks with one split are copied).  chunks, or null: the
+// column sums [nchunks][N] of dY's row chunks, whose sum is p.dbias.
+hipError_t launch_block_reduce(const GemmParams& p, const float* chunks, int nchunks, hipStream_t stream);
+// out[j] = sum over c < nparts of part[c * n + j], for few outputs (a bias
+// gradient's n columns) over many parts:
 // the parts of one output are spread over eight threads, added in a fixed
 // order.
 hipError_t launch_sum_chunks(const float* part, int nparts, int32_t n, float* out, hipStream_t stream);
