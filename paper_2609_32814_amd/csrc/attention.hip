@@ -10,12 +10,13 @@
 // the position-type table (the same for every sequence).  A workgroup of 4
 // wavefronts owns one block of up to 128 query positions of one type i of
 // one (sequence, head), 32 per wave, and walks the keys type by type in
-// blocks of 32.  Positions increase within a type, so the first key block
-// that starts past the workgroup's last query ends that type's walk.  Per key
-// block of type j:
+// steps of 64, whose key and value rows reach LDS by direct copies one step
+// ahead.  Positions increase within a type, so the first key block that
+// starts past the workgroup's last query ends that type's walk.  Per 32-key
+// half of a step of type j:
 //   S^T = K Q^T over the groups of F(i, j) only, with
-//         v_mfma_f32_32x32x16_bf16: the key rows are the A operand (read from
-//         global memory, 16 bytes a lane), the wave's query rows the B
+//         v_mfma_f32_32x32x16_bf16: the key rows are the A operand (from
+//         LDS, 16 bytes a lane), the wave's query rows the B
 //         operand (held in registers for the whole walk), so a lane ends with
 //         16 key scores of one query.  Contraction steps whose 16 features
 //         hold no selected group are skipped; with m = 8 a lane zeroes its
@@ -24,9 +25,7 @@
 //         sum over the lane's 16 values and its partner lane l ^ 32, which
 //         holds the other 16 keys of the same query);
 //   O^T += V^T P^T: the probabilities stay in registers as the B operand;
-//         the value block reaches LDS by direct global-to-LDS copies (issued
-//         before the score step, so they overlap it) and is read back with
-//         transposing reads (ds_read_b64_tr_b16) in exactly the key order in
+//         the value rows are read back with transposing reads (ds_read_b64_tr_b16) in exactly the key order in
 //         which the lane holds its probabilities.
 //
 // Decode (Alg. attention-decoding, the score and aggregation steps) splits

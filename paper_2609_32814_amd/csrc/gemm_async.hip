@@ -3,7 +3,8 @@
 // gradient.
 //
 // Tiles of C are 256 rows (of one type class) x 256 columns (of one output
-// group), computed by one workgroup of 8 wavefronts (2 x 4, 128 x 64 each,
+// group), or fewer of either where the host's estimate favours them (Lay
+// below), computed by one workgroup of 8 wavefronts (2 x 4, 128 x 64 each,
 // swapped-operand v_mfma_f32_32x32x16_bf16 so a lane ends with 4 consecutive
 // output columns).  Two passes of tiles (two-segment contractions first),
 // dealt out per XCD as one list (the second pass in tiles of 128 rows when
