@@ -54,9 +54,6 @@ constexpr int kBlockRows = 128;   // query rows per workgroup
 
 __device__ __attribute__((aligned(256))) uint32_t g_attn_zero[64];
 
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_addr) : "memory", "m0");
-}
 __device__ __forceinline__ void wait_vm_all() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));  // vmcnt(0)

@@ -31,6 +31,37 @@ __device__ __forceinline__ uint16_t f32_to_bf16(float f) {
   return static_cast<uint16_t>(u >> 16);
 }
 
+// ---- copies from global memory into LDS -----------------------------------
+// 16 (dma16) or 4 (dma4) bytes per lane from global memory straight into LDS
+// at lds_addr + 16 * lane (4 * lane); lds_addr is uniform over the wave.
+// Issued as assembly so that the compiler's wait-count bookkeeping, which
+// would otherwise drain every copy in flight before any LDS read, stays out
+// of the kernels' pipelines: their waits are explicit.  The hardware wants
+// one wait state between a scalar write of M0 and the copy that takes its
+// LDS address from it; the compiler puts it in for its own copies but not
+// inside an assembly string, so the s_nop belongs to the string.
+
+__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+__device__ __forceinline__ void dma4(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dword %0, off"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+// agent-coherent (sc1): reads what other workgroups stored, past this XCD's
+// L2
+__device__ __forceinline__ void dma16_sys(const void* g, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off sc1"
+               :
+               : "v"(g), "s"(lds_addr)
+               : "memory", "m0");
+}
+
 // ---- activations -----------------------------------------------------------
 // One GELU for every kernel (GEMM epilogues and the decode kernels), with
 // explicit approximations whose error bounds are stated and tested.

@@ -93,15 +93,6 @@ __device__ __forceinline__ uint64_t ld_agent64(const uint64_t* p) {
 // 64 zero bytes: the source of an input piece that no support reaches
 __device__ __attribute__((aligned(64))) uint32_t g_decode_zero[16];
 
-// 16 bytes per lane from global memory into LDS at lds_addr + 16 * lane;
-// issued as assembly so that the compiler does not wait for every copy in
-// flight before an LDS read (the waits are explicit and counted).
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
 template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt is six bits");
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");

@@ -68,20 +68,6 @@ typedef short v4i16_t __attribute__((ext_vector_type(4)));
 
 __device__ __attribute__((aligned(256))) uint32_t g_stack_zero[64];
 
-__device__ __forceinline__ void dma16_sys(const void* g, uint32_t lds_addr) {
-  // agent-coherent (sc1): reads what other workgroups stored, past this
-  // XCD's L2
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off sc1"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
 __device__ __forceinline__ void wait_vm_all() {
   asm volatile("" ::: "memory");
   __builtin_amdgcn_s_waitcnt((7 << 4) | (15 << 8));

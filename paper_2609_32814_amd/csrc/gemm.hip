@@ -85,26 +85,9 @@ constexpr int CA = TM / 32, CB = TN / 32;           // copies per wave and step
 constexpr int kChunks = 16;                         // 16-byte chunks per K index of a row-contiguous operand
 static_assert(TM == 4 * kChunks && TN == 4 * kChunks && CA == CB, "one copy layout for both operands");
 
-#define STARQ_LDS __attribute__((address_space(3)))
-
 // 256 zero bytes: the source of every copy past a step's K range
 __device__ __attribute__((aligned(256))) uint32_t g_f32_zero[64];
 
-// 16 (dma16) or 4 (dma4) bytes per lane from global memory into LDS at
-// lds_addr + 16 * lane (4 * lane); issued as assembly so that the compiler
-// does not wait for the copies in flight before every LDS read.
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
 template <int N> __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt is six bits");
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");

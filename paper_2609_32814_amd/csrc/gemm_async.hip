@@ -79,24 +79,6 @@ typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
 // operand.
 __device__ __attribute__((aligned(256))) uint32_t g_zero_page[64];
 
-// 16 (dma16) or 4 (dma4) bytes per lane from global memory into LDS at
-// lds_addr + 16 * lane (4 * lane).  Issued as assembly so that the
-// compiler's wait-count bookkeeping, which would otherwise drain every copy
-// in flight before any LDS read, stays out of the pipeline; the waits below
-// are explicit.
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off"
-               :
-               : "v"(g), "s"(lds_addr)
-               : "memory", "m0");
-}
-
 // wait until every vector-memory operation of this wave has completed
 __device__ __forceinline__ void wait_vm_all() {
   asm volatile("" ::: "memory");

@@ -60,12 +60,6 @@ constexpr int kSinkSets = 16;
 constexpr int kSinkLane = 256;
 __device__ __attribute__((aligned(256))) char g_narrow_sink[kSinkSets * 64 * kSinkLane];
 
-__device__ __forceinline__ void dma16(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dwordx4 %0, off" : : "v"(g), "s"(lds_addr) : "memory", "m0");
-}
-__device__ __forceinline__ void dma4(const void* g, uint32_t lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\tglobal_load_lds_dword %0, off" : : "v"(g), "s"(lds_addr) : "memory", "m0");
-}
 template <int N>
 __device__ __forceinline__ void wait_vm() {
   static_assert(N >= 0 && N < 64, "vmcnt");
