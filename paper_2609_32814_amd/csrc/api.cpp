@@ -11,7 +11,6 @@
 #include <cstdlib>
 #include <cstring>
 #include <initializer_list>
-#include <vector>
 
 #include "../../include/star_proj.h"
 #include "kernels.hpp"
@@ -164,57 +163,128 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
 // law's 192- and 384-wide groups take them for the same reason (16384 rows,
 // 768 <-> 1536, q = 4: activation gradients 59 and 67 -> 52 and 58 us,
 // weight gradient 98 -> 87 us).
-double deal_makespan(const std::vector<int32_t>* passes, double epi, int xcds = 8) {
-  constexpr int kGrid = 256, kSlots = kGrid / 8;
-  double worst = 0.0;
-  for (int x = 0; x < xcds; ++x) {
-    double load[kSlots] = {};
-    int64_t v = 0;
-    for (int ps = 0; ps < 2; ++ps) {
-      const int64_t n = static_cast<int64_t>(passes[ps].size()), chunk = (n + 7) / 8;
-      for (int64_t t = x * chunk; t < std::min(n, (x + 1) * chunk); ++t, ++v) {
-        const int64_t r = v / kSlots, pos = v % kSlots;
-        load[(r & 1) ? kSlots - 1 - pos : pos] += passes[ps][t] + epi;
-      }
-    }
-    for (double l : load) worst = std::max(worst, l);
+//
+// The estimate runs at every launch, so it takes runs of equal tiles and not
+// single ones, and allocates nothing (an entry point that runs out of memory
+// can only abort).  Host time of a launch against a tile at a time in
+// vectors: star, q = 64, 16384 x 4096 -> 16384, forward 76 to 125 -> 2 us,
+// activation gradient 150 -> 3 us, weight gradient 80 -> 7 us; dense, q = 1,
+// 131072 rows, forward 240 -> 1 us; q = 64 groups all of different widths
+// stay at 100 to 150 us.
+struct Deal {
+  static constexpr unsigned kXcds = 8, kSlots = 256 / kXcds;
+  int64_t total[2], chunk[2];  // tiles of each pass, of an XCD's share of it
+  double epi;
+  unsigned xcds;  // XCDs looked at
+  struct {
+    int64_t left;  // tiles left in the XCD's share
+    uint64_t v;    // place of the next one among the XCD's tiles of both passes
+    unsigned xcd;
+  } at[2];
+  double load[kXcds][kSlots];
+
+  Deal(int64_t total0, int64_t total1, double epi_, unsigned xcds_ = kXcds)
+      : total{total0, total1}, chunk{(total0 + 7) / 8, (total1 + 7) / 8}, epi(epi_), xcds(xcds_) {
+    for (unsigned x = 0; x < xcds; ++x)
+      for (double& l : load[x]) l = 0.0;
+    for (int ps = 0; ps < 2; ++ps) start(ps, 0);
   }
-  return worst;
-}
-int steps_of(int64_t w) { return static_cast<int>((w + 63) / 64); }
-// mode: the kernel's (forward, activation gradient)
-double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act) {
-  std::vector<int32_t> passes[2];
-  const int q = a.q;
-  const int64_t per = (M + q - 1) / q;  // rows of a type
-  const int rt = tiles_of(per, tm);
-  const bool fwd = mode == kModeFwd;
-  for (int i = 0; i < q; ++i)
-    for (int u = 0; u < rt; ++u)
-      for (int j = 0; j < q; ++j) {
-        const int ct = tiles_of(fwd ? a.r(j) : a.s(j), tn);
-        int st;
-        if (a.law == STAR_LAW_TENSOR2) {
-          int n = 0;
-          st = 0;
-          for (int x = 0; x < q; ++x)
-            if (fwd ? host_in_support(a, i, j, x) : host_in_support(a, i, x, j)) {
-              st += steps_of(fwd ? a.s(x) : a.r(x));
-              ++n;
-            }
-          passes[2 * n > q ? 0 : 1].insert(passes[2 * n > q ? 0 : 1].end(), ct, st);
-          continue;
-        }
-        if (a.law == STAR_LAW_DENSE) st = steps_of(fwd ? a.K() : a.N());
-        else if (fwd) st = steps_of(a.s(j)) + (j != i ? steps_of(a.s(i)) : 0);
-        else st = j == i ? steps_of(a.N()) : steps_of(a.r(j));
-        // pass 0: forward, the two-segment tiles; activation gradient, the
-        // tiles over every output group
-        const int ps = a.law == STAR_LAW_DENSE ? 0 : (fwd ? (j != i ? 0 : 1) : (j == i ? 0 : 1));
-        passes[ps].insert(passes[ps].end(), ct, st);
+  int64_t share(int ps, unsigned x) const {
+    return std::max<int64_t>(0, std::min(chunk[ps], total[ps] - static_cast<int64_t>(x) * chunk[ps]));
+  }
+  void start(int ps, unsigned x) { at[ps] = {share(ps, x), static_cast<uint64_t>(ps == 0 ? 0 : share(0, x)), x}; }
+  // the next n tiles of pass ps, in the kernel's order, have `steps` steps each
+  void add(int ps, int64_t n, int steps) {
+    const double w = steps + epi;
+    while (n > 0 && at[ps].xcd < xcds) {
+      auto& c = at[ps];
+      double* l = load[c.xcd];
+      int64_t k = std::min(n, c.left);
+      n -= k;
+      c.left -= k;
+      auto one = [&]() {
+        const unsigned pos = c.v % kSlots;
+        l[(c.v / kSlots) & 1 ? kSlots - 1 - pos : pos] += w;
+        ++c.v, --k;
+      };
+      while (k > 0 && c.v % kSlots != 0) one();
+      if (const uint64_t rounds = static_cast<uint64_t>(k) / kSlots) {
+        for (unsigned i = 0; i < kSlots; ++i) l[i] += w * static_cast<double>(rounds);
+        c.v += rounds * kSlots;
+        k -= static_cast<int64_t>(rounds * kSlots);
       }
+      while (k > 0) one();
+      if (c.left == 0) start(ps, c.xcd + 1);
+    }
+  }
+  double makespan() const {
+    double worst = 0.0;
+    for (unsigned x = 0; x < xcds; ++x)
+      for (double l : load[x]) worst = std::max(worst, l);
+    return worst;
+  }
+};
+int steps_of(int64_t w) { return static_cast<int>((w + 63) / 64); }
+bool equal_widths(const Alg& a, bool over_r) {
+  for (int g = 1; g < a.q; ++g)
+    if ((over_r ? a.r(g) : a.s(g)) != (over_r ? a.r(0) : a.s(0))) return false;
+  return true;
+}
+// mode: the kernel's (forward, activation gradient); not for the graph law
+double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act) {
+  const int q = a.q;
+  const bool fwd = mode == kModeFwd;
+  const int64_t rt = tiles_of((M + q - 1) / q, tm);  // row tiles of a type
+  int64_t ct[kMaxQGroups], cols = 0;                 // column tiles of a group, of all
+  for (int j = 0; j < q; ++j) cols += ct[j] = tiles_of(fwd ? a.r(j) : a.s(j), tn);
   const double epi = (act ? (fwd ? 3.0 : 2.0) : 1.0) * tn * tm / (256 * 256);
-  return deal_makespan(passes, epi);
+  // pass 0: the two-segment tiles (forward), the tiles over every output
+  // group (activation gradient)
+  if (a.law == STAR_LAW_DENSE) {
+    Deal d(q * rt * cols, 0, epi);
+    d.add(0, d.total[0], steps_of(fwd ? a.K() : a.N()));
+    return d.makespan();
+  }
+  if (a.law == STAR_LAW_TENSOR2) {
+    int st[4][4], ps[4][4];  // q is 1, 2 or 4
+    int64_t total[2] = {0, 0};
+    for (int i = 0; i < q; ++i)
+      for (int j = 0; j < q; ++j) {
+        int n = 0;
+        st[i][j] = 0;
+        for (int x = 0; x < q; ++x)
+          if (fwd ? host_in_support(a, i, j, x) : host_in_support(a, i, x, j)) {
+            st[i][j] += steps_of(fwd ? a.s(x) : a.r(x));
+            ++n;
+          }
+        ps[i][j] = 2 * n > q ? 0 : 1;
+        total[ps[i][j]] += rt * ct[j];
+      }
+    Deal d(total[0], total[1], epi);
+    for (int i = 0; i < q; ++i)
+      for (int64_t u = 0; u < rt; ++u)
+        for (int j = 0; j < q; ++j) d.add(ps[i][j], ct[j], st[i][j]);
+    return d.makespan();
+  }
+  const int own = fwd ? 1 : 0;  // the pass of a type's own group
+  const int64_t mine = rt * cols, others = rt * (q - 1) * cols;
+  Deal d(fwd ? others : mine, fwd ? mine : others, epi);
+  if (equal_widths(a, !fwd)) {  // the contracted groups are all alike
+    const int one = steps_of(fwd ? a.s(0) : a.r(0));
+    d.add(0, d.total[0], fwd ? 2 * one : steps_of(a.N()));
+    d.add(1, d.total[1], one);
+    return d.makespan();
+  }
+  int steps[kMaxQGroups];
+  for (int j = 0; j < q; ++j) steps[j] = steps_of(fwd ? a.s(j) : a.r(j));
+  const int full = steps_of(a.N());
+  for (int i = 0; i < q; ++i)
+    for (int64_t u = 0; u < rt; ++u)
+      for (int j = 0; j < q; ++j) {
+        const int st = fwd ? steps[j] + (j != i ? steps[i] : 0) : (j == i ? full : steps[j]);
+        d.add(j == i ? own : 1 - own, ct[j], st);
+      }
+  return d.makespan();
 }
 // The tiles are 192 wide only where that pads fewer C columns as well: without
 // padding to remove, the 192-wide tiles' extra re-reads of the row tiles
@@ -225,9 +295,7 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
 // (8192 x 768 -> 3072 with GELU, q = 2: cyclic types 50.7 against 55.0 us,
 // 192-row runs 62.8 and 63.8; at 4096 rows 31.8 against 35.6, and 38 with
 // unequal counts that add a row tile).
-int padded_cols(const Alg& a, bool over_r, int tn) {
-  return static_cast<int>(col_tiles(a, over_r, tn) * tn);
-}
+int64_t padded_cols(const Alg& a, bool over_r, int tn) { return col_tiles(a, over_r, tn) * tn; }
 // 128-row tiles take about 0.7 of a 256-row tile's step (128 x 256: 0.75 of a
 // 256 x 256 one, 128 x 192: 0.65), so they pay where 256-row tiles leave CUs
 // without a tile or a long tile beside a short one: 8192 rows, q = 2, 3072 ->
@@ -239,10 +307,10 @@ struct TileShape {
   int tm, tn;
 };
 TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
+  if (a.law == STAR_LAW_GRAPH) return {256, 256};
   const bool over_r = mode != kModeBwdData;
-  const int pad192 = padded_cols(a, over_r, 192), pad256 = padded_cols(a, over_r, 256);
-  const bool try192 = a.law != STAR_LAW_GRAPH &&
-                      (pad192 < pad256 || (pad192 == pad256 && a.law == STAR_LAW_STAR && mode == kModeFwd));
+  const int64_t pad192 = padded_cols(a, over_r, 192), pad256 = padded_cols(a, over_r, 256);
+  const bool try192 = pad192 < pad256 || (pad192 == pad256 && a.law == STAR_LAW_STAR && mode == kModeFwd);
   TileShape best{256, 256};
   double cost = async_makespan(a, mode, M, 256, 256, act);
   auto consider = [&](int tm, int tn, double rate, double margin) {
@@ -253,10 +321,8 @@ TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
     }
   };
   if (try192) consider(256, 192, 0.9, 1.0);
-  if (a.law != STAR_LAW_GRAPH) {
-    consider(128, 256, 0.75, 0.95);
-    if (try192) consider(128, 192, 0.65, best.tm == 128 ? 1.0 : 0.95);
-  }
+  consider(128, 256, 0.75, 0.95);
+  if (try192) consider(128, 192, 0.65, best.tm == 128 ? 1.0 : 0.95);
   return best;
 }
 
@@ -292,34 +358,31 @@ bool weight_first_pass(const Alg& a, int i, int j, int types) {
 // and took as long as the dense product with twice the work.  What a split
 // costs, in steps of about 1.8 us: kItem for its tile of partials (written
 // by all CUs at once), and the bytes the second kernel reads at 4.5 TB/s.
-WeightPlan weight_plan_shape(const Alg& a, int64_t M, int tm, int tn, int most, double* cost) {
-  int64_t count[2][kMaxQGroups + 1] = {};  // tiles per pass and number of types
-  double cells[2] = {};                    // dW cells per pass
-  int c1 = 1;
-  for (int i = 0; i < a.q; ++i)
-    for (int j = 0; j < a.q; ++j) {
-      const int n = weight_types(a, i, j), ps = weight_first_pass(a, i, j, n) ? 0 : 1;
-      count[ps][n] += static_cast<int64_t>(tiles_of(a.s(i), tm)) * tiles_of(a.r(j), tn);
-      cells[ps] += static_cast<double>(a.s(i)) * a.r(j);
-      if (ps == 1) c1 = std::max(c1, n);
-    }
+// The tiles of dW of one shape, per pass and number of row types.
+struct WeightTiles {
+  int tm, tn;
+  int64_t count[2][kMaxQGroups + 1];
+};
+WeightPlan weight_plan_shape(const Alg& a, int64_t M, const WeightTiles& t, const double (&cells)[2], int c1, int most,
+                             double* cost) {
   constexpr double kItem = 4.0, kStepUs = 1.8, kReadBytesUs = 4.5e6;
-  const double rate = tm == 256 && tn == 256 ? 1.0 : 0.9;  // of a smaller tile's step
-  WeightPlan best{tm, tn, 1, 1};
+  const double rate = t.tm == 256 && t.tn == 256 ? 1.0 : 0.9;  // of a smaller tile's step
+  int64_t tiles[2] = {0, 0};
+  for (int ps = 0; ps < 2; ++ps)
+    for (int n = 0; n <= a.q; ++n) tiles[ps] += t.count[ps][n];
+  WeightPlan best{t.tm, t.tn, 1, 1};
   *cost = 0.0;
   for (int ns = 1; ns <= most; ++ns) {
     const int ns1 = a.law == STAR_LAW_DENSE ? ns : std::max(1, (ns * c1 + a.q - 1) / a.q);
-    std::vector<int32_t> passes[2];
+    // (the first XCD's share of a pass is its longest items)
+    Deal d(tiles[0] * ns, tiles[1] * ns1, ns > 1 ? kItem : 1.0, 1);
     for (int ps = 0; ps < 2; ++ps) {
       const int s = ps == 0 ? ns : ns1;
-      for (int n = a.q; n >= 0; --n) {
-        const int64_t rows = (M * n / a.q + s - 1) / s;
-        passes[ps].insert(passes[ps].end(), static_cast<size_t>(count[ps][n] * s), steps_of(rows));
-      }
+      for (int n = a.q; n >= 0; --n)
+        if (t.count[ps][n]) d.add(ps, t.count[ps][n] * s, steps_of((M * n / a.q + s - 1) / s));
     }
     const double read = ns > 1 ? (cells[0] * ns + cells[1] * ns1) * 4.0 / kReadBytesUs / kStepUs : 0.0;
-    // (the first XCD's share of a pass is its longest items)
-    const double c = rate * deal_makespan(passes, ns > 1 ? kItem : 1.0, 1) + read;
+    const double c = rate * d.makespan() + read;
     if (ns == 1 || c < *cost) {
       *cost = c;
       best.nsplit = ns;
@@ -331,19 +394,44 @@ WeightPlan weight_plan_shape(const Alg& a, int64_t M, int tm, int tn, int most, 
 // most: splits at most (rows per split >= 1024 in any case)
 WeightPlan weight_plan(const Alg& a, int64_t M, int most = 16) {
   most = static_cast<int>(std::max<int64_t>(1, std::min<int64_t>(most, M / 1024)));
-  auto padded = [&](int tm, int tn) {
-    int64_t rows = 0;
-    for (int g = 0; g < a.q; ++g) rows += static_cast<int64_t>(tiles_of(a.s(g), tm)) * tm;
-    return rows * padded_cols(a, true, tn);
-  };
-  double cost = 0.0;
-  WeightPlan best = weight_plan_shape(a, M, 256, 256, most, &cost);
-  if (a.law == STAR_LAW_GRAPH) return best;
+  auto padded = [&](int tm, int tn) { return padded_cols(a, false, tm) * padded_cols(a, true, tn); };
+  // the shapes: 256 x 256, and those that pad fewer cells of dW
+  WeightTiles t[3] = {{256, 256, {}}, {256, 192, {}}, {192, 256, {}}};
+  int shapes = 1;
   const int64_t pad = padded(256, 256);
-  for (const auto& s : {std::pair<int, int>{256, 192}, std::pair<int, int>{192, 256}}) {
-    if (padded(s.first, s.second) >= pad) continue;
+  for (int k = 1; k < 3 && a.law != STAR_LAW_GRAPH; ++k)
+    if (padded(t[k].tm, t[k].tn) < pad) t[shapes++] = t[k];
+  double cells[2] = {};  // dW cells per pass
+  int c1 = 1;            // row types of a block of pass 1, at most
+  auto block = [&](int i, int j) {
+    const int n = weight_types(a, i, j), ps = weight_first_pass(a, i, j, n) ? 0 : 1;
+    for (int k = 0; k < shapes; ++k)
+      t[k].count[ps][n] += static_cast<int64_t>(tiles_of(a.s(i), t[k].tm)) * tiles_of(a.r(j), t[k].tn);
+    cells[ps] += static_cast<double>(a.s(i)) * a.r(j);
+    if (ps == 1) c1 = std::max(c1, n);
+  };
+  if (a.law == STAR_LAW_STAR || a.law == STAR_LAW_DENSE) {
+    // the diagonal blocks, and the others (one row type each; under the dense
+    // law every block is alike) as what they leave of all
+    for (int g = 0; g < a.q; ++g) block(g, g);
+    const int ps = a.law == STAR_LAW_DENSE ? 0 : 1, n = a.law == STAR_LAW_DENSE ? a.q : 1;
+    for (int k = 0; k < shapes; ++k) {
+      const int64_t all = col_tiles(a, false, t[k].tm) * col_tiles(a, true, t[k].tn);
+      if (ps == 0) t[k].count[0][n] = all;
+      else t[k].count[1][n] += all - t[k].count[0][a.q];
+    }
+    const double all = static_cast<double>(a.K()) * a.N();
+    if (ps == 0) cells[0] = all;
+    else cells[1] += all - cells[0];
+  } else {
+    for (int i = 0; i < a.q; ++i)
+      for (int j = 0; j < a.q; ++j) block(i, j);
+  }
+  double cost = 0.0;
+  WeightPlan best = weight_plan_shape(a, M, t[0], cells, c1, most, &cost);
+  for (int k = 1; k < shapes; ++k) {
     double c = 0.0;
-    const WeightPlan w = weight_plan_shape(a, M, s.first, s.second, most, &c);
+    const WeightPlan w = weight_plan_shape(a, M, t[k], cells, c1, most, &c);
     if (c < cost) {
       cost = c;
       best = w;
@@ -398,8 +486,9 @@ BwdWs bwd_weight_layout(const Alg& a, int64_t M, const WeightPlan& wp) {
 }
 
 // The layout with the splits that run best, or with as many as fit in
-// `room` bytes.
-BwdWs bwd_weight_fit(const Alg& a, int64_t M, size_t room) {
+// `room` bytes (fp32 operands: they have their own, fixed ones).
+BwdWs bwd_weight_fit(const Alg& a, int64_t M, star_dtype dt, size_t room) {
+  if (dt == STAR_F32) return bwd_weight_layout(a, M, WeightPlan{});
   BwdWs w = bwd_weight_layout(a, M, weight_plan(a, M));
   for (int most = w.wp.nsplit - 1; w.end > room && most >= 1; --most)
     w = bwd_weight_layout(a, M, weight_plan(a, M, most));
@@ -558,7 +647,8 @@ Alg alg_of(const GemmParams& p) {
 }
 
 // column-tile prefix over groups of widths given by starts G
-void fill_tiles(int32_t* pfx, const int64_t* G, int q, int tile) {
+template <typename T>
+void fill_tiles(int32_t* pfx, const T* G, int q, int tile) {
   pfx[0] = 0;
   for (int g = 0; g < q; ++g) pfx[g + 1] = pfx[g] + tiles_of(G[g + 1] - G[g], tile);
 }
@@ -586,13 +676,21 @@ star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_E
 // 1536 -> 768: 77.5 against 54.5 us).
 std::atomic<int> g_fwd_tiles{STAR_TILES_AUTO};
 
-bool use_narrow_fwd(const GemmParams& p) {
-  if (p.elem != 1) return false;
+constexpr TileShape kSmallTiles{64, 128};
+
+// The tile shape of a bf16 forward product or activation gradient.
+TileShape proj_tiles(int mode, const GemmParams& p) {
+  const bool act = p.act != STAR_ACT_NONE;
+  if (mode != kModeFwd) return async_tiles(alg_of(p), mode, p.M, act);
   for (int g = 0; g < p.q; ++g)
-    if (p.S[g + 1] - p.S[g] < 64) return true;
-  const int forced = g_fwd_tiles.load(std::memory_order_relaxed);
-  if (forced != STAR_TILES_AUTO) return forced == STAR_TILES_SMALL;
-  if (static_cast<int64_t>(p.M) < p.q) return true;
+    if (p.S[g + 1] - p.S[g] < 64) return kSmallTiles;
+  switch (g_fwd_tiles.load(std::memory_order_relaxed)) {
+    case STAR_TILES_SMALL: return kSmallTiles;
+    case STAR_TILES_WIDE: return {kTileM, 256};
+    case STAR_TILES_WIDE192: return {kTileM, p.law == STAR_LAW_GRAPH ? 256 : 192};
+    default: break;
+  }
+  if (static_cast<int64_t>(p.M) < p.q) return kSmallTiles;
   const double m = static_cast<double>(p.M) / p.q;  // rows per type
   const double row_tiles = std::ceil(m / 256.0);
   // A tile's mean contraction: K for the dense law, about two groups' worth
@@ -615,11 +713,10 @@ bool use_narrow_fwd(const GemmParams& p) {
     return (fill <= 0.75 && kc < 1024.0 && !many) ||
            (p.q * row_tiles * col_tiles < 128.0 && (p.law == STAR_LAW_GRAPH || p.q * half_tiles * col_tiles < 192.0));
   };
-  // (the estimate behind async_tiles costs host time: asked only where the
-  // two widths disagree)
   const bool n256 = narrow(256), n192 = narrow(192);
-  if (n256 == n192) return n256;
-  return async_tiles(alg_of(p), kModeFwd, p.M, p.act != STAR_ACT_NONE).tn == 192 ? n192 : n256;
+  if (n256 && n192) return kSmallTiles;
+  const TileShape ts = async_tiles(alg_of(p), mode, p.M, act);
+  return (ts.tn == 192 ? n192 : n256) ? kSmallTiles : ts;
 }
 
 // The small-tile forward: column tiles per output group, then the launch.
@@ -631,7 +728,9 @@ hipError_t launch_narrow(NarrowParams& pn, hipStream_t stream) {
 }
 
 hipError_t launch_proj_gemm(int mode, const GemmParams& p, hipStream_t stream) {
-  if (mode == kModeFwd && use_narrow_fwd(p)) {
+  if (p.elem != 1) return launch_gemm(mode, p, stream);
+  const TileShape ts = proj_tiles(mode, p);
+  if (ts.tm == kSmallTiles.tm) {
     NarrowParams pn;
     std::memset(&pn, 0, sizeof(pn));
     pn.q = p.q;
@@ -655,24 +754,12 @@ hipError_t launch_proj_gemm(int mode, const GemmParams& p, hipStream_t stream) {
     for (int g = 0; g < kMaxQGroups; ++g) pn.adj[g] = p.adj[g];
     return launch_narrow(pn, stream);
   }
-  if (p.elem == 1) {
-    GemmParams pa = p;
-    const int32_t* G = (mode == kModeFwd) ? p.R : p.S;  // output column groups
-    TileShape ts = async_tiles(alg_of(p), mode, p.M, p.act != STAR_ACT_NONE);
-    if (mode == kModeFwd) {
-      const int forced = g_fwd_tiles.load(std::memory_order_relaxed);
-      if (forced == STAR_TILES_WIDE) ts = {kTileM, 256};
-      if (forced == STAR_TILES_WIDE192) ts = {kTileM, p.law == STAR_LAW_GRAPH ? 256 : 192};
-    }
-    pa.tile_m = ts.tm;
-    pa.tile_n = ts.tn;
-    const int tn = ts.tn;
-    pa.NTp[0] = 0;
-    for (int g = 0; g < p.q; ++g) pa.NTp[g + 1] = pa.NTp[g] + (G[g + 1] - G[g] + tn - 1) / tn;
-    const int64_t rows_upper = static_cast<int64_t>(p.M) / pa.tile_m + p.q;
-    return launch_gemm_async(mode, pa, rows_upper * pa.NTp[p.q], cu_count(), stream);
-  }
-  return launch_gemm(mode, p, stream);
+  GemmParams pa = p;
+  pa.tile_m = ts.tm;
+  pa.tile_n = ts.tn;
+  fill_tiles(pa.NTp, mode == kModeFwd ? p.R : p.S, p.q, ts.tn);  // C column groups
+  const int64_t rows_upper = static_cast<int64_t>(p.M) / ts.tm + p.q;
+  return launch_gemm_async(mode, pa, rows_upper * pa.NTp[p.q], cu_count(), stream);
 }
 
 star_status run_plan(const int32_t* row_type, int64_t M, int q, void* ws, const PlanWs& pw,
@@ -732,6 +819,80 @@ star_status check_common(const star_algebra* alg, int64_t M, const int32_t* row_
   return STAR_OK;
 }
 
+// The weight gradient of checked arguments; bw: the layout for this
+// workspace.
+star_status run_bwd_weight(const Alg& a, int64_t M, const BwdWs& bw, const void* plan, const void* X, star_dtype xt,
+                           const void* dY, float* dW, float* dbias, void* ws, size_t ws_bytes, hipStream_t stream) {
+  const bool pipelined = xt == STAR_BF16;
+  const bool need_ws = pipelined || bw.nsplit > 1 || (a.law == STAR_LAW_GRAPH && dbias);
+  if (need_ws && M > 0 && (!ws || ws_bytes < bw.end)) return STAR_ERR_WORKSPACE;
+  if (ws && !aligned16(ws)) return STAR_ERR_ALIGN;
+  // M = 0 still defines the output: an empty sum
+  if (M == 0) {
+    hipError_t e = launch_fill_zero(dW, a.K() * a.N(), stream);
+    if (e == hipSuccess && dbias) e = launch_fill_zero(dbias, a.N(), stream);
+    return hip_status(e);
+  }
+  const PlanWs pw = plan_layout(M, a.q);
+  void* pl = const_cast<void*>(plan);
+  star_status st = STAR_OK;
+  GemmParams p;
+  fill_common(p, a, M, xt == STAR_BF16 ? 1 : 0, at<int32_t>(pl, pw.perm),
+              at<int32_t>(pl, pw.offsets));
+  if (pipelined) {
+    // every tile contracts over a range of type-sorted positions; the
+    // kernel reads the rows of X and dY at those positions through perm
+    p.tile_m = bw.wp.tm;
+    p.tile_n = bw.wp.tn;
+    fill_tiles(p.NTp, a.R, a.q, p.tile_n);
+    fill_tiles(p.MTp, a.S, a.q, p.tile_m);
+    p.A = X;
+    p.B = dY;
+    p.dW = dW;
+    p.nsplit = bw.wp.nsplit;
+    p.nsplit1 = bw.wp.nsplit1;
+    p.rmax = static_cast<int32_t>(widest_output(a));
+    if (p.nsplit > 1) p.partial = at<float>(ws, bw.partial_a);
+    const int64_t upper = static_cast<int64_t>(p.MTp[a.q]) * p.NTp[a.q] * p.nsplit;
+    st = hip_status(launch_gemm_async(kModeBwdWeight, p, upper, cu_count(), stream));
+    if (st != STAR_OK) return st;
+    // dbias = column sums of dY over the rows of valid type, in fixed chunks,
+    // added beside the partials of dW if there are any
+    float* cs = dbias ? at<float>(ws, bw.colsum) : nullptr;
+    if (dbias) {
+      const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
+      st = hip_status(launch_column_sum(static_cast<const uint16_t*>(dY), p.N, p.perm, p.offsets, a.q, p.M,
+                                        chunk, kColSumChunks, cs, stream));
+      if (st != STAR_OK) return st;
+    }
+    if (p.nsplit > 1) {
+      p.dbias = dbias;
+      return hip_status(launch_block_reduce(p, cs, kColSumChunks, stream));
+    }
+    return dbias ? hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream)) : STAR_OK;
+  }
+  p.A = X;
+  p.B = dY;
+  p.dW = dW;
+  // the graph law's diagonal tiles do not contract over every row, so its
+  // bias gradient is summed apart (below)
+  p.dbias = a.law == STAR_LAW_GRAPH ? nullptr : dbias;
+  p.nsplit = p.nsplit1 = bw.nsplit;
+  if (bw.nsplit > 1) {
+    p.partial = at<float>(ws, bw.partial);
+    p.dbias_part = at<float>(ws, bw.dbias_part);
+  }
+  st = hip_status(launch_gemm(kModeBwdWeight, p, stream));
+  if (st == STAR_OK && bw.nsplit > 1) st = hip_status(launch_split_reduce(p, stream));
+  if (st != STAR_OK || a.law != STAR_LAW_GRAPH || !dbias) return st;
+  const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
+  float* cs = at<float>(ws, bw.colsum);
+  st = hip_status(launch_column_sum_f32(static_cast<const float*>(dY), p.N, p.perm, p.offsets, a.q, p.M, chunk,
+                                        kColSumChunks, cs, stream));
+  if (st != STAR_OK) return st;
+  return hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream));
+}
+
 }  // namespace
 
 extern "C" {
@@ -760,7 +921,7 @@ size_t star_workspace_bytes(int32_t op, const star_algebra* alg, const star_alge
     case STAR_OP_FFN_FWD:
       return plan_layout(M, a.q).end;
     case STAR_OP_BWD_WEIGHT:
-      return bwd_weight_fit(a, M, SIZE_MAX).end;
+      return bwd_weight_fit(a, M, STAR_BF16, SIZE_MAX).end;
     case STAR_OP_DECODE: {
       Alg d;
       if (parse_alg(alg2, d) != STAR_OK) return 0;
@@ -976,74 +1137,7 @@ star_status star_proj_bwd_weight_planned(const star_algebra* alg, int64_t M, con
   if ((X && !aligned16(X)) || (dY && !aligned16(dY)) || !aligned16(dW) ||
       (dbias && !aligned4(dbias)) || (plan && !aligned16(plan)))
     return STAR_ERR_ALIGN;
-  const BwdWs bw = bwd_weight_fit(a, M, ws_bytes);
-  const bool pipelined = xt == STAR_BF16;
-  const bool need_ws = pipelined || bw.nsplit > 1 || (a.law == STAR_LAW_GRAPH && dbias);
-  if (need_ws && M > 0 && (!ws || ws_bytes < bw.end)) return STAR_ERR_WORKSPACE;
-  if (ws && !aligned16(ws)) return STAR_ERR_ALIGN;
-  // M = 0 still defines the output: an empty sum
-  if (M == 0) {
-    hipError_t e = launch_fill_zero(dW, a.K() * a.N(), stream);
-    if (e == hipSuccess && dbias) e = launch_fill_zero(dbias, a.N(), stream);
-    return hip_status(e);
-  }
-  const PlanWs pw = plan_layout(M, a.q);
-  void* pl = const_cast<void*>(plan);
-  GemmParams p;
-  fill_common(p, a, M, xt == STAR_BF16 ? 1 : 0, at<int32_t>(pl, pw.perm),
-              at<int32_t>(pl, pw.offsets));
-  if (pipelined) {
-    // every tile contracts over a range of type-sorted positions; the
-    // kernel reads the rows of X and dY at those positions through perm
-    p.tile_m = bw.wp.tm;
-    p.tile_n = bw.wp.tn;
-    fill_tiles(p.NTp, a.R, a.q, p.tile_n);
-    fill_tiles(p.MTp, a.S, a.q, p.tile_m);
-    p.A = X;
-    p.B = dY;
-    p.dW = dW;
-    p.nsplit = bw.wp.nsplit;
-    p.nsplit1 = bw.wp.nsplit1;
-    p.rmax = static_cast<int32_t>(widest_output(a));
-    if (p.nsplit > 1) p.partial = at<float>(ws, bw.partial_a);
-    const int64_t upper = static_cast<int64_t>(p.MTp[a.q]) * p.NTp[a.q] * p.nsplit;
-    st = hip_status(launch_gemm_async(kModeBwdWeight, p, upper, cu_count(), stream));
-    if (st != STAR_OK) return st;
-    // dbias = column sums of dY over the rows of valid type, in fixed chunks,
-    // added beside the partials of dW if there are any
-    float* cs = dbias ? at<float>(ws, bw.colsum) : nullptr;
-    if (dbias) {
-      const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
-      st = hip_status(launch_column_sum(static_cast<const uint16_t*>(dY), p.N, p.perm, p.offsets, a.q, p.M,
-                                        chunk, kColSumChunks, cs, stream));
-      if (st != STAR_OK) return st;
-    }
-    if (p.nsplit > 1) {
-      p.dbias = dbias;
-      return hip_status(launch_block_reduce(p, cs, kColSumChunks, stream));
-    }
-    return dbias ? hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream)) : STAR_OK;
-  }
-  p.A = X;
-  p.B = dY;
-  p.dW = dW;
-  // the graph law's diagonal tiles do not contract over every row, so its
-  // bias gradient is summed apart (below)
-  p.dbias = a.law == STAR_LAW_GRAPH ? nullptr : dbias;
-  p.nsplit = p.nsplit1 = bw.nsplit;
-  if (bw.nsplit > 1) {
-    p.partial = at<float>(ws, bw.partial);
-    p.dbias_part = at<float>(ws, bw.dbias_part);
-  }
-  st = hip_status(launch_gemm(kModeBwdWeight, p, stream));
-  if (st == STAR_OK && bw.nsplit > 1) st = hip_status(launch_split_reduce(p, stream));
-  if (st != STAR_OK || a.law != STAR_LAW_GRAPH || !dbias) return st;
-  const int32_t chunk = static_cast<int32_t>((M + kColSumChunks - 1) / kColSumChunks);
-  float* cs = at<float>(ws, bw.colsum);
-  st = hip_status(launch_column_sum_f32(static_cast<const float*>(dY), p.N, p.perm, p.offsets, a.q, p.M, chunk,
-                                        kColSumChunks, cs, stream));
-  if (st != STAR_OK) return st;
-  return hip_status(launch_sum_chunks(cs, kColSumChunks, p.N, dbias, stream));
+  return run_bwd_weight(a, M, bwd_weight_fit(a, M, xt, ws_bytes), plan, X, xt, dY, dW, dbias, ws, ws_bytes, stream);
 }
 
 star_status star_proj_bwd_weight(const star_algebra* alg, int64_t M, const int32_t* row_type,
@@ -1059,15 +1153,14 @@ star_status star_proj_bwd_weight(const star_algebra* alg, int64_t M, const int32
   if ((X && !aligned16(X)) || (dY && !aligned16(dY)) || !aligned16(dW) ||
       (dbias && !aligned4(dbias)))
     return STAR_ERR_ALIGN;
-  const BwdWs bw = bwd_weight_fit(a, M, ws_bytes);
+  const BwdWs bw = bwd_weight_fit(a, M, xt, ws_bytes);
   if (!ws || ws_bytes < bw.end) return STAR_ERR_WORKSPACE;
   if (!aligned16(ws)) return STAR_ERR_ALIGN;
   if (M > 0) {
     st = run_plan(row_type, M, a.q, ws, bw.plan, stream);
     if (st != STAR_OK) return st;
   }
-  return star_proj_bwd_weight_planned(alg, M, ws, X, xt, dY, dyt, dW, dbias, ws, ws_bytes,
-                                      stream);
+  return run_bwd_weight(a, M, bw, ws, X, xt, dY, dW, dbias, ws, ws_bytes, stream);
 }
 
 star_status star_ffn_fwd(const star_algebra* up, const star_algebra* down, int64_t M,

@@ -5,6 +5,9 @@ No test here launches a kernel, so all run without a GPU."""
 import ctypes
 import os
 import re
+import subprocess
+import sys
+import time
 
 import pytest
 
@@ -347,3 +350,27 @@ def test_attention_binding_refuses_bad_tensors(P):
     with pytest.raises(ValueError):
         P.star_attn_decode(sh, torch.zeros(8, dtype=torch.int32), torch.ones(1, dtype=torch.int32),
                            torch.zeros((1, 2, 64), dtype=torch.bfloat16), K, K)
+
+
+def test_workspace_query_of_the_widest_layer_returns():
+    """A host query is a query at any size it accepts: it allocates nothing of
+    the size of the tile list (2^44 tiles here, where a list of them ends the
+    process: the C entry cannot pass an exception on)."""
+    code = ("import paper_2609_32814_amd as P\n"
+            "a = P.Algebra(1, [1 << 30], [1 << 30], 'dense')\n"
+            "print(P.star_workspace_bytes('bwd_weight', a, None, 1024))")
+    r = subprocess.run([sys.executable, "-c", code], cwd=ROOT, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr[-500:]
+    # one split: the plan of 1024 rows (4 KiB and the offsets' line), then 64 chunk sums of 2^30 columns
+    assert int(r.stdout) == 4096 + 256 + 64 * 4 * (1 << 30)
+
+
+def test_workspace_query_time_does_not_follow_the_tile_count(P):
+    """The deal estimate takes runs of equal tiles: 2^24 tiles of 16 splits
+    (seconds and a gigabyte when listed one by one) cost what a few do.  The
+    bound leaves a factor of a thousand for a busy machine."""
+    a = P.Algebra(1, [1 << 20], [1 << 20], "dense")
+    P.star_workspace_bytes("bwd_weight", a, None, 1 << 20)
+    t0 = time.perf_counter()
+    P.star_workspace_bytes("bwd_weight", a, None, 1 << 20)
+    assert time.perf_counter() - t0 < 0.05
