@@ -364,6 +364,48 @@ def test_bwd_weight_parity(P, law, dtype, q, s, r, M):
     assert np.array_equal(to_host(dW2), to_host(dW)) and np.array_equal(to_host(db2), to_host(db))
 
 
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("law", ["star", "dense", "graph"])
+@pytest.mark.parametrize("q", [1, 63, 64])
+def test_tile_lookup_of_many_types(P, q, law, dtype):
+    """A tile's class and column group are looked up with one bound per lane:
+    as many types as lanes and one fewer, widths that give one or two column
+    tiles, classes without rows at both ends and in the middle, rows of no
+    valid type.  Every product of both operand types."""
+    import torch
+    rng = np.random.default_rng(600 + q)
+    edges = (rng.random((q, q)) < 0.3).astype(int).tolist() if law == "graph" else None
+    s = [int(8 * v) for v in rng.integers(8, 12, q)]
+    r = [int(8 * v) for v in rng.integers(1, 36, q)]
+    ga = P.Algebra(q, s, r, law, edges)
+    oa = oracle.Alg(q, tuple(s), tuple(r), law, edges)
+    M = 700
+    t = rng.integers(0, q, M).astype(np.int32)
+    if q > 1:
+        t[np.isin(t, [0, q // 2, q - 1])] = 1
+    t[5] = q  # no valid type
+    ok = t < q
+    X = synth.gaussian(601, 0, (M, oa.K), 1.0, dtype)
+    W = synth.gaussian(601, 1, (oa.K, oa.N), 0.05, dtype)
+    dY = synth.gaussian(601, 2, (M, oa.N), 1.0, dtype)
+    td = types_dev(t)
+    got = []
+    for tiles in ("wide", "auto"):
+        P.star_set_fwd_tiles(tiles)
+        try:
+            got.append(P.star_proj_fwd(ga, td, to_dev(X), to_dev(W), out_dtype=torch.float32))
+        finally:
+            P.star_set_fwd_tiles("auto")
+    rY = oracle.proj_fwd(oa, t[ok], X.exact[ok], W.exact)[0]
+    for Y in got:
+        assert rel_fro(to_host(Y)[ok], rY) <= bar(dtype)
+    dX = P.star_proj_bwd_data(ga, td, to_dev(dY), to_dev(W), out_dtype=torch.float32)
+    assert rel_fro(to_host(dX)[ok], oracle.proj_bwd_data(oa, t[ok], dY.exact[ok], W.exact)) <= bar(dtype)
+    dW, db = P.star_proj_bwd_weight(ga, td, to_dev(X), to_dev(dY))
+    rW, rb = oracle.proj_bwd_weight(oa, t[ok], X.exact[ok], dY.exact[ok])
+    assert rel_fro(to_host(dW), rW) <= bar(dtype) and rel_fro(to_host(db), rb) <= bar(dtype)
+
+
 @pytest.mark.parametrize("law", ["tensor2", "graph"])
 @pytest.mark.parametrize("s,r", [([192] * 4, [384] * 4), ([384, 192, 576, 192], [192, 384, 200, 392])])
 def test_192_wide_tiles_tensor_law(P, law, s, r):
