@@ -147,9 +147,8 @@ __global__ __launch_bounds__(kThreads, kPerCU) void star_gemm_f32_kernel(const G
   const uint32_t lds0 = lds_addr(smem);
 
   // ---- tiles per class and pass: lane i holds class i (q <= 64) ----
-  int32_t units = 0, cnt[2] = {0, 0}, pfx[2], ntp_next = 0;
+  int32_t units = 0, cnt[2] = {0, 0}, pfx[2];
   if (lane < q) {
-    ntp_next = p.NTp[lane + 1];
     if constexpr (MODE == kModeBwdWeight) units = (p.MTp[lane + 1] - p.MTp[lane]) * p.nsplit;
     else units = (p.offsets[lane + 1] - p.offsets[lane] + TM - 1) / TM;
 #pragma unroll
@@ -178,7 +177,7 @@ __global__ __launch_bounds__(kThreads, kPerCU) void star_gemm_f32_kernel(const G
     const int cls = __popcll(__ballot(mypfx <= logical));
     const int32_t before = __builtin_amdgcn_readlane(mypfx - (ps == 0 ? cnt[0] : cnt[1]), cls);
     const Tile t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - before,
-                                                __builtin_amdgcn_readlane(units, cls), p.offsets, ntp_next, TM);
+                                                __builtin_amdgcn_readlane(units, cls), p.offsets, TM);
 
     // ---- copy sources of this tile ----
     // K-contiguous A: the lane's row of copy j (rows past the tile's end read

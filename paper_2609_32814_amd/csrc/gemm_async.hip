@@ -147,7 +147,6 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   // row tiles x splits of pass 0 and of pass 1)
   __shared__ int32_t units_s[2][kMaxQGroups];
   __shared__ int32_t offs_s[kMaxQGroups + 1];
-  __shared__ int32_t ntp_s[64];  // p.NTp[i + 1]
   // tile prefix sums per class: pass 0, pass 1, pass 1 in half-height tiles
   __shared__ int32_t pfx_s[3][kMaxQGroups + 1];
   __shared__ __attribute__((aligned(16))) int32_t rows_s[kRowBufs][BM];
@@ -166,7 +165,6 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   const int lr = lane & 31, lh = lane >> 5;
 
   for (int i = threadIdx.x; i <= q; i += kThreads) offs_s[i] = p.offsets[i];
-  if (threadIdx.x < 64) ntp_s[threadIdx.x] = static_cast<int>(threadIdx.x) < q ? p.NTp[threadIdx.x + 1] : 0;
   __syncthreads();
   for (int i = threadIdx.x; i < q; i += kThreads) {
     if constexpr (MODE == kModeBwdWeight) {
@@ -240,11 +238,11 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     const int ps = v < pcount[0] ? 0 : 1;
     const int32_t logical = pbase[ps] + (ps == 0 ? v : v - pcount[0]);
     const int32_t* pf = pfx_s[ps == 0 ? 0 : p1];
-    const int cls = group_at(pf[min(lane + 1, q)], q, logical);
+    const int cls = last_start(pf, q, logical);
     const bool hh = ps == 1 && half1;
     const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
     t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
-                                     units_s[un][cls], offs_s, ntp_s[lane], hh ? TM / 2 : TM);
+                                     units_s[un][cls], offs_s, hh ? TM / 2 : TM);
     if constexpr (PAIR) t.nsteps *= 2;
     return true;
   };

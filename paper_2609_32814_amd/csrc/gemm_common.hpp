@@ -226,22 +226,25 @@ struct Tile {
   int32_t do_dbias;
 };
 
-// The i < q with bound(i) <= x < bound(i + 1), where the lane holds `next` =
-// bound(lane + 1) of a rising sequence (any value in lanes from q on).  Each
-// lane tests one bound: a walk from bound to bound, the class and the column
-// group of every tile, took a 64-type tile of one K step about 10 us.  Every
-// lane of the wave takes part, with the same x.
-__device__ __forceinline__ int group_at(int32_t next, int q, int32_t x) {
-  return __popcll(__ballot(static_cast<int>(threadIdx.x & 63) < q && next <= x));
+// The last i < q with start[i] <= x (start[0] <= x), by halving: a walk from
+// group to group, for the class and the column group of every tile, took a
+// 64-type tile of one K step about 10 us.
+__device__ __forceinline__ int last_start(const int32_t* start, int q, int32_t x) {
+  int lo = 0, hi = q - 1;
+  while (lo < hi) {
+    const int mid = (lo + hi + 1) >> 1;
+    if (x >= start[mid]) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
 }
 
 // `offs` holds the q + 1 type offsets of the plan (global memory or an LDS
-// copy), `ntp_next` the lane's p.NTp[lane + 1] (lanes from q on: any value).
-// Forward and activation gradient: row tiles are `bm` rows (BM, or BM / 2 for
-// the half-height tiles that balance a short last round).
+// copy).  Forward and activation gradient: row tiles are `bm` rows (BM, or
+// BM / 2 for the half-height tiles that balance a short last round).
 template <int MODE, int LAW, int BN, int BK>
 __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls, int32_t u,
-                                          int32_t units, const int32_t* offs, int32_t ntp_next, int bm = BM) {
+                                          int32_t units, const int32_t* offs, int bm = BM) {
   Tile t;
   const int32_t nsplit = pass_of(MODE, sel) == 0 ? p.nsplit : p.nsplit1;
   // Forward and activation gradient: column tiles vary fastest, so that the
@@ -258,7 +261,7 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
     cidx = u % nc;
   }
   const int ct = col_tile_global(p, sel, cls, cidx);
-  const int cg = group_at(ntp_next, p.q, ct);
+  const int cg = last_start(p.NTp, p.q, ct);
   const int nt = ct - p.NTp[cg];
   t.cls = cls;
   t.cg = cg;
