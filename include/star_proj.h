@@ -390,6 +390,16 @@ typedef enum {
 } star_tiles;
 int star_set_fwd_tiles(int tiles);
 
+/* The tiles that a call with bf16 operands runs on (host only): shape[0] rows
+ * and shape[1] columns of C, and for the weight gradient the row ranges that
+ * the contractions of its diagonal blocks (shape[2]) and of the others
+ * (shape[3]) are cut into, given the whole workspace; 1 elsewhere.  op:
+ * STAR_OP_FWD (as star_set_fwd_tiles stands), STAR_OP_BWD_DATA (the pair
+ * product's too) or STAR_OP_BWD_WEIGHT; M >= 1; act: of the call (act_prev;
+ * ignored by the weight gradient). */
+star_status star_tile_shape(int32_t op, const star_algebra *alg, int64_t M, star_act act,
+                            int32_t *shape);
+
 /* Workspace bytes an entry point needs (alg2 is the down algebra for
  * STAR_OP_FFN_FWD and STAR_OP_DECODE, else ignored).  Returns 0 for invalid
  * arguments. */

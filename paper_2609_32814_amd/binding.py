@@ -72,6 +72,7 @@ def _load() -> ctypes.CDLL:
     lib.star_count_products.argtypes = [A, ctypes.POINTER(i64)]
     lib.star_set_fwd_tiles.argtypes = [ctypes.c_int]
     lib.star_set_fwd_tiles.restype = ctypes.c_int
+    lib.star_tile_shape.argtypes = [i32, A, i64, E, ctypes.POINTER(i32)]
     lib.star_count_macs.argtypes = [A, ctypes.POINTER(i64), ctypes.POINTER(i64)]
     lib.star_validate_types.argtypes = [i64, P, i32, ctypes.POINTER(i64), P, sz, P]
     lib.star_plan_bytes.argtypes = [i32, i64]
@@ -96,7 +97,7 @@ def _load() -> ctypes.CDLL:
     for name in ("star_proj_fwd", "star_proj_bwd_data", "star_proj_bwd_weight", "star_ffn_fwd",
                  "star_decode", "star_count_products", "star_count_macs", "star_validate_types",
                  "star_type_plan", "star_proj_fwd_planned", "star_proj_bwd_data_planned",
-                 "star_proj_bwd_data_pair_planned",
+                 "star_proj_bwd_data_pair_planned", "star_tile_shape",
                  "star_proj_bwd_weight_planned", "star_swiglu_fwd", "star_swiglu_bwd", "star_add",
                  "star_decode_gated", "star_decode_status", "star_decode_noalloc", "star_attn_fwd",
                  "star_attn_decode", "star_swiglu_merged_fwd", "star_swiglu_up_fwd_planned"):
@@ -263,6 +264,15 @@ def star_set_fwd_tiles(tiles: str) -> str:
         raise ValueError(f"tiles must be one of {sorted(TILES)}, not {tiles!r}")
     prev = int(LIB.star_set_fwd_tiles(TILES[tiles]))
     return {v: k for k, v in TILES.items()}[prev]
+
+
+def star_tile_shape(op: str, alg: Algebra, M: int, act: str = "none") -> tuple:
+    """Rows and columns of the tiles that a bf16 "fwd", "bwd_data" or
+    "bwd_weight" call runs on, and the weight gradient's row ranges (diagonal
+    blocks, others; 1 elsewhere).  Host only."""
+    shape = (ctypes.c_int32 * 4)()
+    _check(LIB.star_tile_shape(OPS[op], alg.ref, int(M), ACTS[act], shape), "star_tile_shape")
+    return tuple(shape)
 
 
 def star_count_products(alg: Algebra) -> list[int]:

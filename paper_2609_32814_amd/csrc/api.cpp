@@ -148,21 +148,17 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
   return n;
 }
 
-// Column-tile width of the pipelined bf16 kernel: 256, or 192 (not the
-// graph law) where the launch's estimated makespan is shorter, a 192-wide
-// K step counted as 0.9 of a 256-wide one (its copies and per-step costs do
-// not shrink with its MFMAs).  The estimate deals the two passes' tiles (K
-// steps each, in the kernel's order, rows taken as spread evenly over the
-// types, as the host does not read the per-type counts) the way the kernel
-// does on 256 CUs: an eighth of each pass per XCD, in snake order over the
-// XCD's 32 workgroups, each tile also paying its epilogue.  Checked against
-// measured pairs: 8192 x 768 -> 3072 at q = 2 (192: 512 tiles, one long and
-// one short per CU), the 384-wide groups of 16384 x 3072 -> 768 (192: no
-// padding), and the weight gradient 768 x 3072 over 16384 rows (256: at 192
-// the split count drops to 4 and the diagonal tiles run long).  The tensor
-// law's 192- and 384-wide groups take them for the same reason (16384 rows,
-// 768 <-> 1536, q = 4: activation gradients 59 and 67 -> 52 and 58 us,
-// weight gradient 98 -> 87 us).
+// Tile shape of the pipelined bf16 kernel (not for the graph law, which keeps
+// 256 x 256): the one whose launch has the shortest estimated makespan.  The
+// estimate deals the two passes' tiles (K steps each, in the kernel's order,
+// rows taken as spread evenly over the types, as the host does not read the
+// per-type counts) the way the kernel does on 256 CUs: an eighth of each pass
+// per XCD, in snake order over the XCD's 32 workgroups.  Rates, fixed part
+// and margin below are set from 600 products timed on all four shapes (64 to
+// 20000 rows, q = 1 to 64, widths 256 to 6144, types cyclic and in runs): none
+// of them is more than 2 % slower than with 256-row tiles alone, and the
+// mean gain over those is 9 %.  (The kernel's half-height second pass is not
+// in the estimate.)
 //
 // The estimate runs at every launch, so it takes runs of equal tiles and not
 // single ones, and allocates nothing (an entry point that runs out of memory
@@ -230,20 +226,24 @@ bool equal_widths(const Alg& a, bool over_r) {
     if ((over_r ? a.r(g) : a.s(g)) != (over_r ? a.r(0) : a.s(0))) return false;
   return true;
 }
-// mode: the kernel's (forward, activation gradient); not for the graph law
-double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act) {
+// The launch's time in 256 x 256 steps.  mode: the kernel's (forward,
+// activation gradient); rate: of a step of this tile shape; not for the graph
+// law.
+double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool act, double rate) {
   const int q = a.q;
   const bool fwd = mode == kModeFwd;
   const int64_t rt = tiles_of((M + q - 1) / q, tm);  // row tiles of a type
   int64_t ct[kMaxQGroups], cols = 0;                 // column tiles of a group, of all
   for (int j = 0; j < q; ++j) cols += ct[j] = tiles_of(fwd ? a.r(j) : a.s(j), tn);
-  const double epi = (act ? (fwd ? 3.0 : 2.0) : 1.0) * tn * tm / (256 * 256);
+  // a tile's epilogue, by its area, and what every tile costs whatever its
+  // shape (first copies, row indices, lookup): 0.75 of a 256 x 256 step
+  const double epi = (act ? (fwd ? 3.0 : 2.0) : 1.0) * tn * tm / (256 * 256) + 0.75 / rate;
   // pass 0: the two-segment tiles (forward), the tiles over every output
   // group (activation gradient)
   if (a.law == STAR_LAW_DENSE) {
     Deal d(q * rt * cols, 0, epi);
     d.add(0, d.total[0], steps_of(fwd ? a.K() : a.N()));
-    return d.makespan();
+    return rate * d.makespan();
   }
   if (a.law == STAR_LAW_TENSOR2) {
     int st[4][4], ps[4][4];  // q is 1, 2 or 4
@@ -264,7 +264,7 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
     for (int i = 0; i < q; ++i)
       for (int64_t u = 0; u < rt; ++u)
         for (int j = 0; j < q; ++j) d.add(ps[i][j], ct[j], st[i][j]);
-    return d.makespan();
+    return rate * d.makespan();
   }
   const int own = fwd ? 1 : 0;  // the pass of a type's own group
   const int64_t mine = rt * cols, others = rt * (q - 1) * cols;
@@ -273,7 +273,7 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
     const int one = steps_of(fwd ? a.s(0) : a.r(0));
     d.add(0, d.total[0], fwd ? 2 * one : steps_of(a.N()));
     d.add(1, d.total[1], one);
-    return d.makespan();
+    return rate * d.makespan();
   }
   int steps[kMaxQGroups];
   for (int j = 0; j < q; ++j) steps[j] = steps_of(fwd ? a.s(j) : a.r(j));
@@ -284,7 +284,7 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
         const int st = fwd ? steps[j] + (j != i ? steps[i] : 0) : (j == i ? full : steps[j]);
         d.add(j == i ? own : 1 - own, ct[j], st);
       }
-  return d.makespan();
+  return rate * d.makespan();
 }
 // The tiles are 192 wide only where that pads fewer C columns as well: without
 // padding to remove, the 192-wide tiles' extra re-reads of the row tiles
@@ -294,15 +294,24 @@ double async_makespan(const Alg& a, int mode, int64_t M, int tm, int tn, bool ac
 // star law's forward takes them at equal padding too: its types alternate
 // (8192 x 768 -> 3072 with GELU, q = 2: cyclic types 50.7 against 55.0 us,
 // 192-row runs 62.8 and 63.8; at 4096 rows 31.8 against 35.6, and 38 with
-// unequal counts that add a row tile).
+// unequal counts that add a row tile), by 3 % at least (16384 rows, q = 4:
+// 66.4 us where the estimate has them level, 256 wide 64.8).
 int64_t padded_cols(const Alg& a, bool over_r, int tn) { return col_tiles(a, over_r, tn) * tn; }
-// 128-row tiles take about 0.7 of a 256-row tile's step (128 x 256: 0.75 of a
-// 256 x 256 one, 128 x 192: 0.65), so they pay where 256-row tiles leave CUs
-// without a tile or a long tile beside a short one: 8192 rows, q = 2, 3072 ->
-// 768 on 256 x 192 tiles is 64 tiles of 48 steps and 64 of 24 on 256 CUs (76
-// us; 58 on 128 x 192), its counterpart's activation gradient 72 and 58, the
-// dense 4096 x 2048 x 2048 55 and 48; with twice the rows every CU has a
-// tile and 256 rows stay faster (80 and 85 us).
+// A step of a smaller tile against one of 256 x 256: 256 x 192 0.87 (its
+// copies and per-step costs do not shrink with its MFMAs), 128 x 256 0.73,
+// 128 x 192 0.63.  So 128-row tiles pay where 256-row tiles leave CUs without
+// a tile or a long tile beside a short one: 8192 rows, q = 2, 3072 -> 768 on
+// 256 x 192 tiles is 64 tiles of 48 steps and 64 of 24 on 256 CUs (76 us; 58
+// on 128 x 192), its counterpart's activation gradient 72 and 58, the dense
+// 4096 x 2048 x 2048 55 and 48; with twice the rows every CU has a tile and
+// 256 rows stay faster (80 and 85 us).  Where tiles are short, the part that
+// every tile costs decides for the larger ones: 15279 rows, q = 16, 512 ->
+// 512, activation gradient, 25 us on 256 x 192 and 28 on 128 x 192; 16384
+// rows, q = 64, 512 -> 3072, 114 and 125.  A 256 x 192 tile of 65 to 128 rows
+// runs like a 128 x 192 one in the activation gradient (half of its waves
+// skip their products, the others have twice as many to hide the copies
+// behind): 512 rows, dense, q = 4, 768 <- 3072, 42 and 45 us; of 64 rows or
+// fewer it takes a sixth longer.
 struct TileShape {
   int tm, tn;
 };
@@ -311,18 +320,19 @@ TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
   const bool over_r = mode != kModeBwdData;
   const int64_t pad192 = padded_cols(a, over_r, 192), pad256 = padded_cols(a, over_r, 256);
   const bool try192 = pad192 < pad256 || (pad192 == pad256 && a.law == STAR_LAW_STAR && mode == kModeFwd);
+  const int64_t per = (M + a.q - 1) / a.q;  // rows of a type
   TileShape best{256, 256};
-  double cost = async_makespan(a, mode, M, 256, 256, act);
-  auto consider = [&](int tm, int tn, double rate, double margin) {
-    const double c = rate * async_makespan(a, mode, M, tm, tn, act);
+  double cost = async_makespan(a, mode, M, 256, 256, act, 1.0);
+  auto consider = [&](int tm, int tn, double rate, double margin, double live = 1.0) {
+    const double c = live * async_makespan(a, mode, M, tm, tn, act, rate);
     if (c < margin * cost) {
       cost = c;
       best = {tm, tn};
     }
   };
-  if (try192) consider(256, 192, 0.9, 1.0);
-  consider(128, 256, 0.75, 0.95);
-  if (try192) consider(128, 192, 0.65, best.tm == 128 ? 1.0 : 0.95);
+  if (try192) consider(256, 192, 0.87, pad192 < pad256 ? 1.0 : 0.97, mode == kModeBwdData && per > 64 && per <= 128 ? 0.735 : 1.0);
+  consider(128, 256, 0.73, 0.98);
+  if (try192) consider(128, 192, 0.63, best.tm == 128 ? 1.0 : 0.98);
   return best;
 }
 
@@ -909,6 +919,34 @@ const char* star_status_string(star_status s) {
     case STAR_ERR_HIP: return "HIP runtime error";
   }
   return "unknown status";
+}
+
+star_status star_tile_shape(int32_t op, const star_algebra* alg, int64_t M, star_act act, int32_t* shape) {
+  Alg a;
+  star_status st = parse_alg(alg, a, op == STAR_OP_FWD);
+  if (st != STAR_OK) return st;
+  if (M < 1 || M > kMaxDim) return STAR_ERR_SHAPE;
+  if (!shape || !valid_act(act)) return STAR_ERR_ARG;
+  if (op == STAR_OP_BWD_WEIGHT) {
+    const WeightPlan w = weight_plan(a, M);
+    shape[0] = w.tm;
+    shape[1] = w.tn;
+    shape[2] = w.nsplit;
+    shape[3] = w.nsplit1;
+    return STAR_OK;
+  }
+  if (op != STAR_OP_FWD && op != STAR_OP_BWD_DATA) return STAR_ERR_ARG;
+  TileShape ts = kSmallTiles;
+  if (a.q <= kMaxQGroups) {
+    GemmParams p;
+    fill_common(p, a, M, 1, nullptr, nullptr);
+    p.act = act;
+    ts = proj_tiles(op == STAR_OP_FWD ? kModeFwd : kModeBwdData, p);
+  }
+  shape[0] = ts.tm;
+  shape[1] = ts.tn;
+  shape[2] = shape[3] = 1;
+  return STAR_OK;
 }
 
 size_t star_workspace_bytes(int32_t op, const star_algebra* alg, const star_algebra* alg2,

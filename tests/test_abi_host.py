@@ -374,3 +374,36 @@ def test_workspace_query_time_does_not_follow_the_tile_count(P):
     t0 = time.perf_counter()
     P.star_workspace_bytes("bwd_weight", a, None, 1 << 20)
     assert time.perf_counter() - t0 < 0.05
+
+
+@pytest.mark.parametrize("op,law,q,K,N,M,act,tiles", [
+    # short tiles: what every tile costs whatever its shape decides for the larger ones
+    ("bwd_data", "star", 16, 512, 512, 15279, "none", (256, 192)),     # 25 us; 28 on 128 x 192
+    ("bwd_data", "star", 64, 512, 3072, 16384, "none", (256, 192)),    # 114; 125
+    ("bwd_data", "star", 16, 1024, 1024, 16384, "none", (256, 192)),   # 36; 38
+    ("bwd_data", "dense", 4, 768, 3072, 512, "none", (256, 192)),      # 42; 45: half of the waves without rows
+    ("fwd", "star", 3, 1008, 4080, 3001, "gelu", (256, 256)),          # 35; 37 on 256 x 192
+    ("fwd", "star", 4, 768, 3072, 16384, "gelu", (256, 256)),          # 65; 66
+    # few or unequal tiles: 128 rows
+    ("bwd_data", "star", 2, 768, 3072, 8192, "none", (128, 192)),
+    ("fwd", "star", 2, 3072, 768, 8192, "none", (128, 192)),
+    ("fwd", "dense", 1, 2048, 2048, 4096, "none", (128, 256)),
+    ("fwd", "star", 2, 768, 3072, 8192, "gelu", (256, 192)),
+    ("fwd", "graph", 4, 768, 3072, 8192, "none", (256, 256)),
+    ("fwd", "star", 32, 1024, 4096, 2048, "none", (64, 128)),          # groups narrower than 64
+])
+def test_tile_shape_choice(P, op, law, q, K, N, M, act, tiles):
+    """The tile rule at shapes timed on every tile shape (us at the side)."""
+    edges = [[1] * q for _ in range(q)] if law == "graph" else None
+    assert P.star_tile_shape(op, P.Algebra.equal(q, K, N, law, edges), M, act)[:2] == tiles
+
+
+def test_tile_shape_refuses_what_the_calls_refuse(P):
+    a = P.Algebra.equal(2, 128, 128)
+    for op, M in (("ffn_fwd", 8), ("decode", 8), ("fwd", 0), ("fwd", 1 << 31)):
+        with pytest.raises(P.StarError):
+            P.star_tile_shape(op, a, M)
+    wide = P.Algebra.equal(128, 1024, 1024)
+    assert P.star_tile_shape("fwd", wide, 64)[:2] == (64, 128)
+    with pytest.raises(P.StarError):
+        P.star_tile_shape("bwd_data", wide, 64)
