@@ -367,7 +367,13 @@ bool weight_first_pass(const Alg& a, int i, int j, int types) {
 // q = 4 types, 768 x 1536, ran 64 items of 32 steps beside 192 of 8 (star)
 // and took as long as the dense product with twice the work.  What a split
 // costs, in steps of about 1.8 us: kItem for its tile of partials (written
-// by all CUs at once), and the bytes the second kernel reads at 4.5 TB/s.
+// by all CUs at once; kWhole for the tile of dW without splits), and the
+// bytes the second kernel reads at 3.7 TB/s.  Splits have to win 3 %.  Of 332
+// products timed with 1 to 16 splits (1024 to 30000 rows, q = 1 to 64, every
+// law), none is slower by these than with the former rule of one count for
+// both passes, and the mean is a third faster; with 4.5 TB/s, kItem 4 and no
+// margin the tensor law's 8192 x 4096 x 4096, q = 4, took four splits (298
+// us, unsplit 259).
 // The tiles of dW of one shape, per pass and number of row types.
 struct WeightTiles {
   int tm, tn;
@@ -375,8 +381,8 @@ struct WeightTiles {
 };
 WeightPlan weight_plan_shape(const Alg& a, int64_t M, const WeightTiles& t, const double (&cells)[2], int c1, int most,
                              double* cost) {
-  constexpr double kItem = 4.0, kStepUs = 1.8, kReadBytesUs = 4.5e6;
-  const double rate = t.tm == 256 && t.tn == 256 ? 1.0 : 0.9;  // of a smaller tile's step
+  constexpr double kItem = 3.0, kWhole = 0.5, kStepUs = 1.8, kReadBytesUs = 3.7e6, kWin = 0.97;
+  const double rate = t.tm == 256 && t.tn == 256 ? 1.0 : 0.88;  // of a smaller tile's step
   int64_t tiles[2] = {0, 0};
   for (int ps = 0; ps < 2; ++ps)
     for (int n = 0; n <= a.q; ++n) tiles[ps] += t.count[ps][n];
@@ -385,7 +391,7 @@ WeightPlan weight_plan_shape(const Alg& a, int64_t M, const WeightTiles& t, cons
   for (int ns = 1; ns <= most; ++ns) {
     const int ns1 = a.law == STAR_LAW_DENSE ? ns : std::max(1, (ns * c1 + a.q - 1) / a.q);
     // (the first XCD's share of a pass is its longest items)
-    Deal d(tiles[0] * ns, tiles[1] * ns1, ns > 1 ? kItem : 1.0, 1);
+    Deal d(tiles[0] * ns, tiles[1] * ns1, ns > 1 ? kItem : kWhole, 1);
     for (int ps = 0; ps < 2; ++ps) {
       const int s = ps == 0 ? ns : ns1;
       for (int n = a.q; n >= 0; --n)
@@ -393,7 +399,7 @@ WeightPlan weight_plan_shape(const Alg& a, int64_t M, const WeightTiles& t, cons
     }
     const double read = ns > 1 ? (cells[0] * ns + cells[1] * ns1) * 4.0 / kReadBytesUs / kStepUs : 0.0;
     const double c = rate * d.makespan() + read;
-    if (ns == 1 || c < *cost) {
+    if (ns == 1 || c < (best.nsplit == 1 ? kWin : 1.0) * *cost) {
       *cost = c;
       best.nsplit = ns;
       best.nsplit1 = ns1;

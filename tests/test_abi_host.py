@@ -407,3 +407,14 @@ def test_tile_shape_refuses_what_the_calls_refuse(P):
     assert P.star_tile_shape("fwd", wide, 64)[:2] == (64, 128)
     with pytest.raises(P.StarError):
         P.star_tile_shape("bwd_data", wide, 64)
+
+
+@pytest.mark.parametrize("law,q,K,N,M,shape", [
+    ("tensor2", 4, 4096, 4096, 8192, (256, 256, 1, 1)),   # 259 us; 298 in four and two ranges
+    ("star", 3, 4080, 4080, 8192, (256, 256, 1, 1)),      # 261; 273 in two and one
+    ("dense", 2, 3920, 5216, 8091, (256, 192, 1, 1)),     # 475; 501 in two of 256 x 256
+    ("star", 4, 768, 1536, 8192, (256, 192, 8, 2)),       # 50; 54 in eight and eight
+])
+def test_weight_gradient_ranges(P, law, q, K, N, M, shape):
+    """The number of row ranges at shapes timed with 1 to 16 (us at the side)."""
+    assert P.star_tile_shape("bwd_weight", P.Algebra.equal(q, K, N, law), M) == shape
