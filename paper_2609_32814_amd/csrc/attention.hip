@@ -314,7 +314,15 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
   // global-to-LDS copies of a step's key and value rows (kp: the position of
   // key row `lane`)
   const void* zero = g_attn_zero;
+  // (32 x 32 -> 64 bits: with a 64-bit stride an address cost seven more
+  // instructions, three of them at a quarter of the rate, and star law shapes
+  // of one workgroup a CU, where few chunks are selected, were slower than
+  // with copies of those alone: 1 x 4096 positions, 8 heads of 64, q = 8, 91
+  // -> 94 us, now 91.  Left: 8 x 128 positions, 32 heads of 128 over 8, q =
+  // 8, 102 against 99, copies of rows past a type's end; skipping those by a
+  // branch a copy cost long sequences 2 %)
   constexpr int RPC = 64 / CPR;  // rows of a copy
+  const uint32_t row16 = static_cast<uint32_t>(ldk >> 3);  // a position's stride in 16-byte units
   auto issue = [&](int32_t kp, int stage) {
     char* Kt = tiles + stage * 2 * TILE;
 #pragma unroll
@@ -323,10 +331,11 @@ __global__ __launch_bounds__(fwd_threads<DH>()) void attn_fwd_kernel(const AttnP
       const int row = cp * RPC + lane / CPR, c = lane % CPR;
       const int32_t pos = __shfl(kp, row);
       const bool ok = pos < p.S;
-      const int64_t at = static_cast<int64_t>(ok ? pos : 0) * ldk;
-      dma16(ok ? static_cast<const void*>(Kg + at + 8 * (c ^ key_swz<DH>(row))) : zero, lds_addr(Kt + cp * 1024));
-      dma16(ok ? static_cast<const void*>(Vg + at + 8 * (c ^ value_swz<DH>(row))) : zero,
-            lds_addr(Kt + TILE + cp * 1024));
+      const uint64_t at = (static_cast<uint64_t>(static_cast<uint32_t>(pos)) * row16) << 4;
+      const char* kr = reinterpret_cast<const char*>(Kg + 8 * (c ^ key_swz<DH>(row))) + at;
+      const char* vr = reinterpret_cast<const char*>(Vg + 8 * (c ^ value_swz<DH>(row))) + at;
+      dma16(ok ? static_cast<const void*>(kr) : zero, lds_addr(Kt + cp * 1024));
+      dma16(ok ? static_cast<const void*>(vr) : zero, lds_addr(Kt + TILE + cp * 1024));
     }
   };
 
