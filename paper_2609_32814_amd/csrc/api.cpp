@@ -523,6 +523,7 @@ constexpr size_t kDecodeStatusBytes = kCounterStride * sizeof(int32_t);
 struct DecodeWs {
   size_t h = 0, xb = 0, H = 0, end = 0;      // end: what the call cannot do without
   size_t cnt = 0, cnt_words = 0, part = 0;
+  int cols_up = kDecodePhaseN, cols_dn = kDecodePhaseN;
   int splits_up = 1, splits_dn = 1;
   size_t full = 0;  // with the splits
 };
@@ -544,13 +545,16 @@ DecodeWs decode_layout(const Alg& up, const Alg& down, int64_t M, size_t room = 
   w.cnt = cur;
   w.cnt_words = static_cast<size_t>(std::max(tu, td));
   w.part = align_up(cur + sizeof(int32_t) * w.cnt_words);
-  auto fit = [&](const Alg& a, int32_t tiles) {
+  w.cols_up = decode_phase_cols(up.law, up.q, up.S, up.R, M);
+  w.cols_dn = decode_phase_cols(down.law, down.q, down.S, down.R, M);
+  auto fit = [&](const Alg& a, int32_t tiles, int cols) {
+    if (cols != kDecodePhaseN) return 1;
     int n = decode_phase_splits(a.law, a.q, a.S, tiles, M);
     while (n > 1 && (w.part > room || decode_phase_part_bytes(tiles, n, M) > room - w.part)) --n;
     return n;
   };
-  w.splits_up = fit(up, tu);
-  w.splits_dn = fit(down, td);
+  w.splits_up = fit(up, tu, w.cols_up);
+  w.splits_dn = fit(down, td, w.cols_dn);
   if (w.splits_up > 1 || w.splits_dn > 1)
     w.full = align_up(w.part + std::max(decode_phase_part_bytes(tu, w.splits_up, M),
                                         decode_phase_part_bytes(td, w.splits_dn, M)));
@@ -1345,7 +1349,7 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
   float* h = at<float>(ws, dw.h);
   uint16_t* xb = at<uint16_t>(ws, dw.xb);
   uint16_t* Hb = at<uint16_t>(ws, dw.H);
-  auto fill = [&](DecodePhase& p, const Alg& a) {
+  auto fill = [&](DecodePhase& p, const Alg& a, int cols) {
     std::memset(&p, 0, sizeof(p));
     p.q = a.q;
     p.law = a.law;
@@ -1356,7 +1360,8 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
       p.S[g] = static_cast<int32_t>(a.S[g]);
       p.R[g] = static_cast<int32_t>(a.R[g]);
     }
-    fill_tiles(p.NTp, a.R, a.q, kDecodePhaseN);
+    p.cols = cols;
+    fill_tiles(p.NTp, a.R, a.q, cols);
     p.cnt = at<int32_t>(ws, dw.cnt);
     p.part = at<uint64_t>(ws, dw.part);
     for (int g = 0; g < kMaxQGroups; ++g) p.adj[g] = a.adj[g];
@@ -1365,8 +1370,8 @@ star_status decode_impl(const star_algebra* up, const star_algebra* down, int32_
     p.residual = residual;
   };
   DecodePhase pu, pd;
-  fill(pu, u);
-  fill(pd, d);
+  fill(pu, u, dw.cols_up);
+  fill(pd, d, dw.cols_dn);
   pu.splits = dw.splits_up;
   pd.splits = dw.splits_dn;
   pu.mode = 0;

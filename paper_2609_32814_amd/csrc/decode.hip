@@ -30,6 +30,11 @@
 // tile's workgroups to arrive adds all of them in split order, so results do
 // not depend on timing.  It also sets the tile's counter back to zero for
 // the next projection.  Nobody waits for anybody.
+//
+// A small projection of more than 16 rows takes tiles of 16 columns without
+// splits: with few slices the time is the workgroup's own end (the waves'
+// sums through LDS, bias, activation, stores), which then spreads over four
+// times as many workgroups.  See decode_phase_cols.
 #include <algorithm>
 
 #include "common.hpp"
@@ -40,10 +45,8 @@ namespace starq {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int TN = kDecodePhaseN;     // 64 output columns
 constexpr int SLICE = kDecodeSliceK;  // 32 K rows
-constexpr int kSliceBytes = SLICE * TN * 2;
-constexpr int kBlocks = TN / 16;
+constexpr int kWide = kDecodePhaseN / 16, kNarrow = kDecodeNarrowN / 16;  // 16-column blocks of a tile
 
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 #define STARQ_LDS __attribute__((address_space(3)))
@@ -76,7 +79,7 @@ __device__ __forceinline__ int group_of(const int32_t* starts, int q, int32_t x)
 }
 
 // Slices a wave holds in LDS: two workgroups per CU fit.
-constexpr int wave_slots(int mb) { return mb <= 2 ? 3 : 2; }
+constexpr int wave_slots(int mb, int nb) { return nb == kNarrow ? 4 : (mb <= 2 ? 3 : 2); }
 
 // 16-column block cb of slice row r sits at block cb ^ col_swz(r): the rows
 // a transposing read takes together (0-3 and 8-11 of a 16-row half) then
@@ -98,10 +101,15 @@ template <int N> __device__ __forceinline__ void wait_vm() {
   asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
 }
 
-// MB: 16-row blocks of the step (M <= 16 MB)
-template <int MB>
+// MB: 16-row blocks of the step (M <= 16 MB); NB: 16-column blocks of a tile
+template <int MB, int NB>
 __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodePhase p) {
-  constexpr int kSlots = wave_slots(MB);
+  constexpr int TN = 16 * NB;
+  constexpr int kSliceBytes = SLICE * TN * 2;
+  constexpr int kSlots = wave_slots(MB, NB);
+  // 16 x 16 blocks of the tile that a thread finishes (the waves' sums are
+  // shared out by block): block wave + 4 it, column block of it and row block
+  constexpr int kItems = (NB * MB + 3) / 4;
   constexpr int kSlot = kSliceBytes + MB * 1024;  // a slice's weights and input pieces
   extern __shared__ __attribute__((aligned(16))) char lds[];
   __shared__ unsigned long long rowmask_s[kMaxQGroups];
@@ -169,9 +177,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
   // pieces of rows 16 mb + lane%16
   const int G = lane >> 4;
   const int pl = lane & 15;
-  f32x4_t acc[kBlocks][MB];
+  f32x4_t acc[NB][MB];
 #pragma unroll
-  for (int cb = 0; cb < kBlocks; ++cb)
+  for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) acc[cb][mb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
   // this wave's slices: lo + wave + 4 t, t < n
@@ -179,7 +187,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
   char* mine = lds + wave * (kSlots * kSlot);
   const uint32_t mine_lds = __builtin_amdgcn_readfirstlane(static_cast<uint32_t>(reinterpret_cast<uintptr_t>(mine)));
   // Slice t into its slot: weights, 8 rows a copy (lane l: row l/8, 16 bytes
-  // of it), then the rows' input pieces, one copy a row block (zeros where
+  // of it; a 16-column tile's 32 rows in one copy), then the rows' input pieces, one copy a row block (zeros where
   // the support skips them).  Rows past K repeat row K-1 and columns past
   // the group repeat its first ones (finite values; their products are
   // either multiplied by zero inputs or never stored).
@@ -187,9 +195,9 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
     const int32_t k0 = slices_s[lo + wave + 4 * t] * SLICE;
     const uint32_t dst = mine_lds + (t % kSlots) * kSlot;
 #pragma unroll
-    for (int d = 0; d < SLICE / 8; ++d) {
-      const int r = 8 * d + (lane >> 3), c = lane & 7;
-      int32_t col = n0 + 16 * ((c >> 1) ^ col_swz(r)) + 8 * (c & 1);
+    for (int d = 0; d < NB; ++d) {
+      const int r = SLICE / NB * d + lane / (2 * NB), c = lane % (2 * NB);
+      int32_t col = n0 + 16 * (NB == kWide ? (c >> 1) ^ col_swz(r) : 0) + 8 * (c & 1);
       col = col < nend ? col : n0;
       dma16(p.W + static_cast<int64_t>(min(k0 + r, p.K - 1)) * p.N + col, dst + d * 1024);
     }
@@ -203,7 +211,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
             dst + kSliceBytes + mb * 1024);
     }
   };
-  constexpr int kCopies = SLICE / 8 + MB;  // of a slice
+  constexpr int kCopies = NB + MB;  // of a slice
   for (int t = 0; t < min(n, kSlots); ++t) copy(t);
   for (int t = 0; t < n; ++t) {
     // slice t has landed (the copies of the kSlots - 1 slices after it may
@@ -211,14 +219,14 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
     if (t + kSlots - 1 < n) wait_vm<(kSlots - 1) * kCopies>();
     else wait_vm<0>();
     const char* slot = mine + (t % kSlots) * kSlot;
-    uint4 wf[kBlocks], x[MB];
+    uint4 wf[NB], x[MB];
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb) x[mb] = *reinterpret_cast<const uint4*>(slot + kSliceBytes + mb * 1024 + lane * 16);
 #pragma unroll
-    for (int cb = 0; cb < kBlocks; ++cb) {
+    for (int cb = 0; cb < NB; ++cb) {
       const int r = 8 * G + (pl >> 2);
-      const char* a0 = slot + r * (2 * TN) + (cb ^ col_swz(r)) * 32 + (pl & 3) * 8;
-      const char* a1 = slot + (r + 4) * (2 * TN) + (cb ^ col_swz(r + 4)) * 32 + (pl & 3) * 8;
+      const char* a0 = slot + r * (2 * TN) + (NB == kWide ? cb ^ col_swz(r) : 0) * 32 + (pl & 3) * 8;
+      const char* a1 = slot + (r + 4) * (2 * TN) + (NB == kWide ? cb ^ col_swz(r + 4) : 0) * 32 + (pl & 3) * 8;
       const v4i16_t w0 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a0));
       const v4i16_t w1 = __builtin_amdgcn_ds_read_tr16_b64_v4i16((STARQ_LDS v4i16_t*)(a1));
       wf[cb].x = static_cast<uint16_t>(w0[0]) | (static_cast<uint32_t>(static_cast<uint16_t>(w0[1])) << 16);
@@ -230,7 +238,7 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
     asm volatile("s_waitcnt lgkmcnt(0)" : : : "memory");
     if (t + kSlots < n) copy(t + kSlots);
 #pragma unroll
-    for (int cb = 0; cb < kBlocks; ++cb)
+    for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
       for (int mb = 0; mb < MB; ++mb)
         // D[n][m] += W^T x^T: lane ends with 4 consecutive columns of row m
@@ -238,25 +246,27 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
             __builtin_bit_cast(bf16x8_t, wf[cb]), __builtin_bit_cast(bf16x8_t, x[mb]), acc[cb][mb], 0, 0, 0);
   }
 
-  // add the four waves' sums in a fixed order: thread tid then holds, for
-  // row block mb, columns n0 + 16 (tid / 64) + 4 (lane / 16) .. + 3 of row
-  // 16 mb + lane % 16
+  // add the four waves' sums in a fixed order: thread tid then holds, of row
+  // block mb and column block cb of item wave + 4 it, columns n0 + 16 cb + 4
+  // (lane / 16) .. + 3 of row 16 mb + lane % 16
   __syncthreads();  // every wave is done with its slots
   f32x4_t* red = reinterpret_cast<f32x4_t*>(lds);
 #pragma unroll
-  for (int cb = 0; cb < kBlocks; ++cb)
+  for (int cb = 0; cb < NB; ++cb)
 #pragma unroll
-    for (int mb = 0; mb < MB; ++mb) red[((wave * kBlocks + cb) * MB + mb) * 64 + lane] = acc[cb][mb];
+    for (int mb = 0; mb < MB; ++mb) red[((wave * NB + cb) * MB + mb) * 64 + lane] = acc[cb][mb];
   __syncthreads();
-  f32x4_t z[MB];
+  f32x4_t z[kItems];
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    z[mb] = red[(wave * MB + mb) * 64 + lane];
+  for (int it = 0; it < kItems; ++it) {
+    const int item = min(wave + 4 * it, NB * MB - 1), cb = item % NB, mb = item / NB;
+    z[it] = red[(cb * MB + mb) * 64 + lane];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) z[mb] += red[((w * kBlocks + wave) * MB + mb) * 64 + lane];
+    for (int w = 1; w < 4; ++w) z[it] += red[((w * NB + cb) * MB + mb) * 64 + lane];
   }
 
-  if (p.splits > 1) {
+  if (NB == kWide && p.splits > 1) {
+    // (item wave + 4 mb: column block wave of row block mb)
     // sums as two 8-byte words, one 16 MB x 64 block of them per (tile,
     // split); rows past M are not stored
     const int64_t block = static_cast<int64_t>(MB) * kThreads * 2;
@@ -306,11 +316,12 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
   }
 
 #pragma unroll
-  for (int mb = 0; mb < MB; ++mb) {
-    const int m = 16 * mb + pl;
-    const int32_t n = n0 + 16 * wave + 4 * G;
-    if (m >= p.M || n >= nend) continue;
-    f32x4_t v = z[mb];
+  for (int it = 0; it < kItems; ++it) {
+    const int item = wave + 4 * it;
+    const int m = 16 * (item / NB) + pl;
+    const int32_t n = n0 + 16 * (item % NB) + 4 * G;
+    if (item >= NB * MB || m >= p.M || n >= nend) continue;
+    f32x4_t v = z[it];
     if (p.bias) {
       const float4 bv = *reinterpret_cast<const float4*>(p.bias + n);
       v[0] += bv.x; v[1] += bv.y; v[2] += bv.z; v[3] += bv.w;
@@ -350,18 +361,24 @@ __global__ __launch_bounds__(kThreads, 2) void decode_phase_kernel(const DecodeP
   }
 }
 
-template <int MB>
-hipError_t launch_mb(const DecodePhase& p, hipStream_t stream) {
+template <int MB, int NB>
+hipError_t launch_nb(const DecodePhase& p, hipStream_t stream) {
   // the slots, reused for the waves' sums
-  constexpr size_t smem =
-      std::max<size_t>(4 * wave_slots(MB) * (kSliceBytes + MB * 1024), static_cast<size_t>(4 * kBlocks * MB) * 1024);
+  constexpr size_t smem = std::max<size_t>(4 * wave_slots(MB, NB) * (SLICE * NB * 32 + MB * 1024),
+                                           static_cast<size_t>(4 * NB * MB) * 1024);
   static std::atomic<unsigned long long> lds_set{0};
   const hipError_t attr =
-      ensure_lds_limit(reinterpret_cast<const void*>(decode_phase_kernel<MB>), lds_set, static_cast<int>(smem));
+      ensure_lds_limit(reinterpret_cast<const void*>(decode_phase_kernel<MB, NB>), lds_set, static_cast<int>(smem));
   if (attr != hipSuccess) return attr;
-  hipLaunchKernelGGL(decode_phase_kernel<MB>, dim3(static_cast<unsigned>(p.NTp[p.q] * p.splits)), dim3(kThreads), smem,
-                     stream, p);
+  hipLaunchKernelGGL((decode_phase_kernel<MB, NB>), dim3(static_cast<unsigned>(p.NTp[p.q] * p.splits)), dim3(kThreads),
+                     smem, stream, p);
   return hipGetLastError();
+}
+template <int MB>
+hipError_t launch_mb(const DecodePhase& p, hipStream_t stream) {
+  if (p.cols == kDecodePhaseN) return launch_nb<MB, kWide>(p, stream);
+  if (p.cols == kDecodeNarrowN && p.splits == 1) return launch_nb<MB, kNarrow>(p, stream);
+  return hipErrorInvalidValue;
 }
 
 // Most slices a column tile can need: the support of output group j over the
@@ -377,6 +394,19 @@ int64_t most_slices(int law, int q, const I* S, int64_t M) {
 }
 
 }  // namespace
+
+// 16 columns where a tile has at most 32 slices (eight a wave) and the tiles
+// are no more than the chip's CUs.  Measured with 40 layers, star law, q = 4,
+// 16 against 64 columns, us a projection: 128 <-> 256, 64 rows, 8.8 and 10.8;
+// 256 <-> 512, 17 rows 9.0 and 10.4, 64 rows 9.5 and 12.1; 768 <-> 3072, 64
+// rows, 14.8 and 16.1; 1024 <-> 4096 (the limit of both), 64 rows, 16.3 and
+// 17.9.  Up to 16 rows a thread of the wide tiles finishes one block as well,
+// and 64 columns are level or faster.
+int decode_phase_cols(int law, int q, const int64_t* S, const int64_t* R, int64_t M) {
+  int64_t tiles = 0;
+  for (int g = 0; g < q; ++g) tiles += (R[g + 1] - R[g] + kDecodeNarrowN - 1) / kDecodeNarrowN;
+  return M > 16 && most_slices(law, q, S, M) <= 32 && tiles <= 256 ? kDecodeNarrowN : kDecodePhaseN;
+}
 
 // One workgroup per CU (256), of at least 16 slices (four a wave).  Measured
 // on 2560 <-> 9728, 8 rows of 4 types: 256 workgroups 15.5 to 19.8 us a

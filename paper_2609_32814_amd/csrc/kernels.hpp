@@ -157,12 +157,13 @@ constexpr int kTileM = 256;
 
 constexpr int kDecodeMaxRows = 64;  // rows per step (one new token per sequence)
 constexpr int kDecodeTileN = 16;    // output columns per workgroup of the persistent stack
-constexpr int kDecodePhaseN = 64;   // output columns per workgroup of one projection's launch
+constexpr int kDecodePhaseN = 64;   // output columns per workgroup of one projection's launch ...
+constexpr int kDecodeNarrowN = 16;  // ... and of a small projection's
 constexpr int kDecodeSliceK = 32;   // K rows per streamed slice
 constexpr int kDecodeMaxK = 32768;  // input width of either projection (one-launch-per-projection path)
 
 // One projection of one decode step: out = epilogue(A *_q W + bias) over M
-// rows, a workgroup per kDecodePhaseN output columns and K split.
+// rows, a workgroup per `cols` output columns and K split.
 struct DecodePhase {
   int32_t q;
   int32_t law;
@@ -186,7 +187,8 @@ struct DecodePhase {
   void* Y;                // down, last layer: final output, or null
   int32_t ydtype;
   uint64_t adj[kMaxQGroups];  // law 3: bit j of adj[i] marks the edge i -> j
-  int32_t splits;             // shares of the K slices
+  int32_t cols;               // kDecodePhaseN or kDecodeNarrowN; NTp counts tiles of that width
+  int32_t splits;             // shares of the K slices (1 with kDecodeNarrowN)
   uint64_t* part;             // splits > 1: decode_phase_part_bytes of partial sums
   int32_t* cnt;               // splits > 1: arrivals per column tile, zero at launch and at the end
   int32_t* status;            // or null: kCounterStride words set to zero
@@ -241,8 +243,10 @@ bool decode_stack_resident(int M, int kmax, int D, int ns, bool gated, int nt_up
 // device not held by other work); p.cnt must be zero.
 hipError_t launch_decode_stack(const DecodeStack& p, int grid, hipStream_t stream);
 
-// The K splits a projection of M rows runs best with (`tiles` column tiles,
-// S its q + 1 input group starts), and the bytes of their partial sums.
+// The tile width a projection of M rows runs best with (S and R its q + 1
+// input and output group starts), the K splits (with `tiles` column tiles of
+// kDecodePhaseN), and the bytes of their partial sums.
+int decode_phase_cols(int law, int q, const int64_t* S, const int64_t* R, int64_t M);
 int decode_phase_splits(int law, int q, const int64_t* S, int32_t tiles, int64_t M);
 size_t decode_phase_part_bytes(int32_t tiles, int splits, int64_t M);
 hipError_t launch_decode_phase(const DecodePhase& p, hipStream_t stream);

@@ -799,6 +799,44 @@ def test_decode_split_projections(P, M, law):
         P.star_decode(*args, ws=torch.empty(smallest - 256, dtype=torch.uint8, device="cuda"))
 
 
+@pytest.mark.parametrize("law,s,r,M", [
+    ("star", [72, 64, 24, 96], [136, 8, 200, 168], 17),    # 16-column tiles with remainders, slices across groups
+    ("dense", [72, 64, 24, 96], [136, 8, 200, 168], 48),
+    ("tensor2", [72, 64, 24, 96], [136, 8, 200, 168], 64),
+    ("star", [256] * 4, [1024] * 4, 33),                   # 32 slices and 256 tiles up, 64-column tiles down
+    ("dense", [264, 256, 256, 256], [128] * 4, 33),        # 33 slices up (64 columns), 16-column tiles down
+    ("star", [72, 64, 24, 96], [136, 8, 200, 168], 16),    # 16 rows: 64 columns
+])
+def test_decode_small_projections(P, law, s, r, M):
+    """More layers than the persistent stack holds, projections around the
+    limits of the 16-column tiles.  The 33 layers take two sets of weights in
+    turn; their errors add up like the layers' own contributions, so the bar
+    stays that of one layer."""
+    import torch
+    up_g, up_o = algs(P, 4, s, r, law)
+    dn_g, dn_o = algs(P, 4, r, s, law)
+    D, F, L = up_o.K, up_o.N, 33
+    Wu = [synth.gaussian(1720 + l, 0, (D, F), 0.02, "bf16") for l in (0, 1)]
+    Wd = [synth.gaussian(1720 + l, 1, (F, D), 0.02, "bf16") for l in (0, 1)]
+    bu = [synth.gaussian(1720 + l, 2, (F,), 0.02, "f32") for l in (0, 1)]
+    bd = [synth.gaussian(1720 + l, 3, (D,), 0.02, "f32") for l in (0, 1)]
+    X = synth.gaussian(1722, M, (M, D), 1.0, "bf16")
+    t = (synth.decode_positions(1723, M) % 4).astype(np.int32)
+    t[M // 2] = 4  # no valid type
+    ok = t < 4
+
+    def layers(x):
+        return [x[l % 2] for l in range(L)]
+
+    ref = oracle.decode_stack(up_o, dn_o, t[ok], X.exact[ok], layers([w.exact for w in Wu]),
+                              layers([b.exact for b in bu]), layers([w.exact for w in Wd]),
+                              layers([b.exact for b in bd]))
+    Y = P.star_decode(up_g, dn_g, types_dev(t), to_dev(X), layers([to_dev(w) for w in Wu]),
+                      layers([f32_dev(b.exact) for b in bu]), layers([to_dev(w) for w in Wd]),
+                      layers([f32_dev(b.exact) for b in bd]), "gelu", True, out_dtype=torch.float32)
+    assert rel_fro(to_host(Y)[ok], ref) <= TOL_BF16
+
+
 @pytest.mark.parametrize("M", [1, 16])
 @pytest.mark.parametrize("D,F", [(1024, 8192), (6144, 2048)])
 def test_decode_wider_than_4096(P, M, D, F):
