@@ -171,8 +171,15 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
+# (torch's own way to the raw stream, without the Stream object; it is not a
+# public name, so a torch without it takes the public way)
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(device) -> int:
-    return torch._C._cuda_getCurrentRawStream(device.index)
+    if _raw_stream is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return _raw_stream(device.index)
 
 
 def _check(status: int, where: str):

@@ -418,3 +418,20 @@ def test_tile_shape_refuses_what_the_calls_refuse(P):
 def test_weight_gradient_ranges(P, law, q, K, N, M, shape):
     """The number of row ranges at shapes timed with 1 to 16 (us at the side)."""
     assert P.star_tile_shape("bwd_weight", P.Algebra.equal(q, K, N, law), M) == shape
+
+
+def test_stream_without_the_private_torch_call(monkeypatch):
+    """The raw stream comes from a private torch call where there is one and
+    from the public one where not: the same stream either way."""
+    import torch
+    from paper_2609_32814_amd import binding
+
+    class Stream:
+        cuda_stream = 0x1234
+
+    dev = torch.device("cuda", 1)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda d: Stream() if d == dev else None)
+    monkeypatch.setattr(binding, "_raw_stream", None)
+    assert binding._stream(dev) == 0x1234
+    monkeypatch.setattr(binding, "_raw_stream", lambda i: 0x1000 + i)
+    assert binding._stream(dev) == 0x1001
