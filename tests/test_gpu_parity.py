@@ -472,18 +472,21 @@ def test_bwd_weight_splits_per_pass(P, law, s, r):
 
 
 @pytest.mark.parametrize("law,s,r,M", [
-    ("star", [384, 384], [512, 264], 701),       # 128 x 192 (activation gradient)
-    ("dense", [520, 256], [512, 264], 701),      # 128 x 256
+    ("star", [384, 384], [512, 264], 701),
+    ("dense", [520, 256], [512, 264], 701),
     ("tensor2", [192, 384, 200, 192], [256, 64, 72, 128], 1031),
     ("star", [520, 512], [1536, 1544], 1601),    # the forward too
     ("dense", [384, 776], [1152, 392], 1601),
 ])
 def test_128_row_tiles(P, law, s, r, M):
-    """The tiles of 128 rows that forward and activation gradient take where
-    256-row ones leave CUs without a tile: ragged rows, groups, K steps."""
+    """The 128 x 192 tiles that activation gradients (and the star law's wide
+    forward) take where 256-row ones leave CUs without a tile, next to the
+    small forward tiles of the same layers: ragged rows, groups, K steps.
+    The other shapes: TILE_SHAPES below."""
     import torch
     q = len(s)
     ga, oa = algs(P, q, s, r, law)
+    assert P.star_tile_shape("bwd_data", ga, M)[:2] == (128, 192)
     X = synth.gaussian(495, 0, (M, oa.K), 1.0, "bf16")
     W = synth.gaussian(495, 1, (oa.K, oa.N), 0.05, "bf16")
     dY = synth.gaussian(495, 2, (M, oa.N), 1.0, "bf16")
@@ -499,6 +502,89 @@ def test_128_row_tiles(P, law, s, r, M):
                                   act_prev=act, out_dtype=torch.float32)
         ref = oracle.proj_bwd_data(oa, t, dY.exact, W.exact, Zprev=None if act == "none" else Zp.exact, act_prev=act)
         assert rel_fro(to_host(dX), ref) <= TOL_BF16
+
+
+# Every tile shape that is built, per law: the smallest layers found whose
+# forward or whose activation gradient takes it, with remainders of rows,
+# columns and K steps.  Each test asserts the choice, so a rule that is tuned
+# anew cannot leave a shape untested unnoticed.
+FWD_TILE_SHAPES = [
+    ("dense", (128, 192), [96, 64], [384, 384], 6109),
+    ("dense", (128, 256), [64, 64], [448, 448], 6515),
+    ("dense", (256, 192), [72, 64], [120, 1048], 6507),
+    ("dense", (256, 256), [64, 80, 144], [448, 384, 392], 6069),
+    ("dense", (64, 128), [96, 72], [64, 96], 413),
+    ("star", (128, 192), [128, 96], [304, 312], 5935),
+    ("star", (128, 256), [80, 112], [448, 384], 7097),
+    ("star", (256, 192), [144, 64], [328, 544], 8867),
+    ("star", (256, 256), [64, 168], [512, 504], 8489),
+    ("star", (64, 128), [112, 80], [112, 64], 681),
+    ("tensor2", (128, 192), [88, 104], [392, 384], 5865),
+    ("tensor2", (128, 256), [96, 88], [448, 448], 6307),
+    ("tensor2", (256, 192), [96, 64], [728, 784], 4681),
+    ("tensor2", (256, 256), [80, 120], [1112, 488], 7661),
+    ("tensor2", (64, 128), [176, 64], [240, 104], 335),
+    ("graph", (256, 256), [80, 120], [1112, 488], 7661),
+    ("graph", (64, 128), [176, 64], [240, 104], 335),
+]
+BWD_TILE_SHAPES = [
+    ("dense", (128, 192), [96, 72], [64, 96], 413),
+    ("dense", (128, 256), [104, 256], [72, 72], 309),
+    ("dense", (256, 192), [296, 320], [80, 136], 8357),
+    ("dense", (256, 256), [512, 504], [104, 136], 8261),
+    ("star", (128, 192), [112, 80], [112, 64], 681),
+    ("star", (128, 256), [152, 240], [64, 120], 351),
+    ("star", (256, 192), [280, 264], [96, 144], 8305),
+    ("star", (256, 256), [632, 440], [64, 136], 7245),
+    ("tensor2", (128, 192), [176, 64], [240, 104], 335),
+    ("tensor2", (128, 256), [192, 200], [136, 96], 327),
+    ("tensor2", (256, 192), [296, 304], [64, 144], 8973),
+    ("tensor2", (256, 256), [512, 512], [64, 88], 8517),
+    ("graph", (256, 256), [176, 64], [240, 104], 335),
+]
+
+
+def _tile_shape_algs(P, law, s, r):
+    q = len(s)
+    edges = [[int(i != j and (i + j) % 2) for j in range(q)] for i in range(q)] if law == "graph" else None
+    return P.Algebra(q, s, r, law, edges), oracle.Alg(q, tuple(s), tuple(r), law, edges)
+
+
+@pytest.mark.parametrize("law,tiles,s,r,M", FWD_TILE_SHAPES)
+def test_forward_on_every_tile_shape(P, law, tiles, s, r, M):
+    import torch
+    ga, oa = _tile_shape_algs(P, law, s, r)
+    assert P.star_tile_shape("fwd", ga, M, "gelu")[:2] == tiles
+    X = synth.gaussian(497, 0, (M, oa.K), 1.0, "bf16")
+    W = synth.gaussian(497, 1, (oa.K, oa.N), 0.05, "bf16")
+    b = synth.gaussian(497, 2, (oa.N,), 0.5, "f32")
+    t = np.random.default_rng(497).integers(0, len(s), M).astype(np.int32)
+    Y, Z = P.star_proj_fwd(ga, types_dev(t), to_dev(X), to_dev(W), f32_dev(b.exact), "gelu", Z_out=True,
+                           out_dtype=torch.float32)
+    rY, rZ, _, _ = oracle.proj_fwd(oa, t, X.exact, W.exact, b.exact, "gelu", want_z=True)
+    assert rel_fro(to_host(Y), rY) <= TOL_BF16 and rel_fro(to_host(Z), rZ) <= TOL_BF16
+
+
+@pytest.mark.parametrize("law,tiles,s,r,M", BWD_TILE_SHAPES)
+def test_activation_gradient_on_every_tile_shape(P, law, tiles, s, r, M):
+    """Plain, with a fused GELU', and two products in one."""
+    import torch
+    ga, oa = _tile_shape_algs(P, law, s, r)
+    d1, d2 = (synth.gaussian(500, k, (M, oa.N), 1.0, "bf16") for k in (0, 1))
+    W1, W2 = (synth.gaussian(500, k, (oa.K, oa.N), 0.05, "bf16") for k in (2, 3))
+    Zp = synth.gaussian(500, 4, (M, oa.K), 1.0, "bf16")
+    t = np.random.default_rng(500).integers(0, len(s), M).astype(np.int32)
+    plan = P.star_type_plan(len(s), types_dev(t))
+    plain = oracle.proj_bwd_data(oa, t, d1.exact, W1.exact)
+    for act in ("none", "gelu"):
+        assert P.star_tile_shape("bwd_data", ga, M, act)[:2] == tiles
+        dX = P.star_proj_bwd_data_planned(ga, plan, to_dev(d1), to_dev(W1), Z_prev=None if act == "none" else to_dev(Zp),
+                                          act_prev=act, out_dtype=torch.float32)
+        ref = plain if act == "none" else oracle.proj_bwd_data(oa, t, d1.exact, W1.exact, Zprev=Zp.exact, act_prev=act)
+        assert rel_fro(to_host(dX), ref) <= TOL_BF16
+    dX = P.star_proj_bwd_data_pair_planned(ga, plan, to_dev(d1), to_dev(W1), to_dev(d2), to_dev(W2),
+                                           out_dtype=torch.float32)
+    assert rel_fro(to_host(dX), plain + oracle.proj_bwd_data(oa, t, d2.exact, W2.exact)) <= TOL_BF16
 
 
 @pytest.mark.parametrize("law", ["star", "dense", "tensor2", "graph"])
@@ -520,6 +606,28 @@ def test_bwd_data_pair(P, law, s, r, M):
     for out in (torch.float32, torch.bfloat16):
         dX = P.star_proj_bwd_data_pair_planned(ga, plan, to_dev(d1), to_dev(W1), to_dev(d2), to_dev(W2), out_dtype=out)
         assert dX.dtype == out and rel_fro(to_host(dX), ref) <= TOL_BF16
+
+
+@pytest.mark.parametrize("law,shape,s,r,M", [
+    ("dense", (192, 256, 2), [120, 88], [208, 96], 2309),
+    ("dense", (256, 192, 4), [64, 64], [144, 72], 4387),
+    ("dense", (256, 256, 2), [96, 200], [152, 224], 2623),
+    ("star", (192, 256, 2), [128, 112], [120, 208], 2405),
+    ("star", (256, 192, 2), [80, 64], [128, 160], 2273),
+    ("star", (256, 256, 1), [200, 200], [216, 80], 309),
+    ("tensor2", (192, 256, 2), [80, 64], [256, 264], 2297),
+    ("tensor2", (256, 192, 2), [96, 80], [152, 80], 2383),
+    ("tensor2", (256, 256, 2), [128, 224], [80, 200], 2227),
+])
+def test_weight_gradient_on_every_tile_shape(P, law, shape, s, r, M):
+    ga, oa = algs(P, len(s), s, r, law)
+    assert P.star_tile_shape("bwd_weight", ga, M)[:3] == shape
+    X = synth.gaussian(501, 0, (M, oa.K), 1.0, "bf16")
+    dY = synth.gaussian(501, 1, (M, oa.N), 1.0, "bf16")
+    t = np.random.default_rng(501).integers(0, len(s), M).astype(np.int32)
+    dW, db = P.star_proj_bwd_weight(ga, types_dev(t), to_dev(X), to_dev(dY))
+    rW, rb = oracle.proj_bwd_weight(oa, t, X.exact, dY.exact)
+    assert rel_fro(to_host(dW), rW) <= TOL_BF16 and rel_fro(to_host(db), rb) <= TOL_BF16
 
 
 @pytest.mark.parametrize("r", [[384, 392], [1024, 1032]])
