@@ -238,7 +238,12 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     const int ps = v < pcount[0] ? 0 : 1;
     const int32_t logical = pbase[ps] + (ps == 0 ? v : v - pcount[0]);
     const int32_t* pf = pfx_s[ps == 0 ? 0 : p1];
-    const int cls = last_start(pf, q, logical);
+    int cls = 0;
+    if constexpr (LAW == 2) {
+      while (logical >= pf[cls + 1]) ++cls;
+    } else {
+      cls = last_start(pf, q, logical);
+    }
     const bool hh = ps == 1 && half1;
     const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
     t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
