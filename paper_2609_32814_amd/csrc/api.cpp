@@ -123,18 +123,21 @@ PlanWs plan_layout(int64_t M, int q, size_t base = 0) {
 
 int tiles_of(int64_t w, int tile) { return static_cast<int>((w + tile - 1) / tile); }
 
-// Column-tile width of the weight-gradient GEMM: 128 columns (the
-// contraction is over rows, the output K x N is small).
-constexpr int kBwdWeightNW = 2;
-
+// Row ranges of the weight gradient with fp32 operands: counted in blocks of
+// 256 x 128, about one per CU of a 256-CU device, with at least 1024 rows a
+// range.  That was the tile of an earlier kernel; the present one's are 64 x
+// 64, three workgroups to a CU, and one count serves both passes.  A count of
+// its own has not been measured yet, so this one stays, with which 100
+// products took 0.09 to 0.77 of that kernel's time; it makes more partial
+// sums than the small tiles need (4096 x 768 x 2304, q = 3: four ranges where
+// 432 tiles already cover the CUs).
 int bwd_weight_nsplit(const Alg& a, int64_t M) {
   int64_t mt = 0, nt = 0;
   for (int g = 0; g < a.q; ++g) {
-    mt += tiles_of(a.s(g), kTileM);
-    nt += tiles_of(a.r(g), 64 * kBwdWeightNW);
+    mt += tiles_of(a.s(g), 256);
+    nt += tiles_of(a.r(g), 128);
   }
   const int64_t base = mt * nt;
-  // about one tile per CU of a 256-CU device, rows per split >= 1024
   int64_t ns = (256 + base - 1) / base;
   ns = std::min<int64_t>(ns, 8);
   ns = std::min<int64_t>(ns, std::max<int64_t>(1, M / 1024));
@@ -675,10 +678,9 @@ void fill_tiles(int32_t* pfx, const T* G, int q, int tile) {
 
 star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_ERR_HIP; }
 
-// bf16 operands take the kernel fed by direct global-to-LDS copies (its
-// column tiles are wider, so the tile counts are redone for it); fp32
-// operands the register-staged one.  `upper` bounds the number of tiles of
-// the register-staged kernel.
+// fp32 operands take a kernel of their own, which picks its tiles (launch_gemm);
+// bf16 operands the pipelined kernel, on the tiles async_tiles gives, or in
+// the forward the small-tile kernel.
 // The forward takes the small-tile kernel (64 rows x 128 columns) when the
 // wide kernel's tiles (256 x 256, or 256 x 192 where async_tiles takes
 // those) would be at most three quarters full (rows taken as spread evenly
@@ -686,14 +688,15 @@ star_status hip_status(hipError_t e) { return e == hipSuccess ? STAR_OK : STAR_E
 // too few to fill the chip (128 of 256 rows, or 192 of 128 rows: 2048 rows,
 // q = 2, 768 -> 3072 has 96 and 192, 21 us on the latter and 24 on the small
 // tiles; 4096 rows, 3072 -> 768 has 64 and 128, 55 and 48 us), and when an
-// input group is narrower than 64 (a 64-wide K step would span groups).  The bar was set by timing both kernels
-// on the projection shapes of the paper's kernel study (M = 512, 2048, 8192;
-// q = 4 to 64); from 200 tiles on, 128-row tiles filled to 0.6 are enough
-// (the small tiles run at half the rate: 13013 x 1792 -> 3584, q = 16, 120
-// against 82 us; 12544 x 1728 -> 576, tensor law, 92 against 54).  The fill is that of the tiles that would run: groups 384
+// input group is narrower than 64 (a 64-wide K step would span groups).  The
+// bar was set by timing both kernels on the projection shapes of the paper's
+// kernel study (M = 512, 2048, 8192; q = 4 to 64); from 200 tiles on, 128-row
+// tiles filled to 0.6 are enough (the small tiles run at half the rate: 13013
+// x 1792 -> 3584, q = 16, 120 against 82 us; 12544 x 1728 -> 576, tensor law,
+// 92 against 54).  The fill is that of the tiles that would run: groups 384
 // wide fill 192-wide tiles, and judged by 256-wide ones 16384 x 768 -> 1536
-// took the small tiles (star, q = 4: 47.6 against 34.6 us; tensor law
-// 1536 -> 768: 77.5 against 54.5 us).
+// took the small tiles (star, q = 4: 47.6 against 34.6 us; tensor law 1536 ->
+// 768: 77.5 against 54.5 us).
 std::atomic<int> g_fwd_tiles{STAR_TILES_AUTO};
 
 constexpr TileShape kSmallTiles{64, 128};

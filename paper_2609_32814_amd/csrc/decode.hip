@@ -408,7 +408,10 @@ int decode_phase_cols(int law, int q, const int64_t* S, const int64_t* R, int64_
   return M > 16 && most_slices(law, q, S, M) <= 32 && tiles <= 256 ? kDecodeNarrowN : kDecodePhaseN;
 }
 
-// One workgroup per CU (256), of at least 16 slices (four a wave).  Measured
+// At most one workgroup per CU (256 / tiles, rounded down: with 129 to 255
+// column tiles every tile has one split and the other CUs none, as the up
+// projection of 2560 -> 9728 with its 152), of at least 16 slices (four a
+// wave; 1024 <-> 4096 up to 16 rows stops at 128 workgroups by this).  Measured
 // on 2560 <-> 9728, 8 rows of 4 types: 256 workgroups 15.5 to 19.8 us a
 // projection, 512 (two per CU) 20.1, 768 23.0; 64 rows: 28.3, 34.2, 41.4 (a
 // workgroup's start, its hand-over of partial sums and its arrival cost

@@ -34,11 +34,12 @@
 // tile: small tiles, three workgroups per CU, and operands copied ahead.
 // Against 256 x 128 tiles staged through registers by one workgroup per CU
 // (1111 rows of three types, 768 <-> 2304: 40 to 100 workgroups on the
-// chip): forward 162 and 386 -> 33 us, activation gradients 192 and 460 ->
-// 52 us, weight gradients 416 -> 43 us each.  128 x 128 tiles of the same
-// kernel: 10 % faster on 4096 x 1024 x 4096 (311 against 351 us), three
-// times slower where the long contractions are few (172 against 52 us), so
-// they are not built.
+// chip): forward 162 and 386 -> 37 and 47 us, activation gradients 192 and
+// 460 -> 34 and 55 us, weight gradients 416 -> 44 us each.  128 x 128 tiles
+// of the same kernel: 10 % faster on 4096 x 1024 x 4096 (311 against 351 us),
+// three times slower where the long contractions are few (172 against 52 us),
+// so they are not built; dense forwards that filled the chip with 256 x 128
+// tiles exactly are the one loss (2048 x 4096 x 4096, 597 -> 612 us).
 //
 // Operands go from global memory straight into LDS (16 bytes per lane, 1 KB
 // per copy instruction) in steps of 32 K elements, two steps ahead of the

@@ -8,11 +8,12 @@
 // swapped-operand v_mfma_f32_32x32x16_bf16 so a lane ends with 4 consecutive
 // output columns).  Two passes of tiles (two-segment contractions first),
 // dealt out per XCD as one list (the second pass in tiles of 128 rows when
-// whole tiles would leave the load uneven); the epilogue follows the
-// register-staged kernel.  Weight gradient: C = X^T dY over the type-sorted positions of the
-// rows whose support pairs the tile's groups, rows read in place through
-// perm (the rows of each stage's 64 positions are copied into LDS one stage
-// ahead), split along the positions into deterministic partials.
+// whole tiles would leave the load uneven); the accumulators start from the
+// bias, and the epilogue applies the activation or its derivative to them.
+// Weight gradient: C = X^T dY over the type-sorted positions of the rows whose
+// support pairs the tile's groups, rows read in place through perm (the rows
+// of each stage's 64 positions are copied into LDS one stage ahead), split
+// along the positions into deterministic partials.
 //
 // Operands go from global memory straight into LDS with
 // global_load_lds_dwordx4 (16 bytes per lane, 1 KB per wavefront
