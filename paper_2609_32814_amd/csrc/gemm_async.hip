@@ -70,6 +70,11 @@ constexpr int SMEM = 2 * STAGE_BYTES;           // 128 KB
 constexpr int DMA_A = A_BYTES / 1024 / kWaves;  // A copies per wave per stage (4)
 constexpr int DMA_B = B_BYTES / 1024 / kWaves;  // B copies per wave per stage (4)
 constexpr int kRowBufs = 4;                     // row-index / bias buffers
+#ifdef STARQ_MANY_TYPES
+constexpr bool kMany = true;  // tiles look their class and column group up by ballots
+#else
+constexpr bool kMany = false;  // ... by a walk
+#endif
 
 typedef short v4i16_t __attribute__((ext_vector_type(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -148,6 +153,7 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
   // row tiles x splits of pass 0 and of pass 1)
   __shared__ int32_t units_s[2][kMaxQGroups];
   __shared__ int32_t offs_s[kMaxQGroups + 1];
+  __shared__ int32_t ntp_s[kMany ? kMaxQGroups : 1];  // p.NTp[i + 1]
   // tile prefix sums per class: pass 0, pass 1, pass 1 in half-height tiles
   __shared__ int32_t pfx_s[3][kMaxQGroups + 1];
   __shared__ __attribute__((aligned(16))) int32_t rows_s[kRowBufs][BM];
@@ -185,6 +191,9 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     int32_t run = 0;
     for (int i = 0; i < q; ++i) {
       pfx_s[threadIdx.x][i] = run;
+      if constexpr (kMany) {
+        if (threadIdx.x == 0) ntp_s[i] = p.NTp[i + 1];
+      }
       run += units_s[threadIdx.x == 2 || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0][i] * ncols_sel(p, sel, i);
     }
     pfx_s[threadIdx.x][q] = run;
@@ -240,15 +249,19 @@ __global__ __launch_bounds__(kThreads, 1) void star_gemm_async_kernel(const Gemm
     const int32_t logical = pbase[ps] + (ps == 0 ? v : v - pcount[0]);
     const int32_t* pf = pfx_s[ps == 0 ? 0 : p1];
     int cls = 0;
-    if constexpr (LAW == 2) {
-      while (logical >= pf[cls + 1]) ++cls;
+    if constexpr (kMany) {
+      cls = group_at(pf[min(lane + 1, q)], q, logical);
     } else {
-      cls = last_start(pf, q, logical);
+      while (logical >= pf[cls + 1]) ++cls;
     }
     const bool hh = ps == 1 && half1;
     const int un = hh || (MODE == kModeBwdWeight && ps == 1) ? 1 : 0;
-    t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, logical - pf[cls],
-                                     units_s[un][cls], offs_s, hh ? TM / 2 : TM);
+    const int32_t u = logical - pf[cls], bm = hh ? TM / 2 : TM;
+    if constexpr (kMany)
+      t = make_tile<MODE, LAW, TN, BK, true>(p, sel_for(MODE, LAW, ps), cls, u, units_s[un][cls], offs_s, bm,
+                                             ntp_s[lane]);
+    else
+      t = make_tile<MODE, LAW, TN, BK>(p, sel_for(MODE, LAW, ps), cls, u, units_s[un][cls], offs_s, bm);
     if constexpr (PAIR) t.nsteps *= 2;
     return true;
   };
@@ -825,15 +838,30 @@ hipError_t launch_act(const GemmParams& p, int64_t upper, int cus, hipStream_t s
 template <int MODE>
 hipError_t launch_async(const GemmParams& p, int64_t upper, int cus, hipStream_t stream) {
   if (p.law == 3) return launch_act<MODE, 3>(p, upper, cus, stream);
-  if (p.law == 2) return launch_act<MODE, 2>(p, upper, cus, stream);
-  return p.law == 1 ? launch_act<MODE, 1>(p, upper, cus, stream)
-                    : launch_act<MODE, 0>(p, upper, cus, stream);
+  if constexpr (!kMany) {
+    if (p.law == 2) return launch_act<MODE, 2>(p, upper, cus, stream);
+    if (p.law == 1) return launch_act<MODE, 1>(p, upper, cus, stream);
+  }
+  return launch_act<MODE, 0>(p, upper, cus, stream);
 }
 
 }  // namespace
 
+#ifdef STARQ_MANY_TYPES
+hipError_t launch_gemm_async_many(int mode, const GemmParams& p, int64_t upper_tiles, int cus,
+                                  hipStream_t stream) {
+  if (p.law != 0 && p.law != 3) return hipErrorInvalidValue;
+#else
+// From 17 types on, the star and graph laws run the build of
+// gemm_async_many.hip.  At 16 it is faster where tiles are short (activation
+// gradient, 12544 rows, 1664 <- 512: 34 -> 28 us) and slower where they are
+// long and few (2048 rows, 768 <- 3072: 46.6 -> 48.0; 512 rows 41.8 -> 44.5).
+constexpr int kFewTypes = 16;
+
 hipError_t launch_gemm_async(int mode, const GemmParams& p, int64_t upper_tiles, int cus,
                              hipStream_t stream) {
+  if (p.q > kFewTypes && (p.law == 0 || p.law == 3)) return launch_gemm_async_many(mode, p, upper_tiles, cus, stream);
+#endif
   if (mode == kModeFwd) return launch_async<kModeFwd>(p, upper_tiles, cus, stream);
   if (mode == kModeBwdWeight) return launch_async<kModeBwdWeight>(p, upper_tiles, cus, stream);
   return launch_async<kModeBwdData>(p, upper_tiles, cus, stream);

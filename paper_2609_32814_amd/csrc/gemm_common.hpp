@@ -226,29 +226,21 @@ struct Tile {
   int32_t do_dbias;
 };
 
-// The last i < q with start[i] <= x (start[0] <= x), by halving: a walk from
-// group to group, for the class and the column group of every tile, took a
-// 64-type tile of one K step about 10 us.  The tensor law has at most four
-// groups and keeps the walk, in the same words as ever: its kernels' registers
-// follow them (weight gradient of 16384 rows, 768 x 1536: 61.6 us, 63.7 by
-// halving, 64.5 by a walk with one more test).  So does the fp32 kernel (64
-// columns a tile), whose workgroups look up one tile each.
-__device__ __forceinline__ int last_start(const int32_t* start, int q, int32_t x) {
-  int lo = 0, hi = q - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (x >= start[mid]) lo = mid;
-    else hi = mid - 1;
-  }
-  return lo;
+// The i < q with start(i) <= x < start(i + 1), where the lane holds `next` =
+// start(lane + 1) of a rising sequence (any value in lanes from q on): one
+// bound a lane and a ballot.  Every lane of the wave takes part, with the
+// same x.
+__device__ __forceinline__ int group_at(int32_t next, int q, int32_t x) {
+  return __popcll(__ballot(static_cast<int>(threadIdx.x & 63) < q && next <= x));
 }
 
 // `offs` holds the q + 1 type offsets of the plan (global memory or an LDS
 // copy).  Forward and activation gradient: row tiles are `bm` rows (BM, or
-// BM / 2 for the half-height tiles that balance a short last round).
-template <int MODE, int LAW, int BN, int BK>
-__device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls, int32_t u,
-                                          int32_t units, const int32_t* offs, int bm = BM) {
+// BM / 2 for the half-height tiles that balance a short last round).  MANY:
+// the column group by group_at, with ntp_next the lane's p.NTp[lane + 1].
+template <int MODE, int LAW, int BN, int BK, bool MANY = false>
+__device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls, int32_t u, int32_t units,
+                                          const int32_t* offs, int bm = BM, int32_t ntp_next = 0) {
   Tile t;
   const int32_t nsplit = pass_of(MODE, sel) == 0 ? p.nsplit : p.nsplit1;
   // Forward and activation gradient: column tiles vary fastest, so that the
@@ -266,10 +258,10 @@ __device__ __forceinline__ Tile make_tile(const GemmParams& p, int sel, int cls,
   }
   const int ct = col_tile_global(p, sel, cls, cidx);
   int cg = 0;
-  if constexpr (LAW == 2 || BN == 64) {
-    while (cg + 1 < p.q && ct >= p.NTp[cg + 1]) ++cg;
+  if constexpr (MANY) {
+    cg = group_at(ntp_next, p.q, ct);
   } else {
-    cg = last_start(p.NTp, p.q, ct);
+    while (cg + 1 < p.q && ct >= p.NTp[cg + 1]) ++cg;
   }
   const int nt = ct - p.NTp[cg];
   t.cls = cls;

@@ -98,6 +98,9 @@ hipError_t launch_column_sum_f32(const float* src, int32_t N, const int32_t* per
 hipError_t launch_graph_fill(int mode, const GemmParams& p, hipStream_t stream);
 hipError_t launch_gemm_async(int mode, const GemmParams& p, int64_t upper_tiles, int cus,
                              hipStream_t stream);
+// its build for many row types (star and graph laws), which it calls itself
+hipError_t launch_gemm_async_many(int mode, const GemmParams& p, int64_t upper_tiles, int cus,
+                                  hipStream_t stream);
 // Small-tile forward (gemm_narrow.hip): tiles of 64 rows of one type x
 // gemm_narrow_cols() columns of one output group; p.NTp counts column tiles
 // of that width; n_rb bounds the row blocks over all types.
