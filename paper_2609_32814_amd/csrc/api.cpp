@@ -157,11 +157,12 @@ int64_t col_tiles(const Alg& a, bool over_r, int tn) {
 // rows taken as spread evenly over the types, as the host does not read the
 // per-type counts) the way the kernel does on 256 CUs: an eighth of each pass
 // per XCD, in snake order over the XCD's 32 workgroups.  Rates, fixed part
-// and margin below are set from 600 products timed on all four shapes (64 to
-// 20000 rows, q = 1 to 64, widths 256 to 6144, types cyclic and in runs): none
-// of them is more than 2 % slower than with 256-row tiles alone, and the
-// mean gain over those is 9 %.  (The kernel's half-height second pass is not
-// in the estimate.)
+// and margin below are set from 611 products timed on all four shapes (64 to
+// 20000 rows, q = 1 to 64, widths 256 to 6144, types cyclic and in runs):
+// six activation gradients of 65 to 128 rows a type are 3 to 9 % slower than
+// with 256-row tiles alone (below), no other by more than 2 %, and the mean
+// is 9 % faster.  (The kernel's half-height second pass is not in the
+// estimate.)
 //
 // The estimate runs at every launch, so it takes runs of equal tiles and not
 // single ones, and allocates nothing (an entry point that runs out of memory
@@ -310,11 +311,11 @@ int64_t padded_cols(const Alg& a, bool over_r, int tn) { return col_tiles(a, ove
 // 256 rows stay faster (80 and 85 us).  Where tiles are short, the part that
 // every tile costs decides for the larger ones: 15279 rows, q = 16, 512 ->
 // 512, activation gradient, 25 us on 256 x 192 and 28 on 128 x 192; 16384
-// rows, q = 64, 512 -> 3072, 114 and 125.  A 256 x 192 tile of 65 to 128 rows
-// runs like a 128 x 192 one in the activation gradient (half of its waves
-// skip their products, the others have twice as many to hide the copies
-// behind): 512 rows, dense, q = 4, 768 <- 3072, 42 and 45 us; of 64 rows or
-// fewer it takes a sixth longer.
+// rows, q = 64, 512 -> 3072, 114 and 125.   A 256 x 192
+// tile of 65 to 128 rows runs like a 128 x 192 one in the activation gradient
+// (half of its waves skip their products; 512 rows of four types alike, dense,
+// 768 <- 3072, 42 and 45 us), but the host does not know the counts, and with
+// 256 rows in two of the four types it takes 58 us and 128 x 192 tiles 44.
 struct TileShape {
   int tm, tn;
 };
@@ -323,17 +324,16 @@ TileShape async_tiles(const Alg& a, int mode, int64_t M, bool act) {
   const bool over_r = mode != kModeBwdData;
   const int64_t pad192 = padded_cols(a, over_r, 192), pad256 = padded_cols(a, over_r, 256);
   const bool try192 = pad192 < pad256 || (pad192 == pad256 && a.law == STAR_LAW_STAR && mode == kModeFwd);
-  const int64_t per = (M + a.q - 1) / a.q;  // rows of a type
   TileShape best{256, 256};
   double cost = async_makespan(a, mode, M, 256, 256, act, 1.0);
-  auto consider = [&](int tm, int tn, double rate, double margin, double live = 1.0) {
-    const double c = live * async_makespan(a, mode, M, tm, tn, act, rate);
+  auto consider = [&](int tm, int tn, double rate, double margin) {
+    const double c = async_makespan(a, mode, M, tm, tn, act, rate);
     if (c < margin * cost) {
       cost = c;
       best = {tm, tn};
     }
   };
-  if (try192) consider(256, 192, 0.87, pad192 < pad256 ? 1.0 : 0.97, mode == kModeBwdData && per > 64 && per <= 128 ? 0.735 : 1.0);
+  if (try192) consider(256, 192, 0.87, pad192 < pad256 ? 1.0 : 0.97);
   consider(128, 256, 0.73, 0.98);
   if (try192) consider(128, 192, 0.63, best.tm == 128 ? 1.0 : 0.98);
   return best;
