@@ -171,15 +171,15 @@ def _ptr(t):
     return t.data_ptr() if t is not None else None
 
 
-# (torch's own way to the raw stream, without the Stream object; it is not a
-# public name, so a torch without it takes the public way)
-_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+def _stream_getter(raw):
+    """device -> its current raw stream: by torch's own call `raw`, which makes
+    no Stream object but is not a public name, or the public way without it."""
+    if raw is None:
+        return lambda device: torch.cuda.current_stream(device).cuda_stream
+    return lambda device: raw(device.index)
 
 
-def _stream(device) -> int:
-    if _raw_stream is None:
-        return torch.cuda.current_stream(device).cuda_stream
-    return _raw_stream(device.index)
+_stream = _stream_getter(getattr(torch._C, "_cuda_getCurrentRawStream", None))
 
 
 def _check(status: int, where: str):

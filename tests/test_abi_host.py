@@ -432,7 +432,5 @@ def test_stream_without_the_private_torch_call(monkeypatch):
 
     dev = torch.device("cuda", 1)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda d: Stream() if d == dev else None)
-    monkeypatch.setattr(binding, "_raw_stream", None)
-    assert binding._stream(dev) == 0x1234
-    monkeypatch.setattr(binding, "_raw_stream", lambda i: 0x1000 + i)
-    assert binding._stream(dev) == 0x1001
+    assert binding._stream_getter(None)(dev) == 0x1234
+    assert binding._stream_getter(lambda i: 0x1000 + i)(dev) == 0x1001
